@@ -385,9 +385,10 @@ int64_t stb_gemv_batched_workspace_bytes(int32_t n_layers, const stb_cfg_t* cons
  * Tiled 2:4 layers run on the structured-sparse matrix instruction (kept weights plus an index word as the operand,
  * Sec. 3.1 / App. C; its 32x32x32 form).
  * From a few hundred tokens on (where it is estimated to be faster) the call first expands the weights to the workspace,
- * fp16, 2 bytes a weight position (2:4: 1.125), and multiplies those: same terms, same fp32 accumulation.  A workspace of at least
- * what the other kernels need (T x (gathered salient columns and partial tiles)) but less than
- * stb_gemm_workspace_bytes() runs those instead.
+ * fp16, 2 bytes a weight position (2:4: 1.125), and multiplies those: same terms, same fp32 accumulation.  A smaller
+ * workspace, of at least what the other kernels need (T x (gathered salient columns and partial tiles)), runs those instead:
+ * stb_gemm_form says how much that is.  Results of the two differ within rounding, so a program that wants the same
+ * bits from call to call passes the same workspace size.
  * Where a (tokens x rows) tile per workgroup would not fill whole rounds of the chip, the columns are dealt to up to 16 groups of
  * workgroups that each leave an fp32 partial tile in the workspace, and a second kernel adds the partial tiles in a fixed
  * order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.
@@ -403,6 +404,21 @@ int stb_gemm(const stb_layout_t* dev, const void* X, int32_t T, void* Y, int32_t
  * including max_sal_half, which stb_tile sets), its pointers are not.  Negative stb_status on a bad
  * argument. */
 int64_t stb_gemm_workspace_bytes(const stb_layout_t* layout, int32_t T);
+
+/* What stb_gemm runs for (layout, T) when it is given a workspace of `workspace_bytes` bytes: `out->kernel` one of the
+ * values below, `out->k_groups` the number of groups that the columns are dealt to (1: no partial tiles) and
+ * `out->workspace_bytes` the scratch that this form uses.  workspace_bytes = 0 describes the form that needs least (a call
+ * with less than its out->workspace_bytes returns STB_EINVAL, or STB_ENULL without a workspace), INT64_MAX the one that
+ * runs with stb_gemm_workspace_bytes().  Host arithmetic on the size fields, as there.
+ * Errors: STB_ENULL, STB_EINVAL. */
+#define STB_GEMM_GENERIC 0     /* the row-major kernel, any N:M; a tiled layout without a prefill kernel (stb_gemm: STB_EUNSUPPORTED) */
+#define STB_GEMM_FUSED 1       /* weights expanded by the wavefronts that multiply them */
+#define STB_GEMM_EXPANDED 2    /* weights expanded to the workspace first */
+typedef struct {
+    int32_t kernel, k_groups;
+    int64_t workspace_bytes;
+} stb_gemm_form_t;
+int stb_gemm_form(const stb_layout_t* layout, int32_t T, int64_t workspace_bytes, stb_gemm_form_t* out);
 
 /* Measurement aid: reads `bytes` bytes (a multiple of 16, 16-byte aligned) of device memory with 128-bit loads
  * from every compute unit and writes one 32-bit checksum per workgroup to `sink` (device, at least 4096

@@ -58,7 +58,12 @@ class stb_layout_t(C.Structure):
     )
 
 
+class stb_gemm_form_t(C.Structure):
+    _fields_ = [("kernel", C.c_int32), ("k_groups", C.c_int32), ("workspace_bytes", C.c_int64)]
+
+
 STB_KIND_ROWMAJOR, STB_KIND_TILED = 0, 1
+STB_GEMM_GENERIC, STB_GEMM_FUSED, STB_GEMM_EXPANDED = 0, 1, 2
 
 PLANE_FIELDS = (("mask", "off_mask", "mask_bytes"), ("sign", "off_sign", "sign_bytes"),
                 ("region", "off_region", "region_bytes"), ("res_sign", "off_res", "res_bytes"),
@@ -69,7 +74,7 @@ PLANE_FIELDS = (("mask", "off_mask", "mask_bytes"), ("sign", "off_sign", "sign_b
 _LIB = None
 
 EXPORTS = ("stb_layout_sizes", "stb_layout_bind", "stb_tiled_sizes", "stb_tile", "stb_untile", "stb_tile_device", "stb_pack", "stb_pack_obc", "stb_hessian_factor", "stb_pack_obc_hybrid", "stb_pack_obc_hybrid_workspace_bytes", "stb_pack_device", "stb_pack_device_workspace_bytes", "stb_unpack", "stb_salient_columns", "stb_salient_columns_hc", "stb_layer_l2_norm", "stb_layer_nm_assignment", "stb_code24_export", "stb_code24_import", "stb_code24_index", "stb_dequant", "stb_gemv",
-           "stb_gemv_static", "stb_gemv_workspace_bytes", "stb_gemv_batched", "stb_gemv_batched_workspace_bytes", "stb_gemm", "stb_gemm_workspace_bytes", "stb_probe_read", "stb_probe_mfma", "stb_set_kernel_override", "stb_strerror", "stb_last_hip_error")
+           "stb_gemv_static", "stb_gemv_workspace_bytes", "stb_gemv_batched", "stb_gemv_batched_workspace_bytes", "stb_gemm", "stb_gemm_workspace_bytes", "stb_gemm_form", "stb_probe_read", "stb_probe_mfma", "stb_set_kernel_override", "stb_strerror", "stb_last_hip_error")
 
 
 def _lib():
@@ -142,6 +147,8 @@ def _lib():
                              C.c_void_p, C.c_int64, C.c_void_p]
     lib.stb_gemm_workspace_bytes.argtypes = [P(stb_layout_t), C.c_int32]
     lib.stb_gemm_workspace_bytes.restype = C.c_int64
+    lib.stb_gemm_form.argtypes = [P(stb_layout_t), C.c_int32, C.c_int64, P(stb_gemm_form_t)]
+    lib.stb_gemm_form.restype = C.c_int
     lib.stb_probe_read.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
     lib.stb_probe_read.restype = C.c_int
     lib.stb_probe_mfma.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
@@ -428,6 +435,12 @@ def stb_gemm_workspace_bytes(layout: stb_layout_t, T: int) -> int:
     if r < 0:
         raise StbError(int(r), "stb_gemm_workspace_bytes")
     return int(r)
+
+
+def stb_gemm_form(layout: stb_layout_t, T: int, workspace_bytes: int = 2 ** 63 - 1) -> stb_gemm_form_t:
+    out = stb_gemm_form_t()
+    _check(_lib().stb_gemm_form(C.byref(layout), T, workspace_bytes, C.byref(out)), "stb_gemm_form")
+    return out
 
 
 def stb_gemm(layout_dev: stb_layout_t, X_dev, T: int, Y_dev, y_fp32: bool = False, workspace=None,

@@ -738,18 +738,40 @@ extern "C" int stb_gemv_batched(int32_t n_layers, const stb_layout_t* const* dev
     return STB_OK;
 }
 
-extern "C" int64_t stb_gemm_workspace_bytes(const stb_layout_t* layout, int32_t T) {
+// The sizes of `layout` from its cfg and max_sal_half alone.  tiled: whether the prefill kernels of the tiled order take it.
+static int gemm_sizes(const stb_layout_t* layout, int32_t T, stb_layout_t* sizes, bool* tiled) {
     if (!layout) return STB_ENULL;
-    stb_layout_t ref;
-    int rc = layout->kind == STB_KIND_TILED ? stb_tiled_sizes(&layout->cfg, &ref)
-                                            : (layout->kind == STB_KIND_ROWMAJOR ? stb_layout_sizes(&layout->cfg, &ref) : STB_EINVAL);
+    const int rc = layout->kind == STB_KIND_TILED ? stb_tiled_sizes(&layout->cfg, sizes)
+                                                  : (layout->kind == STB_KIND_ROWMAJOR ? stb_layout_sizes(&layout->cfg, sizes) : STB_EINVAL);
     if (rc) return rc;
     if (T < 1) return STB_EINVAL;
-    if (layout->kind == STB_KIND_ROWMAJOR || !stb_tiled_supported(layout)) return 0;
-    if (layout->max_sal_half < 0 || layout->max_sal_half > 8 * ref.sal_chunks) return STB_EINVAL;
-    stb_layout_t tmp = ref;
-    tmp.max_sal_half = layout->max_sal_half;
-    return stb_tiled_gemm_workspace(&tmp, T);      // gathered salient columns of X, partial tiles of a K split
+    *tiled = layout->kind == STB_KIND_TILED && stb_tiled_supported(layout);
+    if (!*tiled) return STB_OK;
+    if (layout->max_sal_half < 0 || layout->max_sal_half > 8 * sizes->sal_chunks) return STB_EINVAL;
+    sizes->max_sal_half = layout->max_sal_half;
+    return STB_OK;
+}
+
+extern "C" int64_t stb_gemm_workspace_bytes(const stb_layout_t* layout, int32_t T) {
+    stb_layout_t sizes;
+    bool tiled = false;
+    const int rc = gemm_sizes(layout, T, &sizes, &tiled);
+    if (rc) return rc;
+    return tiled ? stb_tiled_gemm_workspace(&sizes, T) : 0;
+}
+
+extern "C" int stb_gemm_form(const stb_layout_t* layout, int32_t T, int64_t workspace_bytes, stb_gemm_form_t* out) {
+    if (!out) return STB_ENULL;
+    stb_layout_t sizes;
+    bool tiled = false;
+    const int rc = gemm_sizes(layout, T, &sizes, &tiled);
+    if (rc) return rc;
+    if (workspace_bytes < 0) return STB_EINVAL;
+    out->kernel = STB_GEMM_GENERIC;
+    out->k_groups = 1;
+    out->workspace_bytes = 0;
+    if (tiled) stb_tiled_gemm_form(&sizes, T, workspace_bytes, out);
+    return STB_OK;
 }
 
 extern "C" int stb_gemm(const stb_layout_t* dev, const void* X, int32_t T, void* Y, int32_t y_fp32,

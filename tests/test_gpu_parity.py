@@ -574,6 +574,31 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
             assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
 
 
+def test_gemm_runs_in_the_scratch_that_the_smaller_form_asks_for(torch_cuda):
+    """A program that does not want to hold expanded weights asks stb_gemm_form for the other form's scratch: the call runs in
+    exactly that, and is refused with less."""
+    torch = torch_cuda
+    n, k, T = 1290, 1152, 2000
+    _say(f"[case] gemm in the smaller scratch {n}x{k} 2:4 T={T}")
+    L = make_layer(n, k, 5, n_salient=300)
+    pm = S.PackedMatrix.pack(L["W"], L["xnorm"], L["sal_bitmap"], 2, 4, 0).to_device(tiled=True)
+    assert S.stb_gemm_form(pm.dev_layout, T).kernel == S.STB_GEMM_EXPANDED
+    least = S.stb_gemm_form(pm.dev_layout, T, 0)
+    assert least.kernel == S.STB_GEMM_FUSED and least.workspace_bytes < S.stb_gemm_workspace_bytes(pm.dev_layout, T)
+    x = make_x(T, k, 6)
+    y_ref, bound = O.matmul(x, O.unpack(_oracle_planes_from(pm), n, k, 2, 4))
+    xd = torch.from_numpy(x).cuda()
+    ws = S.new_device_scratch(least.workspace_bytes)
+    ws.fill_(0xFF)
+    yd = torch.full((T, n), float("nan"), dtype=torch.float32, device="cuda")
+    S.stb_gemm(pm.dev_layout, xd, T, yd, True, ws)
+    torch.cuda.synchronize()
+    _within_bound(yd.cpu().numpy(), y_ref, bound, "smaller form")
+    with pytest.raises(S.StbError) as e:
+        S.stb_gemm(pm.dev_layout, xd, T, yd, True, ws[:-256])
+    assert e.value.status == S.STB_EINVAL
+
+
 def test_zero_activations_and_zero_weights(torch_cuda):
     torch = torch_cuda
     n, k = 70, 256

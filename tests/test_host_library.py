@@ -573,3 +573,42 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "one GPU" in (r.stdout + r.stderr)
+
+
+@pytest.mark.parametrize("n,k,N,M,T,sal_half", [(8192, 8192, 6, 8, 2048, 9), (11008, 4096, 4, 8, 8192, 0), (8192, 28672, 2, 4, 2048, 20),
+                                                (13824, 5120, 6, 8, 64, 8), (4999, 3200, 5, 8, 100, 12), (16, 128, 3, 4, 1, 1)])
+def test_the_scratch_of_either_prefill_form_can_be_asked_for(n, k, N, M, T, sal_half):
+    """stb_gemm_form: the form that needs least and what it needs, the one that runs with stb_gemm_workspace_bytes(), and
+    where a call changes from one to the other."""
+    lay = S.stb_tiled_sizes(S.make_cfg(n, k, N, M, sal_half))
+    lay.max_sal_half = sal_half
+    full = S.stb_gemm_workspace_bytes(lay, T)
+    least, best = S.stb_gemm_form(lay, T, 0), S.stb_gemm_form(lay, T)
+    assert least.kernel == S.STB_GEMM_FUSED and least.workspace_bytes <= full
+    assert S.stb_gemm_form(lay, T, full).kernel == best.kernel and best.workspace_bytes <= full
+    for form in (least, best):
+        again = S.stb_gemm_form(lay, T, form.workspace_bytes)
+        assert (again.kernel, again.k_groups, again.workspace_bytes) == (form.kernel, form.k_groups, form.workspace_bytes)
+        # partial tiles, and expanded weights (2:4: the kept ones and 2 bits of index each), have their room
+        weights = 0 if form.kernel == S.STB_GEMM_FUSED else (1.125 if (N, M) == (2, 4) else 2) * n * k
+        assert form.workspace_bytes >= weights + (4 * form.k_groups * T * n if form.k_groups > 1 else 0)
+    if n * k >= 2 ** 25 and T >= 2048:
+        assert best.kernel == S.STB_GEMM_EXPANDED and least.workspace_bytes < full // 3
+        assert S.stb_gemm_form(lay, T, best.workspace_bytes - 1).kernel == S.STB_GEMM_FUSED
+    rm = S.stb_gemm_form(S.stb_layout_sizes(S.make_cfg(n, k, N, M, sal_half)), T, 0)
+    assert (rm.kernel, rm.k_groups, rm.workspace_bytes) == (S.STB_GEMM_GENERIC, 1, 0)
+
+
+def test_gemm_form_rejects_what_the_workspace_query_rejects():
+    lay = S.stb_tiled_sizes(S.make_cfg(32, 256, 4, 8, 3))
+    for T, room in ((0, 0), (-1, 0), (4, -1)):
+        with pytest.raises(S.StbError) as e:
+            S.stb_gemm_form(lay, T, room)
+        assert e.value.status == S.STB_EINVAL
+    lay.max_sal_half = 1000
+    with pytest.raises(S.StbError) as e:
+        S.stb_gemm_form(lay, 4, 0)
+    assert e.value.status == S.STB_EINVAL
+    out = S.stb_gemm_form_t()
+    assert S.binding._lib().stb_gemm_form(None, 4, 0, C.byref(out)) == S.STB_ENULL
+    assert S.binding._lib().stb_gemm_form(C.byref(lay), 4, 0, None) == S.STB_ENULL
