@@ -574,6 +574,37 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
             assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
 
 
+@pytest.mark.parametrize("n,k,N,M,T", [(13824, 5120, 6, 8, 64), (13184, 2560, 4, 8, 64), (13184, 2560, 2, 4, 64), (13184, 2560, 6, 8, 24),
+                                       (10880, 3072, 4, 8, 69), (5632, 1024, 2, 4, 200), (6608, 1408, 4, 8, 770), (1536, 1024, 6, 8, 770)])
+def test_an_fp32_sum_runs_over_no_more_columns_than_fill_the_chip(n, k, N, M, T, torch_cuda):
+    """How many superblocks of 512 columns an accumulator runs over, read off the result: the first column contributes 2^15,
+    four columns of every superblock 2^-10 each, a quarter of the last place of 2^15, which an accumulator that holds 2^15 loses
+    and any other keeps.  A launch of fewer than 200 workgroups (64 or 128 tokens x 256 rows) deals the columns at least to
+    as many groups as make it 256, 16 at most: error grows with the root of a sum's length."""
+    torch = torch_cuda
+    _say(f"[case] length of sums {n}x{k} {N}:{M} T={T}")
+    ns = -(-k // 512)
+    base = -(-T // (64 if T <= 64 else 128)) * -(-n // 256)
+    longest = ns if base >= 200 else -(-ns // min(16, ns, -(-256 // base)))
+    assert longest < ns
+    W = np.ones((n, k), np.float32)
+    pm = S.PackedMatrix.pack(W, np.ones(k, np.float32), np.zeros(k // 32, np.uint32), N, M, 1).to_device(tiled=True)
+    x = np.zeros(k, np.float16)
+    for c in range(0, k, 512):
+        x[c:c + 128:32] = 2.0 ** -10
+    x[0] = 2.0 ** 15
+    xd = torch.from_numpy(np.tile(x, (T, 1))).cuda()
+    y = torch.empty((T, n), dtype=torch.float32, device="cuda")
+    if T <= 32:
+        S.stb_gemv(pm.dev_layout, xd, T, y, True, S.new_device_scratch(S.stb_gemv_workspace_bytes(pm.cfg, T), zero=True))
+    else:
+        S.stb_gemm(pm.dev_layout, xd, T, y, True, S.new_device_scratch(S.stb_gemm_workspace_bytes(pm.dev_layout, T)))
+    torch.cuda.synchronize()
+    kept = (y.double() - 2.0 ** 15) * 2.0 ** 10 / 4             # superblocks outside the first sum (each adds a whole last place)
+    assert bool((kept == kept[0, 0]).all())
+    assert 1 <= ns - int(kept[0, 0]) <= longest, (ns, float(kept[0, 0]), longest)
+
+
 def test_gemm_runs_in_the_scratch_that_the_smaller_form_asks_for(torch_cuda):
     """A program that does not want to hold expanded weights asks stb_gemm_form for the other form's scratch: the call runs in
     exactly that, and is refused with less."""
