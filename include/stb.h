@@ -452,7 +452,8 @@ int stb_probe_mfma(int32_t kind, int32_t valu, int32_t steps, int32_t n_workgrou
  *   gemm_kernel  0 automatic; 1 keeps 2:4 layers on the dense-instruction prefill kernel (16x16x32 form); 2 runs any
  *                tiled layer on the 32x32x16 form of the dense kernel; 3 runs 2:4 layers on the 16x16x64 form of the
  *                sparse instruction; 4 runs any tiled layer on the kernel that shares the expanded operands of a
- *                workgroup through LDS
+ *                workgroup through LDS; 5 multiplies weights expanded to the workspace, whatever T is, 6 the same with
+ *                the columns dealt to up to 16 groups (stb_gemm_workspace_bytes and stb_gemm_form answer for the choice in force)
  * Errors: STB_EINVAL (a value outside the lists above; nothing is changed then). */
 int stb_set_kernel_override(int32_t gemv_kernel, int32_t gemv_visits, int32_t gemv_splits, int32_t gemm_kernel);
 

@@ -471,7 +471,7 @@ extern "C" int stb_kernel_override(int which) { return which >= 0 && which < 4 ?
 
 extern "C" int stb_set_kernel_override(int32_t gemv_kernel, int32_t gemv_visits, int32_t gemv_splits, int32_t gemm_kernel) {
     if (gemv_kernel < 0 || gemv_kernel > 1 || gemv_visits < 0 || gemv_visits > 8 || gemv_splits < 0 || gemv_splits > 64 ||
-        gemm_kernel < 0 || gemm_kernel > 4)
+        gemm_kernel < 0 || gemm_kernel > 6)
         return STB_EINVAL;
     g_override[0].store(gemv_kernel, std::memory_order_relaxed);
     g_override[1].store(gemv_visits, std::memory_order_relaxed);

@@ -544,11 +544,12 @@ def test_gemm_with_a_k_split_is_reproducible_and_matches_the_oracle(N, M, torch_
 
 @pytest.mark.parametrize("n,k,N,M,T,sal", [(1001, 1536, 3, 8, 700, 70), (1792, 1664, 5, 8, 260, 0), (517, 4224, 6, 8, 1030, 200), (257, 8320, 4, 8, 1500, 420),
                                            (2577, 1152, 4, 8, 769, 129), (1040, 896, 6, 8, 2049, 896),
-                                           (1800, 1664, 2, 4, 700, 83), (520, 8320, 2, 4, 1500, 0), (1290, 1152, 2, 4, 2000, 300)])
+                                           (1800, 1664, 2, 4, 700, 83), (520, 8320, 2, 4, 1500, 0), (1290, 1152, 2, 4, 2000, 300),
+                                           (1, 128, 6, 8, 1, 1), (16, 128, 2, 4, 127, 128), (255, 256, 4, 8, 129, 128), (513, 4352, 2, 4, 33, 129)])
 def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
-    """Calls of a few hundred tokens and up multiply weights expanded to the workspace: rows, tokens, column blocks and
-    salient entries past the last full tile, with and without a K split, fp16 and fp32, twice with the same bits; and, in
-    a workspace that only holds the fused kernels' scratch, those."""
+    """The product on weights expanded to the workspace, asked for whole and with a K split (the last group may hold
+    residual columns alone, or main and residual ones), beside the form that the call takes by itself: rows, tokens, column
+    blocks and salient entries past the last full tile, fp16 and fp32, twice with the same bits, in exactly the scratch asked for."""
     torch = torch_cuda
     _say(f"[case] expanded gemm {n}x{k} {N}:{M} T={T} salient={sal}")
     L = make_layer(n, k, 300 + n, n_salient=sal)
@@ -557,21 +558,28 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
     x = make_x(T, k, n)
     y_ref, bound = O.matmul(x, What)
     xd = torch.from_numpy(x).cuda()
-    need = S.stb_gemm_workspace_bytes(pm.dev_layout, T)
-    assert need >= (1.125 if (N, M) == (2, 4) else 2) * n * k     # room for the expanded weights: this call uses them when it gets it all
-    for fp32 in (False, True):
-        outs = []
-        for ws_bytes in (need, need) + ((need - 256,) if n == 1290 else ()):     # (there the fused kernels need less)
-            ws = S.new_device_scratch(ws_bytes)
-            ws.fill_(0xFF)
-            y = torch.full((T, n), float("nan"), dtype=torch.float32 if fp32 else torch.float16, device="cuda")
-            S.stb_gemm(pm.dev_layout, xd, T, y, fp32, ws)
-            torch.cuda.synchronize()
-            outs.append(y.cpu().numpy())
-            _within_bound(outs[-1], y_ref, bound, f"T={T} fp32={fp32} workspace {ws_bytes}")
-        assert outs[0].tobytes() == outs[1].tobytes()
-        if fp32:                                    # fp32 sums of exact products: far inside the fp16 bound
-            assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
+    pairs = (k + -(-sal // 128) * 128) // 128                   # the groups are multiples of 128 columns, residual ones included
+    for asked in (0, S.GEMM_WHOLE, S.GEMM_WHOLE_SPLIT):
+        with forced(gemm_kernel=asked):
+            form = S.stb_gemm_form(pm.dev_layout, T)
+            if asked:
+                assert form.kernel == S.STB_GEMM_EXPANDED
+                assert form.k_groups == (1 if asked == S.GEMM_WHOLE else -(-pairs // -(-pairs // 16)))
+                assert form.workspace_bytes >= (1.125 if (N, M) == (2, 4) else 2) * n * k + (form.k_groups > 1) * form.k_groups * T * n * 4
+            for fp32 in (False, True):
+                outs = []
+                for _ in range(2):
+                    ws = S.new_device_scratch(form.workspace_bytes)
+                    if ws is not None:
+                        ws.fill_(0xFF)
+                    y = torch.full((T, n), float("nan"), dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+                    S.stb_gemm(pm.dev_layout, xd, T, y, fp32, ws)
+                    torch.cuda.synchronize()
+                    outs.append(y.cpu().numpy())
+                    _within_bound(outs[-1], y_ref, bound, f"T={T} fp32={fp32} form {form.kernel} in {form.k_groups} groups")
+                assert outs[0].tobytes() == outs[1].tobytes()
+                if fp32:                            # fp32 sums of exact products: far inside the fp16 bound
+                    assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
 
 
 @pytest.mark.parametrize("n,k,N,M,T", [(13824, 5120, 6, 8, 64), (13184, 2560, 4, 8, 64), (13184, 2560, 2, 4, 64), (13184, 2560, 6, 8, 24),
