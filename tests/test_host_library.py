@@ -612,3 +612,16 @@ def test_gemm_form_rejects_what_the_workspace_query_rejects():
     out = S.stb_gemm_form_t()
     assert S.binding._lib().stb_gemm_form(None, 4, 0, C.byref(out)) == S.STB_ENULL
     assert S.binding._lib().stb_gemm_form(C.byref(lay), 4, 0, None) == S.STB_ENULL
+
+
+@pytest.mark.parametrize("n,k,N,M,T,sal,half,form", [
+    (8192, 8192, 6, 8, 2048, 409, 8, "expanded"), (11008, 4096, 4, 8, 8192, 204, 8, "expanded"), (4640, 1408, 4, 8, 4648, 70, 7, "expanded"),
+    (6358, 1024, 6, 8, 2877, 20, 4, "expanded"), (2690, 14208, 3, 8, 2058, 710, 9, "expanded"), (1024, 8192, 6, 8, 2048, 409, 8, "expanded"),
+    (8192, 28672, 2, 4, 2048, 1433, 9, "expanded"), (11008, 4096, 2, 4, 8192, 204, 8, "expanded"), (12339, 2048, 6, 8, 866, 102, 7, "expanded"),
+    (1904, 4096, 5, 8, 1370, 204, 8, "expanded"), (28672, 4096, 3, 8, 300, 204, 7, "fused"), (12432, 3200, 2, 4, 590, 160, 7, "fused"),
+    (11001, 4224, 4, 8, 333, 211, 7, "fused"), (5600, 4224, 5, 8, 362, 0, 0, "fused")])
+def test_the_form_of_a_prefill_call_is_the_one_measured_faster(n, k, N, M, T, sal, half, form):
+    """Shapes on which both forms were timed, on three sets of buffers in turn, and differ by 10 % or more."""
+    lay = S.stb_tiled_sizes(S.make_cfg(n, k, N, M, sal))
+    lay.max_sal_half = half
+    assert S.stb_gemm_form(lay, T).kernel == (S.STB_GEMM_EXPANDED if form == "expanded" else S.STB_GEMM_FUSED)
