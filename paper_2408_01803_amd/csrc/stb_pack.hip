@@ -365,8 +365,11 @@ __device__ inline void candidate(int t, double mx, double& q1, double& q2, bool&
 //     G_t = sum over rows and regions of (sum a)^2 / count,
 // and all G_t of a (row, block) follow from the suffix sums of one histogram over the 140 sorted break points p1(t) and
 // p2(t) = 2 p1(t).  k_search_gain computes G_t with a proven error bound; k_search_narrow keeps the candidates that
-// could still be the minimum of D_t: almost always one, and then it is the answer.  Where several are left (equal
-// partitions, tiny layers) k_exact_errors / k_exact_pick evaluate D_t for those alone, in the defined order.
+// could still be the minimum of D_t: almost always one, and then it is the answer.  Of candidates that part the block's values
+// alike, which have the same D_t bit for bit, the first is kept: the numbers of values above p1(t) and p2(t) fall with t, so two
+// candidates are alike where their sums are equal.  (Without that a layer of few distinct magnitudes evaluates all that tie:
+// 11008 x 4096 4:8 of one magnitude 7.6 ms, now 1.0; of two 7.7 and 1.8; 28672 x 8192 of 15 9.3 and 3.2.)  Where several are left
+// k_exact_errors / k_exact_pick evaluate D_t for those alone, in the defined order.
 constexpr int SC_NV = 70;                  // candidates that are not skipped when the block has a non-zero weight: 2 c_t <= 0.9
 constexpr int SC_ROWS = 32;                // rows whose histograms are in LDS at a time
 constexpr int SC_STEPS = 8;                // ... and how often: rows per workgroup = SC_ROWS * SC_STEPS
@@ -406,11 +409,12 @@ __device__ inline int search_bin(float a, float gs, float go, const float* tau) 
 // A load instruction covers 8 rows x 128 bytes, so that few lanes of one atomic instruction share a row's bin (with 2 rows
 // x 512 bytes and a histogram for either break point: 1281 us).  Bound by LDS accesses (about 200 cycles a row and block).
 // 28672 x 8192 at 4:8: 0.81 ms (1.14 with loops around every bin search), against 21.7 ms for evaluating every candidate in the defined order.
-__global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ gain) {
+__global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ gain, unsigned long long* __restrict__ above) {
     __shared__ unsigned long long hist[SC_ROWS * SC_BINS];
     __shared__ double inv[256];            // 1 / count (a count is at most 128; 8 bits are read)
     __shared__ float tau[2 * SC_NV + 2];
     double* const part = reinterpret_cast<double*>(hist);      // (after the last step)
+    uint32_t* const part_n = reinterpret_cast<uint32_t*>(part + 4 * SC_NV);
     const int tid = threadIdx.x, q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
     const float mxf = __uint_as_float(a.mxbits[q]);
     if (mxf == 0.0f) return;               // nothing kept and non-salient, or all zero: every candidate is the same
@@ -443,6 +447,7 @@ __global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ 
     const double step = (0.9 - 0.1) / 159.0;
     const bool tiny = !(mxf > 1e-30f);     // (or not a number: the loops end all the same)
     double g_t = 0.0;
+    uint32_t n_t = 0;                      // values above p1(t) and above p2(t)
     const float gs = (float)(1.0 / (step * mx)), go = (float)(1.0 - 0.1 / step);
     for (int st = 0; st < SC_STEPS; st++) {
         const int i0 = (chunk * SC_STEPS + st) * SC_ROWS;
@@ -492,6 +497,7 @@ __global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ 
                 const unsigned long long* h = hist + r * SC_BINS;
                 const unsigned long long all = h[0], above1 = h[pos1 + 1], above2 = h[pos2 + 1];
                 const unsigned long long mid = above1 - above2, low = all - above1;
+                n_t += (uint32_t)(above1 >> 44) + (uint32_t)(above2 >> 44);
                 const double s0 = sum_of(low), s1 = sum_of(mid), s2 = sum_of(above2);
                 g_t += s0 * s0 * inv[(low >> 44) & 255] + s1 * s1 * inv[(mid >> 44) & 255] + s2 * s2 * inv[(above2 >> 44) & 255];
             }
@@ -500,15 +506,18 @@ __global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ 
         for (int e = tid; e < SC_ROWS * SC_BINS; e += 320) hist[e] = 0;
         __syncthreads();
     }
-    if (tid < 4 * SC_NV) part[tid] = g_t;
+    if (tid < 4 * SC_NV) { part[tid] = g_t; part_n[tid] = n_t; }
     __syncthreads();
-    if (tid < SC_NV)                                           // in units of (mx / 2^36)^2
+    if (tid < SC_NV) {                                         // in units of (mx / 2^36)^2
         unsafeAtomicAdd(gain + (size_t)q * SC_NV + tid, part[tid] + part[SC_NV + tid] + part[2 * SC_NV + tid] + part[3 * SC_NV + tid]);
+        atomicAdd(above + (size_t)q * SC_NV + tid, (unsigned long long)part_n[tid] + part_n[SC_NV + tid] + part_n[2 * SC_NV + tid] + part_n[3 * SC_NV + tid]);
+    }
 }
 
-// One thread per block: the candidates whose G_t is within the error bounds (taken four times over) of the largest.  One
-// left: it is the answer.  Several: their bits go to the block's mask for the exact evaluation.
-__global__ void k_search_narrow(PK a, const double* __restrict__ gain, uint32_t* __restrict__ left) {
+// One thread per block: the candidates whose G_t is within the error bounds (taken four times over) of the largest, the first of
+// those that part the values alike.  One left: it is the answer.  Several: their bits go to the block's mask for the exact
+// evaluation.
+__global__ void k_search_narrow(PK a, const double* __restrict__ gain, const unsigned long long* __restrict__ above, uint32_t* __restrict__ left) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= a.nb) return;
     uint32_t* mask = left + (size_t)q * SC_MASKW;
@@ -522,8 +531,14 @@ __global__ void k_search_narrow(PK a, const double* __restrict__ gain, uint32_t*
     const double K = (double)a.cnt[q] * 4722366482869645213696.0;                                  // 2^72
     const double slack = 4.0 * (1.0 / 68719476736.0 + (4.0 * (double)a.n + 200.0) / 9007199254740992.0) * K;
     int many = 0, first = 0;
-    for (int t = SC_NV - 1; t >= 0; t--)
-        if (g[t] >= best - slack) { many++; first = t; mask[t >> 5] |= 1u << (t & 31); }
+    unsigned long long kept = 0;
+    for (int t = 0; t < SC_NV; t++) {
+        const unsigned long long n = above[(size_t)q * SC_NV + t];
+        if (!(g[t] >= best - slack) || (many > 0 && n == kept)) continue;
+        if (many++ == 0) first = t;
+        kept = n;
+        mask[t >> 5] |= 1u << (t & 31);
+    }
     if (many == 1) {
         bool skip;
         candidate(first, mx, a.p12[2 * q], a.p12[2 * q + 1], skip);
@@ -870,7 +885,7 @@ inline int64_t up256(int64_t v) { return (v + 255) / 256 * 256; }
 
 struct WsPlan {
     int64_t status, rs, cols, rowacc, stats, mxbits, cnt, p12, hist, sel, err, total;
-    int64_t err_bytes;          // gains of all blocks (k_search_gain), then errors of the remaining candidates
+    int64_t err_bytes;          // gains and counts of all blocks (k_search_gain), then errors of the remaining candidates
 };
 
 WsPlan plan_workspace(const stb_cfg_t& c, int per_block) {
@@ -887,11 +902,11 @@ WsPlan plan_workspace(const stb_cfg_t& c, int per_block) {
     p.p12 = o; o += up256(nb * 16);
     p.hist = o; o += up256(nb * 2 * 256 * 4);
     p.sel = o; o += up256(nb * 16);
-    // the gains of all blocks, then candidate errors: as many blocks at once as fit into 1 GiB, at least one
+    // the gains and counts of all blocks, then candidate errors: as many blocks at once as fit into 1 GiB, at least one
     const int64_t per_block_bytes = n * CAND * 8;
     int64_t batch = (1ll << 30) / per_block_bytes;
     batch = batch < 1 ? 1 : (batch > nb ? nb : batch);
-    p.err_bytes = c.region_mode != 0 ? 0 : batch * per_block_bytes > nb * SC_NV * 8 ? batch * per_block_bytes : nb * SC_NV * 8;
+    p.err_bytes = c.region_mode != 0 ? 0 : batch * per_block_bytes > nb * SC_NV * 16 ? batch * per_block_bytes : nb * SC_NV * 16;
     p.err = o; o += up256(p.err_bytes);
     p.total = o;
     return p;
@@ -1017,10 +1032,11 @@ static int search_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream
     auto ok = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; return e == hipSuccess; };
     double* const err = (double*)(ws + wp.err);
     uint32_t* const left = a.hist;                             // (nb * 512 words; the tertile split alone uses them otherwise)
-    ok(hipMemsetAsync(err, 0, (size_t)a.nb * SC_NV * 8, st));
+    unsigned long long* const above = (unsigned long long*)(err + (size_t)a.nb * SC_NV);       // behind the gains
+    ok(hipMemsetAsync(err, 0, (size_t)a.nb * SC_NV * 16, st));
     const int rows = SC_ROWS * SC_STEPS;
-    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(320), 0, st, a, err);
-    hipLaunchKernelGGL(k_search_narrow, dim3((a.nb + 63) / 64), dim3(64), 0, st, a, err, left);
+    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(320), 0, st, a, err, above);
+    hipLaunchKernelGGL(k_search_narrow, dim3((a.nb + 63) / 64), dim3(64), 0, st, a, err, above, left);
     ok(hipGetLastError());
     std::vector<uint32_t> mask((size_t)a.nb * SC_MASKW);
     ok(hipMemcpyAsync(mask.data(), left, mask.size() * 4, hipMemcpyDeviceToHost, st));

@@ -8,6 +8,7 @@ import hashlib
 import json
 import os
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -178,6 +179,39 @@ def test_device_packer_break_points_where_candidates_are_close(n, values, torch_
     pm = _pack_on_device(torch_cuda, W, xnorm, bitmap, 4, 8, 0)
     for name, v in ref.items():
         assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+
+
+@pytest.mark.parametrize("levels", [1, 2, 15])
+def test_device_packer_takes_no_longer_where_candidates_tie(levels, torch_cuda):
+    """A layer of few distinct magnitudes, on which most candidates of the break-point search part the weights alike: the host's
+    bytes, in at most three times the time of a layer of normal weights (evaluating all that tie took five to eight times)."""
+    torch = torch_cuda
+    n, k = 5504, 2048
+    L = make_layer(n, k, 41)
+    _say(f"[case] pack {n}x{k} of {levels} magnitudes")
+    top = np.abs(L["W"]).max()
+    few = (np.sign(L["W"]) * np.ceil(np.abs(L["W"]) / top * levels) * (top / levels)).astype(np.float32)
+    times = {}
+    for name, W in (("normal", L["W"]), ("few", few)):
+        Wd, xd = torch.from_numpy(W).cuda(), torch.from_numpy(L["xnorm"]).cuda()
+        bd = torch.from_numpy(L["sal_bitmap"].view(np.int32)).cuda()
+        cfg = S.make_cfg(n, k, 4, 8, len(L["sal_cols"]), 0)
+        lay = S.stb_layout_sizes(cfg)
+        img, ws = S.new_device_scratch(lay.image_bytes), S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg))
+        S.stb_layout_bind(lay, img.data_ptr())
+        each = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            S.stb_pack_device(Wd, xd, bd, lay, False, ws)             # (waits for its kernels)
+            each.append(time.perf_counter() - t0)
+        times[name] = min(each)
+        host = S.PackedMatrix.pack(W, L["xnorm"], L["sal_bitmap"], 4, 8, 0)
+        got = img.cpu().numpy()
+        for field, off, size in S.PLANE_FIELDS:
+            o, sz = getattr(lay, off), getattr(lay, size)
+            assert (got[o:o + sz] == host.plane(field)).all(), (name, field)
+    assert times["few"] <= 3.0 * times["normal"], times
 
 
 TILE_CASES = [c for c in PACK_CASES if _tiled_ok(c[2], c[3])]
