@@ -15,8 +15,10 @@ until the hand-written wait, so they must not be copied in between.  The compile
 registers; once it spills vector registers to scratch it may save exactly such a register, and the kernel computes
 with what was there before the load (seen once with a tighter occupancy bound: wrong numbers, no fault).
 `spilled_asm_kernels` lists the kernels that spill a vector register straight after one of their `asm` loads wrote it.
+A register move does the same without a spill: a branch inside a loop with loads in flight (around a rare step, say) made
+the compiler give values new registers ahead of the wait.  `copied_asm_kernels` lists the kernels with such a move.
 
-`build()` runs both checks on every device source and fails on a finding; tests call them too.
+`build()` runs the checks on every device source and fails on a finding; tests call them too.
 """
 from __future__ import annotations
 
@@ -177,6 +179,43 @@ def spilled_asm_kernels(isa_text: str) -> List[Tuple[str, List[int]]]:
     return [(k, sorted(v)) for k, v in found.items()]
 
 
+_COPY = ("v_mov_b32", "v_mov_b64", "v_accvgpr_write", "v_accvgpr_read", "v_accvgpr_mov")
+
+
+def copied_asm_kernels(isa_text: str) -> List[Tuple[str, List[int]]]:
+    """(kernel, registers) for every kernel that moves a vector register which, in program order, an asm load wrote and no
+    vector-memory wait has followed."""
+    found: Dict[str, set] = {}
+    cur, in_asm, flying = None, False, set()
+    for raw in isa_text.splitlines():
+        s = raw.strip()
+        if raw and not raw[0].isspace() and not raw.startswith((".", ";")):
+            cur, flying = raw.split(":")[0], set()
+            continue
+        if s.startswith(";;#ASM"):
+            in_asm = s.startswith(";;#ASMSTART")
+            continue
+        t = s.split(";")[0].strip()
+        if not t or t.startswith("."):
+            continue
+        op = t.split()[0]
+        if op == "s_waitcnt":
+            if "vmcnt" in t:
+                flying = set()                              # whatever was in flight has been waited for (or counted) here
+        elif op.startswith(_VMEM):
+            if "load" in op and "lds" not in op:
+                dst = _vregs(_operands(t)[0])
+                flying = flying | dst if in_asm else flying - dst
+        elif op.startswith(("v_", "ds_read", "ds_load")):
+            ops = _operands(t)
+            if op.startswith(_COPY):
+                hit = _vregs(",".join(ops[1:])) & flying
+                if hit:
+                    found.setdefault(cur, set()).update(hit)
+            flying = flying - _vregs(ops[0] if ops else "")
+    return [(k, sorted(v)) for k, v in found.items()]
+
+
 def compile_to_isa(source: str, out_path: str, hipcc: str, flags: List[str]) -> str:
     cmd = [hipcc, *flags, "-S", "--offload-device-only", "-o", out_path, source]
     subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
@@ -185,8 +224,10 @@ def compile_to_isa(source: str, out_path: str, hipcc: str, flags: List[str]) -> 
 
 
 def check_source(source: str, build_dir: str, hipcc: str, flags: List[str]) -> List[tuple]:
-    """Findings of both checks for one device source (empty: clean)."""
+    """Findings of the three checks for one device source (empty: clean)."""
     out = os.path.join(build_dir, os.path.basename(source) + ".s")
     text = compile_to_isa(source, out, hipcc, flags)
     return hazards(text) + [(0, f"spills v{regs}", 0, f"kernel {name}: destinations of its asm loads", -1)
-                            for name, regs in spilled_asm_kernels(text)]
+                            for name, regs in spilled_asm_kernels(text)] + \
+        [(0, f"copies v{regs}", 0, f"kernel {name}: destinations of its asm loads, ahead of the wait", -1)
+         for name, regs in copied_asm_kernels(text)]

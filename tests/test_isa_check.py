@@ -118,6 +118,45 @@ def test_a_spill_of_a_value_computed_after_the_wait_is_no_finding():
     assert isa_check.spilled_asm_kernels(SPILL_OF_A_COMPUTED_VALUE) == []
 
 
+COPY_OF_A_LOAD_IN_FLIGHT = """
+kernel:
+\t;;#ASMSTART
+\tglobal_load_dwordx2 v[10:11], v1, s[4:5]
+\t;;#ASMEND
+\tv_add_u32_e32 v2, v3, v4
+\tv_mov_b32_e32 v20, v11
+\t;;#ASMSTART
+\ts_waitcnt vmcnt(0)
+\t;;#ASMEND
+\ts_endpgm
+"""
+
+COPIES_THAT_ARE_FINE = """
+kernel:
+\t;;#ASMSTART
+\tglobal_load_dwordx2 v[10:11], v1, s[4:5]
+\t;;#ASMEND
+\tv_mov_b32_e32 v20, v12
+\t;;#ASMSTART
+\ts_waitcnt vmcnt(0)
+\t;;#ASMEND
+\tv_mov_b32_e32 v20, v11
+\tglobal_load_dword v13, v1, s[4:5]
+\ts_endpgm
+other:
+\tv_accvgpr_write_b32 a0, v13
+\ts_endpgm
+"""
+
+
+def test_a_move_of_a_register_that_an_asm_load_still_writes_is_found():
+    assert isa_check.copied_asm_kernels(COPY_OF_A_LOAD_IN_FLIGHT) == [("kernel", [11])]
+
+
+def test_moves_of_other_registers_and_after_the_wait_are_no_finding():
+    assert isa_check.copied_asm_kernels(COPIES_THAT_ARE_FINE) == []
+
+
 def test_the_device_sources_of_the_package_are_clean(tmp_path):
     inc = ["-I" + os.path.join(stb_build.ROOT, "include"), "-I" + stb_build.CSRC]
     srcs = [os.path.join(stb_build.CSRC, s) for s in stb_build.DEVICE_SOURCES]
