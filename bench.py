@@ -45,13 +45,13 @@ ROW_POOL_BYTES = 600 << 20     # per-layer rotation of the breakdown rows: more 
 # runs, scaled by what the same counters read for a copy of known size); the summaries under profiles/ give the runs.
 # None = not measured for the build that is checked in.
 # Decode: 94.50 MB read + 0.26 MB written per launch, average of the step's four launches
-# (profiles/gemv24_group_kernel_workload5_decode_b1.md).  Prefill: bytes read + written per launch of the cases that were
-# measured, keyed by (T, n, k) (profiles/gemm_kernels_workloads4_5_prefill.md).
+# (profiles/gemv24_group_kernel_workload5_decode_b1.md).  Prefill: bytes read + written per call (expansion, product and the
+# reduction of a K split) of the cases that were measured, keyed by (T, n, k) (profiles/expanded_prefill_and_device_packer.md).
 MEASURED_DECODE_TRAFFIC_BYTES_PER_LAUNCH = 94_760_000
 MEASURED_GEMM_TRAFFIC_BYTES_PER_LAUNCH = {
-    (2048, 4096, 4096): 89_200_000, (8192, 4096, 4096): 421_500_000, (2048, 11008, 4096): 245_900_000,
-    (8192, 11008, 4096): 1_151_000_000, (2048, 8192, 8192): 387_000_000, (2048, 1024, 8192): 75_100_000,
-    (2048, 28672, 8192): 1_164_600_000, (2048, 8192, 28672): 1_092_100_000,
+    (2048, 4096, 4096): 255_600_000, (8192, 4096, 4096): 884_000_000, (2048, 11008, 4096): 692_600_000,
+    (8192, 11008, 4096): 2_327_000_000, (2048, 8192, 8192): 958_900_000, (2048, 1024, 8192): 200_600_000,
+    (2048, 28672, 8192): 3_269_800_000, (2048, 8192, 28672): 3_031_600_000,
 }
 
 # The calls of one decode step over workload 5, by layer name: layers of a group share their input vector.
@@ -179,10 +179,18 @@ def pack_spec(S, make_layer, spec, torch=None):
     return pm
 
 
-def gemm_kernel_name(spec):
-    if (spec.N, spec.M) == (2, 4):
-        return "gemm24_wide_kernel (v_smfmac_f32_32x32x32_f16)"
-    return "gemm_tiled_kernel (v_mfma_f32_16x16x32_f16)"
+def gemm_kernel_name(S, spec, layout, T):
+    """The product's kernel, as the library says which form it takes."""
+    form = S.stb_gemm_form(layout, T)
+    if form.kernel == S.STB_GEMM_GENERIC:
+        return "gemm_generic_kernel"
+    sparse = (spec.N, spec.M) == (2, 4)
+    split = f", {form.k_groups} K groups" if form.k_groups > 1 else ""
+    if form.kernel == S.STB_GEMM_EXPANDED:
+        return f"gemm_panel_kernel ({'v_smfmac_f32_16x16x64_f16' if sparse else 'v_mfma_f32_16x16x32_f16'}{split}) on weights that gemm_prepare_kernel expands"
+    if sparse:
+        return f"gemm24_kernel (v_smfmac_f32_16x16x64_f16{split})" if T <= 64 else f"gemm24_wide_kernel (v_smfmac_f32_32x32x32_f16{split})"
+    return f"gemm_tiled_kernel (v_mfma_f32_16x16x32_f16{split})"
 
 
 def main():
@@ -353,7 +361,7 @@ def main():
             tf = flops / med / 1e6
             row = dict(workload=cfg, layer=spec.name, T=T, n=spec.n, k=spec.k, nm=f"{spec.N}:{spec.M}",
                        us=round(med, 1), us_best=round(best, 1), tflops=round(tf, 2),
-                       frac_of_f16_mfma_peak=round(tf / MFMA_F16_PEAK_TFLOPS, 4), kernel=gemm_kernel_name(spec))
+                       frac_of_f16_mfma_peak=round(tf / MFMA_F16_PEAK_TFLOPS, 4), kernel=gemm_kernel_name(S, spec, pm.dev_layout, T))
             if (spec.N, spec.M) == (2, 4):
                 # the sparse instruction multiplies the kept weights only: 2*T*n*k*N/M flops are executed, and
                 # `tflops` (2*T*n*k) is the dense-equivalent rate

@@ -383,15 +383,15 @@ int64_t stb_gemv_batched_workspace_bytes(int32_t n_layers, const stb_cfg_t* cons
  * the gathered salient columns of X, which the call first writes to the workspace); the row-major kind runs a
  * generic kernel for any N:M (the two terms of a salient weight go through two contractions there too).
  * Tiled 2:4 layers run on the structured-sparse matrix instruction (kept weights plus an index word as the operand,
- * Sec. 3.1 / App. C; its 32x32x32 form).
+ * Sec. 3.1 / App. C; its 16x16x64 form up to 64 tokens and on expanded weights, its 32x32x32 form otherwise).
  * From a few hundred tokens on (where it is estimated to be faster) the call first expands the weights to the workspace,
  * fp16, 2 bytes a weight position (2:4: 1.125), and multiplies those: same terms, same fp32 accumulation.  A smaller
  * workspace, of at least what the other kernels need (T x (gathered salient columns and partial tiles)), runs those instead:
  * stb_gemm_form says how much that is.  Results of the two differ within rounding, so a program that wants the same
  * bits from call to call passes the same workspace size.
- * Where a (tokens x rows) tile per workgroup would not fill whole rounds of the chip, the columns are dealt to up to 16 groups of
- * workgroups that each leave an fp32 partial tile in the workspace, and a second kernel adds the partial tiles in a fixed
- * order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.
+ * Where a (tokens x rows) tile per workgroup would not fill the chip, or not whole rounds of it, the columns are dealt to up to 16
+ * groups of workgroups that each leave an fp32 partial tile in the workspace, and a second kernel adds the partial tiles in a
+ * fixed order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.
  * X: device fp16 [T][k], finite values (a padding column or token re-reads valid elements of X and meets zero
  * weights or an output that is never stored).  Y: device [T][n], fp16 or fp32, fully overwritten.  workspace: device scratch of at
  * least stb_gemm_workspace_bytes() bytes, 256-byte aligned (may be NULL when that is 0); it needs no

@@ -1154,7 +1154,7 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
 }
 
 // ------------------------------------------------------------------------------------------------
-// stb_tile in device memory: the record permutation of the host routine, one thread per (row, block)
+// stb_tile in device memory: the record permutation of the host routine, a wavefront a tile of 64 records
 // ------------------------------------------------------------------------------------------------
 namespace {
 
