@@ -391,7 +391,8 @@ int64_t stb_gemv_batched_workspace_bytes(int32_t n_layers, const stb_cfg_t* cons
  * bits from call to call passes the same workspace size.
  * Where a (tokens x rows) tile per workgroup would not fill the chip, or not whole rounds of it, the columns are dealt to up to 16
  * groups of workgroups that each leave an fp32 partial tile in the workspace, and a second kernel adds the partial tiles in a
- * fixed order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.
+ * fixed order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.  fp32 outputs are split
+ * further where that shortens the sums of an idle chip, so an fp16 output need not be the rounded fp32 one of another call.
  * X: device fp16 [T][k], finite values (a padding column or token re-reads valid elements of X and meets zero
  * weights or an output that is never stored).  Y: device [T][n], fp16 or fp32, fully overwritten.  workspace: device scratch of at
  * least stb_gemm_workspace_bytes() bytes, 256-byte aligned (may be NULL when that is 0); it needs no
@@ -400,12 +401,12 @@ int64_t stb_gemv_batched_workspace_bytes(int32_t n_layers, const stb_cfg_t* cons
 int stb_gemm(const stb_layout_t* dev, const void* X, int32_t T, void* Y, int32_t y_fp32,
              void* workspace, int64_t workspace_bytes, void* stream);
 
-/* Scratch bytes stb_gemm needs for (layout, T): the size fields of `layout` are read (for the tiled kind
+/* Scratch bytes stb_gemm needs for (layout, T), whatever y_fp32 is: the size fields of `layout` are read (for the tiled kind
  * including max_sal_half, which stb_tile sets), its pointers are not.  Negative stb_status on a bad
  * argument. */
 int64_t stb_gemm_workspace_bytes(const stb_layout_t* layout, int32_t T);
 
-/* What stb_gemm runs for (layout, T) when it is given a workspace of `workspace_bytes` bytes: `out->kernel` one of the
+/* What stb_gemm runs for (layout, T, y_fp32) when it is given a workspace of `workspace_bytes` bytes: `out->kernel` one of the
  * values below, `out->k_groups` the number of groups that the columns are dealt to (1: no partial tiles) and
  * `out->workspace_bytes` the scratch that this form uses.  workspace_bytes = 0 describes the form that needs least (a call
  * with less than its out->workspace_bytes returns STB_EINVAL, or STB_ENULL without a workspace), INT64_MAX the one that
@@ -418,7 +419,7 @@ typedef struct {
     int32_t kernel, k_groups;
     int64_t workspace_bytes;
 } stb_gemm_form_t;
-int stb_gemm_form(const stb_layout_t* layout, int32_t T, int64_t workspace_bytes, stb_gemm_form_t* out);
+int stb_gemm_form(const stb_layout_t* layout, int32_t T, int32_t y_fp32, int64_t workspace_bytes, stb_gemm_form_t* out);
 
 /* Measurement aid: reads `bytes` bytes (a multiple of 16, 16-byte aligned) of device memory with 128-bit loads
  * from every compute unit and writes one 32-bit checksum per workgroup to `sink` (device, at least 4096

@@ -147,7 +147,7 @@ def _lib():
                              C.c_void_p, C.c_int64, C.c_void_p]
     lib.stb_gemm_workspace_bytes.argtypes = [P(stb_layout_t), C.c_int32]
     lib.stb_gemm_workspace_bytes.restype = C.c_int64
-    lib.stb_gemm_form.argtypes = [P(stb_layout_t), C.c_int32, C.c_int64, P(stb_gemm_form_t)]
+    lib.stb_gemm_form.argtypes = [P(stb_layout_t), C.c_int32, C.c_int32, C.c_int64, P(stb_gemm_form_t)]
     lib.stb_gemm_form.restype = C.c_int
     lib.stb_probe_read.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
     lib.stb_probe_read.restype = C.c_int
@@ -437,9 +437,9 @@ def stb_gemm_workspace_bytes(layout: stb_layout_t, T: int) -> int:
     return int(r)
 
 
-def stb_gemm_form(layout: stb_layout_t, T: int, workspace_bytes: int = 2 ** 63 - 1) -> stb_gemm_form_t:
+def stb_gemm_form(layout: stb_layout_t, T: int, y_fp32: bool = False, workspace_bytes: int = 2 ** 63 - 1) -> stb_gemm_form_t:
     out = stb_gemm_form_t()
-    _check(_lib().stb_gemm_form(C.byref(layout), T, workspace_bytes, C.byref(out)), "stb_gemm_form")
+    _check(_lib().stb_gemm_form(C.byref(layout), T, int(y_fp32), workspace_bytes, C.byref(out)), "stb_gemm_form")
     return out
 
 

@@ -760,17 +760,17 @@ extern "C" int64_t stb_gemm_workspace_bytes(const stb_layout_t* layout, int32_t 
     return tiled ? stb_tiled_gemm_workspace(&sizes, T) : 0;
 }
 
-extern "C" int stb_gemm_form(const stb_layout_t* layout, int32_t T, int64_t workspace_bytes, stb_gemm_form_t* out) {
+extern "C" int stb_gemm_form(const stb_layout_t* layout, int32_t T, int32_t y_fp32, int64_t workspace_bytes, stb_gemm_form_t* out) {
     if (!out) return STB_ENULL;
     stb_layout_t sizes;
     bool tiled = false;
     const int rc = gemm_sizes(layout, T, &sizes, &tiled);
     if (rc) return rc;
-    if (workspace_bytes < 0) return STB_EINVAL;
+    if (workspace_bytes < 0 || (y_fp32 != 0 && y_fp32 != 1)) return STB_EINVAL;
     out->kernel = STB_GEMM_GENERIC;
     out->k_groups = 1;
     out->workspace_bytes = 0;
-    if (tiled) stb_tiled_gemm_form(&sizes, T, workspace_bytes, out);
+    if (tiled) stb_tiled_gemm_form(&sizes, T, y_fp32, workspace_bytes, out);
     return STB_OK;
 }
 

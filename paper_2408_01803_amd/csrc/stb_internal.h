@@ -59,7 +59,7 @@ int stb_tiled_gemm(const stb_layout_t* L, const void* X, int T, void* Y, int y_f
                    int64_t workspace_bytes, void* stream, int* hip_err);
 int64_t stb_tiled_gemm_workspace(const stb_layout_t* L, int T);
 // What that call runs in workspace_bytes bytes (an aligned workspace).
-void stb_tiled_gemm_form(const stb_layout_t* L, int T, int64_t workspace_bytes, stb_gemm_form_t* out);
+void stb_tiled_gemm_form(const stb_layout_t* L, int T, int y_fp32, int64_t workspace_bytes, stb_gemm_form_t* out);
 // Host: the derived tables of the tiled order (padded bitmap and prefix, table of salient columns, maxima) from the
 // row-major bitmap and prefix; the output arrays hold tl->salmap_bytes, tl->salprefix_bytes, tl->saltab_bytes.
 int stb_host_tiled_tables(const stb_layout_t* tl, const uint32_t* bitmap, const uint32_t* prefix, uint32_t* bitmap_out,

@@ -595,12 +595,12 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
     pairs = (k + -(-sal // 128) * 128) // 128                   # the groups are multiples of 128 columns, residual ones included
     for asked in (0, S.GEMM_WHOLE, S.GEMM_WHOLE_SPLIT):
         with forced(gemm_kernel=asked):
-            form = S.stb_gemm_form(pm.dev_layout, T)
-            if asked:
-                assert form.kernel == S.STB_GEMM_EXPANDED
-                assert form.k_groups == (1 if asked == S.GEMM_WHOLE else -(-pairs // -(-pairs // 16)))
-                assert form.workspace_bytes >= (1.125 if (N, M) == (2, 4) else 2) * n * k + (form.k_groups > 1) * form.k_groups * T * n * 4
             for fp32 in (False, True):
+                form = S.stb_gemm_form(pm.dev_layout, T, fp32)
+                if asked:
+                    assert form.kernel == S.STB_GEMM_EXPANDED
+                    assert form.k_groups == (1 if asked == S.GEMM_WHOLE else -(-pairs // -(-pairs // 16)))
+                    assert form.workspace_bytes >= (1.125 if (N, M) == (2, 4) else 2) * n * k + (form.k_groups > 1) * form.k_groups * T * n * 4
                 outs = []
                 for _ in range(2):
                     ws = S.new_device_scratch(form.workspace_bytes)
@@ -621,7 +621,7 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
 def test_an_fp32_sum_runs_over_no_more_columns_than_fill_the_chip(n, k, N, M, T, torch_cuda):
     """How many superblocks of 512 columns an accumulator runs over, read off the result: the first column contributes 2^15,
     four columns of every superblock 2^-10 each, a quarter of the last place of 2^15, which an accumulator that holds 2^15 loses
-    and any other keeps.  A launch of fewer than 200 workgroups (64 or 128 tokens x 256 rows) deals the columns at least to
+    and any other keeps.  A launch with fp32 outputs of fewer than 200 workgroups (64 or 128 tokens x 256 rows) deals the columns at least to
     as many groups as make it 256, 16 at most: error grows with the root of a sum's length."""
     torch = torch_cuda
     _say(f"[case] length of sums {n}x{k} {N}:{M} T={T}")
@@ -655,8 +655,8 @@ def test_gemm_runs_in_the_scratch_that_the_smaller_form_asks_for(torch_cuda):
     _say(f"[case] gemm in the smaller scratch {n}x{k} 2:4 T={T}")
     L = make_layer(n, k, 5, n_salient=300)
     pm = S.PackedMatrix.pack(L["W"], L["xnorm"], L["sal_bitmap"], 2, 4, 0).to_device(tiled=True)
-    assert S.stb_gemm_form(pm.dev_layout, T).kernel == S.STB_GEMM_EXPANDED
-    least = S.stb_gemm_form(pm.dev_layout, T, 0)
+    assert S.stb_gemm_form(pm.dev_layout, T, True).kernel == S.STB_GEMM_EXPANDED
+    least = S.stb_gemm_form(pm.dev_layout, T, True, 0)
     assert least.kernel == S.STB_GEMM_FUSED and least.workspace_bytes < S.stb_gemm_workspace_bytes(pm.dev_layout, T)
     x = make_x(T, k, 6)
     y_ref, bound = O.matmul(x, O.unpack(_oracle_planes_from(pm), n, k, 2, 4))

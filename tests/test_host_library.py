@@ -583,35 +583,36 @@ def test_the_scratch_of_either_prefill_form_can_be_asked_for(n, k, N, M, T, sal_
     lay = S.stb_tiled_sizes(S.make_cfg(n, k, N, M, sal_half))
     lay.max_sal_half = sal_half
     full = S.stb_gemm_workspace_bytes(lay, T)
-    least, best = S.stb_gemm_form(lay, T, 0), S.stb_gemm_form(lay, T)
-    assert least.kernel == S.STB_GEMM_FUSED and least.workspace_bytes <= full
-    assert S.stb_gemm_form(lay, T, full).kernel == best.kernel and best.workspace_bytes <= full
-    for form in (least, best):
-        again = S.stb_gemm_form(lay, T, form.workspace_bytes)
-        assert (again.kernel, again.k_groups, again.workspace_bytes) == (form.kernel, form.k_groups, form.workspace_bytes)
-        # partial tiles, and expanded weights (2:4: the kept ones and 2 bits of index each), have their room
-        weights = 0 if form.kernel == S.STB_GEMM_FUSED else (1.125 if (N, M) == (2, 4) else 2) * n * k
-        assert form.workspace_bytes >= weights + (4 * form.k_groups * T * n if form.k_groups > 1 else 0)
-    if n * k >= 2 ** 25 and T >= 2048:
-        assert best.kernel == S.STB_GEMM_EXPANDED and least.workspace_bytes < full // 3
-        assert S.stb_gemm_form(lay, T, best.workspace_bytes - 1).kernel == S.STB_GEMM_FUSED
-    rm = S.stb_gemm_form(S.stb_layout_sizes(S.make_cfg(n, k, N, M, sal_half)), T, 0)
+    for fp32 in (False, True):
+        least, best = S.stb_gemm_form(lay, T, fp32, 0), S.stb_gemm_form(lay, T, fp32)
+        assert least.kernel == S.STB_GEMM_FUSED and least.workspace_bytes <= full
+        assert S.stb_gemm_form(lay, T, fp32, full).kernel == best.kernel and best.workspace_bytes <= full
+        for form in (least, best):
+            again = S.stb_gemm_form(lay, T, fp32, form.workspace_bytes)
+            assert (again.kernel, again.k_groups, again.workspace_bytes) == (form.kernel, form.k_groups, form.workspace_bytes)
+            # partial tiles, and expanded weights (2:4: the kept ones and 2 bits of index each), have their room
+            weights = 0 if form.kernel == S.STB_GEMM_FUSED else (1.125 if (N, M) == (2, 4) else 2) * n * k
+            assert form.workspace_bytes >= weights + (4 * form.k_groups * T * n if form.k_groups > 1 else 0)
+        if n * k >= 2 ** 25 and T >= 2048:
+            assert best.kernel == S.STB_GEMM_EXPANDED and least.workspace_bytes < full // 3
+            assert S.stb_gemm_form(lay, T, fp32, best.workspace_bytes - 1).kernel == S.STB_GEMM_FUSED
+    rm = S.stb_gemm_form(S.stb_layout_sizes(S.make_cfg(n, k, N, M, sal_half)), T, False, 0)
     assert (rm.kernel, rm.k_groups, rm.workspace_bytes) == (S.STB_GEMM_GENERIC, 1, 0)
 
 
 def test_gemm_form_rejects_what_the_workspace_query_rejects():
     lay = S.stb_tiled_sizes(S.make_cfg(32, 256, 4, 8, 3))
-    for T, room in ((0, 0), (-1, 0), (4, -1)):
+    for T, fp32, room in ((0, 0, 0), (-1, 0, 0), (4, 0, -1), (4, 2, 0)):
         with pytest.raises(S.StbError) as e:
-            S.stb_gemm_form(lay, T, room)
+            S.stb_gemm_form(lay, T, fp32, room)
         assert e.value.status == S.STB_EINVAL
     lay.max_sal_half = 1000
     with pytest.raises(S.StbError) as e:
-        S.stb_gemm_form(lay, 4, 0)
+        S.stb_gemm_form(lay, 4, False, 0)
     assert e.value.status == S.STB_EINVAL
     out = S.stb_gemm_form_t()
-    assert S.binding._lib().stb_gemm_form(None, 4, 0, C.byref(out)) == S.STB_ENULL
-    assert S.binding._lib().stb_gemm_form(C.byref(lay), 4, 0, None) == S.STB_ENULL
+    assert S.binding._lib().stb_gemm_form(None, 4, 0, 0, C.byref(out)) == S.STB_ENULL
+    assert S.binding._lib().stb_gemm_form(C.byref(lay), 4, 0, 0, None) == S.STB_ENULL
 
 
 @pytest.mark.parametrize("n,k,N,M,T,sal,half,form", [
