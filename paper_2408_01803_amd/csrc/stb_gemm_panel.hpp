@@ -175,9 +175,9 @@ template <int K> __device__ inline void wait_a(ASet& a) {
 }
 
 // A workgroup is 256 rows x 128 tokens: four wavefronts of 64 rows x 128 tokens (128 accumulator registers, two wavefronts a SIMD)
-// and 64 KB of X stages, two workgroups a compute unit.  Large dense launches keep the matrix pipes busy for 0.74 to 0.82 of their time (8192 x
-// 8192 at T = 2048: 0.80 in 223 us, 3.5 GB through L2), as a library product of that size does; the sparse form for 0.49 (8192 x 28672:
-// 593 us), bound by the operands' way through L2 (14.7 MB a us, hit rate 0.72) and LDS.  (Eight wavefronts on 256 tokens, one workgroup a compute unit, read less
+// and 64 KB of X stages, two workgroups a compute unit.  Large dense launches keep the matrix pipes busy for 0.76 to 0.82 of their time (8192 x
+// 8192 at T = 2048: 0.80 in 217 us, 3.5 GB through L2), as a library product of that size does; the sparse form for 0.50 (8192 x 28672:
+// 610 us), bound by the operands' way through L2 (14.3 MB a us, hit rate 0.72) and LDS.  (Eight wavefronts on 256 tokens, one workgroup a compute unit, read less
 // but wait for each other: 266 against 258 us on 8192 x 8192 at T = 2048, 630 against 601 on 11008 x 4096 at 8192.  Four wavefronts
 // of 128 x 128 need 256 accumulator registers, which the compiler moves about: 584 register copies for 256 matrix instructions.)
 constexpr int PN_TOK = 128, PN_XSZ = PN_TOK * 128, PN_LDS = PN_BUFS * PN_XSZ;
