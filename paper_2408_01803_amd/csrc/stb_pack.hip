@@ -23,7 +23,8 @@
 namespace {
 
 constexpr int CAND = 160;                  // break-point candidates of Alg. 2
-constexpr uint32_t ST_NONFINITE = 1u, ST_SALIENT = 2u;
+constexpr int MK_ROWS = 256;               // rows of one block that a workgroup of the mask kernels takes
+constexpr uint32_t ST_NONFINITE = 1u, ST_SALIENT = 2u, ST_GROUP = 4u, ST_UNDECIDED = 8u;
 
 struct PK {
     const float* W;
@@ -43,7 +44,7 @@ struct PK {
     double* rs;             // [n][nbS] row sums of |W| (whole row, or per block)
     double2* cols;          // [k] column sums of |W| and their reciprocals
     double* rowacc;         // [n][nbS]
-    double* stats;          // [nbS][2] mean, deviation
+    double* stats;          // [nbS][2] mean, deviation (k_layer_mean: mean, 1 if the scores may be compared in fp32)
     uint32_t* mxbits;       // [nb] largest kept non-salient magnitude of the block (fp32 bits)
     uint32_t* cnt;          // [nb] number of kept non-salient weights of the block
     double* p12;            // [nb][2] break points
@@ -64,7 +65,256 @@ __device__ inline double div_by(double x, double d, double y) {
 }
 __device__ inline double recip(double d) { return d > 0.0 ? 1.0 / d : 0.0; }
 
-// ---- Standardized Importance: sums ------------------------------------------------------------------------------
+// ---- N:M mask from bounds (importance over the whole layer) -------------------------------------------------------------
+// The mask needs the order of the scores s = (mu - mean) / sd * xnorm inside a group, not their values.  sd > 0 is common
+// to all of them, the sums and the mean are within a few (n + k) roundings of their true values whatever the order of the
+// additions, and the true mean of mu is (non-zero rows + non-zero columns) / (n k): every row's shares add up to 1, and
+// every column's.  So sums in any order decide all groups in which no kept score is within the error bounds of a pruned one;
+// a tie or a near-tie anywhere (ST_UNDECIDED) sends the layer through the sums in the defined order below.  Layers of
+// continuous weights decide (at 28672 x 8192 the bounds leave a group in about one layer of a hundred); those of a single
+// magnitude, whose scores are rounding errors, do not.
+// 28672 x 8192: sums 0.19 ms and mask 0.20 (a pass over the weights takes 0.18 each), against 0.40 + 0.37 + 0.38 + 2 x 0.14 for
+// the sums in order and 0.34 for the mask.
+constexpr int FS_COLS = 1024, FS_BATCH = 8, FS_WGS = 768;        // (three workgroups a compute unit)
+
+// Row and column sums of |w| in no defined order.  Workgroup = `rows` rows x 1024 columns, a thread 4 columns, the next 8 rows
+// in flight; the rows are dealt so that the chip holds all workgroups at once (64 rows each, with nine times the
+// additions in memory: 0.29 ms).
+__global__ __launch_bounds__(256, 3) void k_layer_sums(PK a, int rows) {
+    __shared__ double part[2][FS_BATCH * 256];
+    const int chunks = (a.k + FS_COLS - 1) / FS_COLS, tid = threadIdx.x;
+    const int j = (int)(blockIdx.x % (unsigned)chunks) * FS_COLS + 4 * tid, i0 = (int)(blockIdx.x / (unsigned)chunks) * rows;
+    const bool own = j < a.k;
+    const float* w = a.W + (size_t)i0 * a.k + (own ? j : 0);
+    double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
+    uint32_t top = 0;
+    float4 v[FS_BATCH];
+    auto load = [&](int b) {                               // the next FS_BATCH rows; b = the first, from i0
+#pragma unroll
+        for (int u = 0; u < FS_BATCH; u++) {
+            v[u] = own && i0 + b + u < a.n ? *reinterpret_cast<const float4*>(w) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            w += a.k;
+        }
+    };
+    load(0);
+#pragma unroll 1
+    for (int b = 0; b < rows && i0 + b < a.n; b += FS_BATCH) {
+        double* const sums = part[(b / FS_BATCH) & 1];
+#pragma unroll
+        for (int u = 0; u < FS_BATCH; u++) {
+            const float e[4] = {fabsf(v[u].x), fabsf(v[u].y), fabsf(v[u].z), fabsf(v[u].w)};
+#pragma unroll
+            for (int p = 0; p < 4; p++) top = __float_as_uint(e[p]) > top ? __float_as_uint(e[p]) : top;
+            const double d0 = (double)e[0], d1 = (double)e[1], d2 = (double)e[2], d3 = (double)e[3];
+            c0 += d0; c1 += d1; c2 += d2; c3 += d3;
+            sums[u * 256 + tid] = (d0 + d1) + (d2 + d3);
+        }
+        if (b + FS_BATCH < rows) load(b + FS_BATCH);
+        __syncthreads();                                   // (the sums before the last are read by then: two buffers)
+        const int r = tid >> 5;
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; m++) s += sums[r * 256 + 32 * m + (tid & 31)];
+#pragma unroll
+        for (int d = 16; d > 0; d >>= 1) s += __shfl_xor(s, d);
+        if ((tid & 31) == 0 && i0 + b + r < a.n) unsafeAtomicAdd(a.rs + i0 + b + r, s);
+    }
+    if (own) {
+        unsafeAtomicAdd(&a.cols[j].x, c0); unsafeAtomicAdd(&a.cols[j + 1].x, c1);
+        unsafeAtomicAdd(&a.cols[j + 2].x, c2); unsafeAtomicAdd(&a.cols[j + 3].x, c3);
+    }
+    if (top >= 0x7F800000u) atomicOr(a.status, ST_NONFINITE);              // an infinity or a NaN
+}
+
+// One workgroup: the mean of mu from the numbers of non-zero rows and columns, the check of xnorm, and whether all sums and
+// norms are of a size that fp32 scores cannot leave the fp32 range with.
+__global__ __launch_bounds__(1024) void k_layer_mean(PK a) {
+    __shared__ uint32_t total, wide;
+    if (threadIdx.x == 0) { total = 0; wide = 0; }
+    __syncthreads();
+    uint32_t nonzero = 0, far = 0, bad = 0;
+    auto odd = [](double v) { return v != 0.0 && !(v >= 0x1p-40 && v <= 0x1p40); };
+    for (int i = threadIdx.x; i < a.n; i += 1024) { const double v = a.rs[i]; nonzero += v != 0.0; far |= odd(v); }
+    for (int j = threadIdx.x; j < a.k; j += 1024) {
+        const double v = a.cols[j].x;
+        const float x = a.xnorm[j];
+        nonzero += v != 0.0;
+        far |= odd(v) || odd((double)x);
+        bad |= !(x >= 0.0f) || !__builtin_isfinite(x);
+    }
+    if (nonzero) atomicAdd(&total, nonzero);
+    if (far) atomicOr(&wide, 1u);
+    if (bad) atomicOr(a.status, ST_NONFINITE);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    a.stats[0] = (double)total / ((double)a.n * (double)a.k);
+    a.stats[1] = wide ? 0.0 : 1.0;
+}
+
+// Which N of every M scores are kept (bit p of the result), the left one of equals first.
+template <int M, typename T>
+__device__ inline uint32_t rank_keep(const T (&s)[8], int N) {
+    int better[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // entries that rank before p: a higher score, or an equal one further left
+#pragma unroll
+    for (int p = 1; p < 8; p++)
+#pragma unroll
+        for (int o = p / M * M; o < p; o++) {
+            const bool left = s[o] >= s[p];
+            better[p] += left;
+            better[o] += !left;
+        }
+    uint32_t byte = 0;
+#pragma unroll
+    for (int p = 0; p < 8; p++) byte |= better[p] < N ? 1u << p : 0u;
+    return byte;
+}
+
+// The mask byte of 8 weights in float64, with the bounds: kept and pruned scores must differ by more than both errors, which
+// are below (n + k + 16) 2^-50 x (mu + mean) each: sums of n or k terms and their mean are off by less than 2 (n + k) + 16
+// roundings of 2^-53 in the defined order, and here.  Scores that are equal by definition (xnorm 0 for both, or weight 0 and
+// the same norm) are ties in either order.
+template <int M>
+__device__ __forceinline__ uint32_t mask_byte_f64(const PK& a, const float (&e)[8], int i, int j0, double mean, bool& undecided) {
+    double s[8], err[8];
+    float x[8];
+    const double rinv = recip(a.rs[i]), eta = (double)(a.n + a.k + 16) * 0x1p-50;
+#pragma unroll
+    for (int p = 0; p < 8; p++) {
+        x[p] = a.xnorm[j0 + p];
+        const double mu = (double)e[p] * (rinv + recip(a.cols[j0 + p].x));
+        s[p] = (mu - mean) * (double)x[p];
+        err[p] = (mu + mean) * (double)x[p] * eta;
+    }
+    const uint32_t byte = rank_keep<M>(s, a.N);
+#pragma unroll
+    for (int p = 0; p < 8; p++)
+#pragma unroll
+        for (int o = p / M * M; o < p / M * M + M; o++) {
+            if (o == p) continue;
+            const bool tie = x[o] == x[p] && (x[p] == 0.0f || (e[o] == 0.0f && e[p] == 0.0f));
+            if ((byte >> p) & ~(byte >> o) & 1u) undecided |= !(s[p] - s[o] > err[p] + err[o]) && !tie;
+        }
+    return byte;
+}
+
+// The N-th and (N+1)-th largest of each M scores: Batcher's network, of which the compiler keeps what those two need.
+template <int M, int N>
+__device__ inline void around_cut(const float (&s)[8], int h, float& low, float& high) {
+    float v[M];
+#pragma unroll
+    for (int p = 0; p < M; p++) v[p] = s[h + p];
+    auto order = [&](int i, int j) { const float a = fmaxf(v[i], v[j]), b = fminf(v[i], v[j]); v[i] = a; v[j] = b; };
+    if constexpr (M == 8) {
+        order(0, 1); order(2, 3); order(4, 5); order(6, 7);
+        order(0, 2); order(1, 3); order(4, 6); order(5, 7);
+        order(1, 2); order(5, 6); order(0, 4); order(1, 5); order(2, 6); order(3, 7);
+        order(2, 4); order(3, 5); order(1, 2); order(3, 4); order(5, 6);
+    } else {
+        order(0, 1); order(2, 3); order(0, 2); order(1, 3); order(1, 2);
+    }
+    low = v[N - 1];
+    high = N < M ? v[N < M ? N : 0] : -__builtin_inff();
+}
+
+// A workgroup takes 256 rows of one block: 16 rows at a time, a thread 8 columns, whose column sums and norms stay in
+// registers.  Scores in fp32, whose error is below 2^-20 xnorm (mu + mean): where the N-th largest of a group is further than
+// both errors above the next, the scores not below it are kept; the few groups in a million where it is not are taken again
+// in float64.  Also the largest kept non-salient magnitude and their number per block.
+template <int M, int N>
+__global__ __launch_bounds__(256) void k_layer_mask(PK a) {
+    if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ST_UNDECIDED) return;     // (the layer goes the other way)
+    const int q = (int)(blockIdx.x % (unsigned)a.nb), g = threadIdx.x & 15, r = threadIdx.x >> 4;
+    const int ibeg = (int)(blockIdx.x / (unsigned)a.nb) * MK_ROWS + r, j0 = q * STB_BLOCK + 8 * g;
+    const int iend = (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS < a.n ? (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS : a.n;
+    const double mean = a.stats[0];
+    const bool narrow = a.stats[1] != 0.0;
+    float x[8], cx[8], mx8[8], mxtop = 0.0f;       // xnorm, xnorm / column sum, mean * xnorm
+    uint32_t normal[8];                            // all ones where the column is not salient
+#pragma unroll
+    for (int p = 0; p < 8; p++) {
+        const float c = (float)a.cols[j0 + p].x;
+        x[p] = a.xnorm[j0 + p];
+        cx[p] = c > 0.0f ? x[p] * __builtin_amdgcn_rcpf(c) : 0.0f;
+        mx8[p] = (float)mean * x[p];
+        mxtop = fmaxf(mxtop, mx8[p]);
+        normal[p] = sal_bit(a.sal, j0 + p) ? 0u : ~0u;
+    }
+    const uint32_t normal8 = ~(a.sal[j0 >> 5] >> (8 * (g & 3))) & 0xFFu;
+    uint32_t mx = 0, members = 0, again = 0;       // again: rows (of the thread's 16) to take in float64
+    float4 n0[2], n1[2];
+    double nrs[2] = {0.0, 0.0};
+    auto load = [&](int u, int i) {
+        if (i >= iend) return;
+        const float4* w = reinterpret_cast<const float4*>(a.W + (size_t)i * a.k + j0);
+        n0[u] = w[0];
+        n1[u] = w[1];
+        nrs[u] = a.rs[i];
+    };
+    auto row = [&](int u, int i) {
+        if (i >= iend) return;
+        const float e[8] = {fabsf(n0[u].x), fabsf(n0[u].y), fabsf(n0[u].z), fabsf(n0[u].w), fabsf(n1[u].x), fabsf(n1[u].y), fabsf(n1[u].z), fabsf(n1[u].w)};
+        const float rsum = (float)nrs[u], rinv = rsum > 0.0f ? __builtin_amdgcn_rcpf(rsum) : 0.0f;
+        load(u, i + 32);
+        float s[8], top = 0.0f, low[2], high[2];
+#pragma unroll
+        for (int p = 0; p < 8; p++) {
+            s[p] = __builtin_fmaf(e[p], __builtin_fmaf(rinv, x[p], cx[p]), -mx8[p]);
+            top = fmaxf(top, s[p]);
+        }
+        around_cut<M, N>(s, 0, low[0], high[0]);
+        if constexpr (M == 4) around_cut<M, N>(s, 4, low[1], high[1]);
+        else { low[1] = low[0]; high[1] = high[0]; }
+        const float gap = fminf(low[0] - high[0], low[1] - high[1]);
+        const bool sure = narrow && gap > 0x1p-19f * (top + 2.0f * mxtop);
+        if (!sure) again |= 1u << ((i - ibeg) >> 4);
+        uint32_t byte = 0;
+#pragma unroll
+        for (int p = 0; p < 8; p++) {
+            const bool kept = s[p] >= (sure ? low[p / 4] : __builtin_inff());
+            byte |= kept ? 1u << p : 0u;
+            const uint32_t bits = kept ? __float_as_uint(e[p]) & normal[p] : 0u;      // magnitudes order like their bit patterns
+            mx = bits > mx ? bits : mx;
+        }
+        a.mask[(size_t)i * a.mask_stride + (j0 >> 3)] = (uint8_t)byte;
+        members += (uint32_t)__popc(byte & normal8);
+    };
+    load(0, ibeg);
+    load(1, ibeg + 16);
+#pragma unroll 1
+    for (int i = ibeg; i < iend; i += 32) {
+        row(0, i);
+        row(1, i + 16);
+    }
+    bool undecided = false;
+    for (; again; again &= again - 1) {
+        const int i = ibeg + 16 * (__ffs(again) - 1);
+        const float* w = a.W + (size_t)i * a.k + j0;
+        float e[8];
+#pragma unroll
+        for (int p = 0; p < 8; p++) e[p] = fabsf(w[p]);
+        const uint32_t byte = mask_byte_f64<M>(a, e, i, j0, mean, undecided);
+#pragma unroll
+        for (int p = 0; p < 8; p++) {
+            const uint32_t bits = (byte >> p) & 1u ? __float_as_uint(e[p]) & normal[p] : 0u;
+            mx = bits > mx ? bits : mx;
+        }
+        a.mask[(size_t)i * a.mask_stride + (j0 >> 3)] = (uint8_t)byte;
+        members += (uint32_t)__popc(byte & normal8);
+    }
+    if (undecided) atomicOr(a.status, ST_UNDECIDED);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const uint32_t om = __shfl_xor(mx, d);
+        mx = om > mx ? om : mx;
+        members += __shfl_xor(members, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        if (mx) atomicMax(a.mxbits + q, mx);
+        if (members) atomicAdd(a.cnt + q, members);
+    }
+}
+
+// ---- Standardized Importance: sums in the defined order (importance per block, and layers that the bounds do not decide) ------------------------------------------------------------------------------
 // A sum over a row (or column, or the rows' accumulators) is sequential by definition: one lane's chain.  So that nothing
 // else is on that chain, four wavefronts of a workgroup load, convert and (for the sums of mu) divide into an LDS tile,
 // and a fifth adds the tile before, a lane a row.  One barrier a tile.
@@ -282,7 +532,6 @@ __global__ __launch_bounds__(64) void k_total(PK a) {
 // entries of a group with the fewest counts are kept.  28672 x 8192: 0.34 ms (0.96 with a thread that
 // fetches everything for its 8 columns), with the maxima and counts that a second
 // pass over the weights took 990 us for (one thread a row and block, each walking its own 512 bytes).
-constexpr int MK_ROWS = 256;
 template <int M>
 __global__ __launch_bounds__(256) void k_mask(PK a) {
     const int q = (int)(blockIdx.x % (unsigned)a.nb), g = threadIdx.x & 15, r = threadIdx.x >> 4;
@@ -316,18 +565,7 @@ __global__ __launch_bounds__(256) void k_mask(PK a) {
             const double mu = div_by(av, rsv, rinv) + div_by(av, col[p].x, col[p].y);
             s[p] = div_by(mu - mean, sd, sinv) * (double)xn[p];
         }
-        int better[8] = {0, 0, 0, 0, 0, 0, 0, 0};      // entries that rank before p: a higher score, or an equal one further left
-#pragma unroll
-        for (int p = 1; p < 8; p++)
-#pragma unroll
-            for (int o = p / M * M; o < p; o++) {
-                const bool left = s[o] >= s[p];
-                better[p] += left;
-                better[o] += !left;
-            }
-        uint32_t byte = 0;
-#pragma unroll
-        for (int p = 0; p < 8; p++) byte |= better[p] < a.N ? 1u << p : 0u;
+        const uint32_t byte = rank_keep<M>(s, a.N);
         a.mask[(size_t)i * a.mask_stride + (j0 >> 3)] = (uint8_t)byte;
         const uint32_t kept = byte & normal;
         members += (uint32_t)__popc(kept);
@@ -792,7 +1030,7 @@ __global__ __launch_bounds__(256) void k_assign(PK a) {
         wave_order();
     }
     c0 = STB_BLOCK / 8 * n8 - c1 - c2 - co;
-    if (live && odd) atomicOr(a.status, ST_SALIENT << 1);              // a group that does not keep N: scores that do not order (NaN)
+    if (live && odd) atomicOr(a.status, ST_GROUP);                 // a group that does not keep N: scores that do not order (NaN)
     // residual binarisation of the kept salient weights (Eq. 4)
     const uint16_t ao16 = stb_f64_to_f16_bits(co > 0 ? so / (double)co : 0.0);
     double sr = 0.0;
@@ -1105,21 +1343,38 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
     const int T = 256;
     // the salient bitmap must hold exactly cfg.n_salient columns before anything indexes the res_sign rows by it
     hipLaunchKernelGGL(k_salient_tables, dim3(1), dim3(64), 0, st, a);
+    const dim3 mask_grid((unsigned)((int64_t)((a.n + MK_ROWS - 1) / MK_ROWS) * a.nb));
+    if (!a.per_block) {
+        const int64_t chunks = (a.k + FS_COLS - 1) / FS_COLS, rows = (a.n * chunks + FS_WGS * FS_BATCH - 1) / (FS_WGS * FS_BATCH) * FS_BATCH;
+        hipLaunchKernelGGL(k_layer_sums, dim3((unsigned)((a.n + rows - 1) / rows * chunks)), dim3(T), 0, st, a, (int)rows);
+        hipLaunchKernelGGL(k_layer_mean, dim3(1), dim3(1024), 0, st, a);
+        switch (a.M * 16 + a.N) {
+#define STB_MASK(M, N) case M * 16 + N: hipLaunchKernelGGL((k_layer_mask<M, N>), mask_grid, dim3(T), 0, st, a); break;
+            STB_MASK(4, 1) STB_MASK(4, 2) STB_MASK(4, 3) STB_MASK(4, 4)
+            STB_MASK(8, 1) STB_MASK(8, 2) STB_MASK(8, 3) STB_MASK(8, 4) STB_MASK(8, 5) STB_MASK(8, 6) STB_MASK(8, 7) STB_MASK(8, 8)
+#undef STB_MASK
+            default: return STB_EINVAL;
+        }
+    }
     uint32_t status = 0;
     ok(hipGetLastError());
     ok(hipMemcpyAsync(&status, a.status, 4, hipMemcpyDeviceToHost, st));
     ok(hipStreamSynchronize(st));
     if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
     if (status & ST_SALIENT) return STB_EINVAL;
-    const unsigned row_wgs = (unsigned)((a.n + RC_ROWS - 1) / RC_ROWS);
-    hipLaunchKernelGGL(k_abs_sums, dim3(a.k / CC_COLS + row_wgs), dim3(CHAIN_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_mu_sums<1>, dim3(row_wgs), dim3(CHAIN_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_total<0>, dim3(a.nbS), dim3(64), 0, st, a);
-    hipLaunchKernelGGL(k_mu_sums<2>, dim3(row_wgs), dim3(CHAIN_THREADS), 0, st, a);
-    hipLaunchKernelGGL(k_total<1>, dim3(a.nbS), dim3(64), 0, st, a);
-    const dim3 mask_grid((unsigned)((int64_t)((a.n + MK_ROWS - 1) / MK_ROWS) * a.nb));
-    if (a.M == 4) hipLaunchKernelGGL(k_mask<4>, mask_grid, dim3(T), 0, st, a);
-    else hipLaunchKernelGGL(k_mask<8>, mask_grid, dim3(T), 0, st, a);
+    if (status & ST_NONFINITE) return STB_ENONFINITE;
+    if (a.per_block || (status & ST_UNDECIDED)) {
+        if (status) ok(hipMemsetAsync(ws + wp.mxbits, 0, (size_t)(wp.p12 - wp.mxbits), st));       // maxima and counts of the mask by bounds
+        if (status) ok(hipMemsetAsync(a.status, 0, 4, st));
+        const unsigned row_wgs = (unsigned)((a.n + RC_ROWS - 1) / RC_ROWS);
+        hipLaunchKernelGGL(k_abs_sums, dim3(a.k / CC_COLS + row_wgs), dim3(CHAIN_THREADS), 0, st, a);
+        hipLaunchKernelGGL(k_mu_sums<1>, dim3(row_wgs), dim3(CHAIN_THREADS), 0, st, a);
+        hipLaunchKernelGGL(k_total<0>, dim3(a.nbS), dim3(64), 0, st, a);
+        hipLaunchKernelGGL(k_mu_sums<2>, dim3(row_wgs), dim3(CHAIN_THREADS), 0, st, a);
+        hipLaunchKernelGGL(k_total<1>, dim3(a.nbS), dim3(64), 0, st, a);
+        if (a.M == 4) hipLaunchKernelGGL(k_mask<4>, mask_grid, dim3(T), 0, st, a);
+        else hipLaunchKernelGGL(k_mask<8>, mask_grid, dim3(T), 0, st, a);
+    }
     if (a.region_mode == 0) {
         try {
             const int rc = search_breakpoints(a, wp, ws, st, hip_err);

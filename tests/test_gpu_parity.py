@@ -181,6 +181,39 @@ def test_device_packer_break_points_where_candidates_are_close(n, values, torch_
         assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
 
 
+@pytest.mark.parametrize("values", ["normal", "zeros", "zero rows and columns", "twin columns", "one magnitude", "zero norms", "wide norms", "huge", "subnormal"])
+@pytest.mark.parametrize("n,k,N,M", [(1, 128, 4, 8), (65, 1152, 2, 4), (257, 1024, 6, 8)])
+def test_device_packer_mask_where_scores_are_close(n, k, N, M, values, torch_cuda):
+    """The mask from bounds and, where those leave a group open, from the sums in the defined order: ties by definition, ties that
+    only the defined order decides, the ends of the fp32 range, and the edges of the 64-row x 1024-column sums: the oracle's bytes."""
+    rng = np.random.default_rng(n + len(values))
+    W = rng.standard_normal((n, k)).astype(np.float32)
+    xnorm = np.abs(1 + 0.3 * rng.standard_normal(k)).astype(np.float32)
+    if values == "zeros":
+        W[rng.random((n, k)) < 0.7] = 0.0
+        xnorm[:] = 1.0
+    elif values == "zero rows and columns":
+        W[::3] = 0.0
+        W[:, 5::16] = 0.0
+    elif values == "twin columns":
+        W[:, 1::2], xnorm[1::2] = -W[:, 0::2], xnorm[0::2]
+    elif values == "one magnitude":
+        W = np.where(W >= 0, np.float32(0.75), np.float32(-0.75))
+    elif values == "zero norms":
+        xnorm[rng.random(k) < 0.6] = 0.0
+    elif values == "wide norms":
+        xnorm *= np.float32(10.0) ** rng.integers(-37, 38, k).astype(np.float32)
+    elif values == "huge":
+        W *= np.float32(5e37)
+    elif values == "subnormal":
+        W = (np.round(W * 20) * 1.4012984643e-45).astype(np.float32)
+    none = np.zeros(k // 32, dtype=np.uint32)
+    _say(f"[case] mask {n}x{k} {N}:{M} {values}")
+    pm = _pack_on_device(torch_cuda, W, xnorm, none, N, M, 0)
+    for name, v in O.pack(W, xnorm, none, N, M, 0).items():
+        assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+
+
 @pytest.mark.parametrize("levels", [1, 2, 15])
 def test_device_packer_takes_no_longer_where_candidates_tie(levels, torch_cuda):
     """A layer of few distinct magnitudes, on which most candidates of the break-point search part the weights alike: the host's
