@@ -27,7 +27,10 @@
 #include <hip/hip_fp16.h>
 
 #include <atomic>
+#include <climits>
 #include <cstddef>
+#include <cstring>
+#include <type_traits>
 
 #include "stb_tiled.hpp"
 
@@ -40,7 +43,14 @@ typedef _Float16 half16_t __attribute__((ext_vector_type(16)));
 
 constexpr int LDS24 = 160 * 1024 - 64; // dynamic LDS a workgroup may ask for (a few bytes are static)
 constexpr int MAXV24 = 8;             // most superblocks a wavefront visits per row tile
-constexpr int PHASE24 = 15;           // row tiles between two reductions (a multiple of 3: three tile buffers)
+constexpr int TILES24 = 4;            // tile buffers of a wavefront: three tiles are on their way while it works on one
+constexpr int PHASE24 = 15;           // row tiles whose partial products (1 KB each at 16 rows of x) a wavefront's LDS is planned for
+// Row tiles between two reductions: all of them, or as many as fit into that LDS at 64 bytes a row of x, in whole rounds of the
+// tile buffers.
+inline int phase24(int R, int B) {
+    const int fit = (R < PHASE24 ? R : PHASE24) * 16 / B;
+    return R <= fit ? R : fit / TILES24 * TILES24;
+}
 
 // Packed operands of one (row, block): mask, sign and id words of the two half blocks, scales, alpha_r.
 struct Tile24 {
@@ -70,14 +80,15 @@ struct LaneOff24 {
     uint32_t m, s, r, c, a, t;        // mask, sign, region, scales, res_scale, res_t
 };
 
-// The loads of one tile, one asm statement: packed planes first, then (RES) the res_t word.
+// The loads of one tile, one asm statement: packed planes first, then (RES) the res_t word.  go = 0: none of them is issued.  The
+// branch is inside the statement, so the compiler sees no join at which it might copy registers with loads in flight.
 template <bool RES>
-__device__ inline void fetch24(Tile24& d, const char* image, int tile, const LaneOff24& lo) {
+__device__ inline void fetch24(Tile24& d, const char* image, int tile, const LaneOff24& lo, int go) {
     const uint32_t t10 = (uint32_t)tile << 10;
     const uint32_t vm = t10 + lo.m, vr = t10 + lo.r, vs = (t10 >> 1) + lo.s, vc = (t10 >> 1) + lo.c, va = (t10 >> 3) + lo.a;
     if constexpr (RES) {
         const uint32_t vt = (t10 >> 2) + lo.t;
-        asm volatile(STB24_SGPR_SETTLE
+        asm volatile("s_cmp_eq_u32 %16, 0\n\ts_cbranch_scc1 .Lskip%=\n\t" STB24_SGPR_SETTLE
                      "global_load_dwordx2 %0, %9, %15\n\t"
                      "global_load_dwordx2 %1, %9, %15 offset:512\n\t"
                      "global_load_dword %2, %10, %15\n\t"
@@ -86,11 +97,13 @@ __device__ inline void fetch24(Tile24& d, const char* image, int tile, const Lan
                      "global_load_dwordx2 %5, %11, %15 offset:512\n\t"
                      "global_load_dwordx2 %6, %12, %15\n\t"
                      "global_load_ushort %7, %13, %15\n\t"
-                     "global_load_dword %8, %14, %15"
-                     : "=&v"(d.m0), "=&v"(d.m1), "=&v"(d.s0), "=&v"(d.s1), "=&v"(d.r0), "=&v"(d.r1), "=&v"(d.sc), "=&v"(d.ar), "=&v"(d.et)
-                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "v"(vt), "s"(image));
+                     "global_load_dword %8, %14, %15\n"
+                     ".Lskip%=:"
+                     : "+&v"(d.m0), "+&v"(d.m1), "+&v"(d.s0), "+&v"(d.s1), "+&v"(d.r0), "+&v"(d.r1), "+&v"(d.sc), "+&v"(d.ar), "+&v"(d.et)
+                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "v"(vt), "s"(image), "s"(go)
+                     : "scc");
     } else {
-        asm volatile(STB24_SGPR_SETTLE
+        asm volatile("s_cmp_eq_u32 %14, 0\n\ts_cbranch_scc1 .Lskip%=\n\t" STB24_SGPR_SETTLE
                      "global_load_dwordx2 %0, %8, %13\n\t"
                      "global_load_dwordx2 %1, %8, %13 offset:512\n\t"
                      "global_load_dword %2, %9, %13\n\t"
@@ -98,29 +111,26 @@ __device__ inline void fetch24(Tile24& d, const char* image, int tile, const Lan
                      "global_load_dwordx2 %4, %10, %13\n\t"
                      "global_load_dwordx2 %5, %10, %13 offset:512\n\t"
                      "global_load_dwordx2 %6, %11, %13\n\t"
-                     "global_load_ushort %7, %12, %13"
-                     : "=&v"(d.m0), "=&v"(d.m1), "=&v"(d.s0), "=&v"(d.s1), "=&v"(d.r0), "=&v"(d.r1), "=&v"(d.sc), "=&v"(d.ar)
-                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "s"(image));
+                     "global_load_ushort %7, %12, %13\n"
+                     ".Lskip%=:"
+                     : "+&v"(d.m0), "+&v"(d.m1), "+&v"(d.s0), "+&v"(d.s1), "+&v"(d.r0), "+&v"(d.r1), "+&v"(d.sc), "+&v"(d.ar)
+                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "s"(image), "s"(go)
+                     : "scc");
     }
 }
 
-template <int K>
-__device__ inline void wait24(Tile24& d) {
-    asm volatile("s_waitcnt vmcnt(%9)"
-                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s0), "+v"(d.s1), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar),
-                   "+v"(d.et)
-                 : "n"(K));
-}
-// The same in two steps: the packed planes (the older loads of a tile), then the res_t word.
-template <int K>
-__device__ inline void wait24_main(Tile24& d) {
-    asm volatile("s_waitcnt vmcnt(%8)"
-                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s0), "+v"(d.s1), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar)
-                 : "n"(K));
-}
-template <int K, typename T>
-__device__ inline void wait24_res(T& d) {
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(d.et) : "n"(K));
+// Waits until at most min(later, 3) tiles of L loads each are outstanding: the loads of the tile are older than those of the
+// `later` tiles fetched after it (at most three are).
+#define STB24_WAIT_TILE \
+    "s_cmp_lt_i32 %[later], 3\n\ts_cbranch_scc1 .Ltwo%=\n\ts_waitcnt vmcnt(%[three])\n\ts_branch .Lend%=\n.Ltwo%=:\n\t" \
+    "s_cmp_lt_i32 %[later], 2\n\ts_cbranch_scc1 .Lone%=\n\ts_waitcnt vmcnt(%[two])\n\ts_branch .Lend%=\n.Lone%=:\n\t" \
+    "s_cmp_lt_i32 %[later], 1\n\ts_cbranch_scc1 .Llast%=\n\ts_waitcnt vmcnt(%[one])\n\ts_branch .Lend%=\n.Llast%=:\n\t" \
+    "s_waitcnt vmcnt(0)\n.Lend%=:"
+template <int L>
+__device__ inline void wait24(Tile24& d, int later) {
+    asm volatile(STB24_WAIT_TILE
+                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s0), "+v"(d.s1), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar), "+v"(d.et)
+                 : [later] "s"(later), [three] "n"(3 * L), [two] "n"(2 * L), [one] "n"(L) : "scc");
 }
 
 // The same for 6:8 layers: 12 bytes of sign bits per block (not cut in halves), 12 bytes of ids per half block.
@@ -135,13 +145,13 @@ struct Tile68 {
 constexpr int LMAIN68 = 7;
 
 template <bool RES>
-__device__ inline void fetch24(Tile68& d, const char* image, int tile, const LaneOff24& lo) {
+__device__ inline void fetch24(Tile68& d, const char* image, int tile, const LaneOff24& lo, int go) {
     const uint32_t t10 = (uint32_t)tile << 10;
     const uint32_t vm = t10 + lo.m, vs = (uint32_t)tile * 768u + lo.s, vr = (uint32_t)tile * 1536u + lo.r;
     const uint32_t vc = (t10 >> 1) + lo.c, va = (t10 >> 3) + lo.a;
     if constexpr (RES) {
         const uint32_t vt = (t10 >> 2) + lo.t;
-        asm volatile(STB24_SGPR_SETTLE
+        asm volatile("s_cmp_eq_u32 %15, 0\n\ts_cbranch_scc1 .Lskip%=\n\t" STB24_SGPR_SETTLE
                      "global_load_dwordx2 %0, %8, %14\n\t"
                      "global_load_dwordx2 %1, %8, %14 offset:512\n\t"
                      "global_load_dwordx3 %2, %9, %14\n\t"
@@ -149,35 +159,32 @@ __device__ inline void fetch24(Tile68& d, const char* image, int tile, const Lan
                      "global_load_dwordx3 %4, %10, %14 offset:768\n\t"
                      "global_load_dwordx2 %5, %11, %14\n\t"
                      "global_load_ushort %6, %12, %14\n\t"
-                     "global_load_dword %7, %13, %14"
-                     : "=&v"(d.m0), "=&v"(d.m1), "=&v"(d.s), "=&v"(d.r0), "=&v"(d.r1), "=&v"(d.sc), "=&v"(d.ar), "=&v"(d.et)
-                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "v"(vt), "s"(image));
+                     "global_load_dword %7, %13, %14\n"
+                     ".Lskip%=:"
+                     : "+&v"(d.m0), "+&v"(d.m1), "+&v"(d.s), "+&v"(d.r0), "+&v"(d.r1), "+&v"(d.sc), "+&v"(d.ar), "+&v"(d.et)
+                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "v"(vt), "s"(image), "s"(go)
+                     : "scc");
     } else {
-        asm volatile(STB24_SGPR_SETTLE
+        asm volatile("s_cmp_eq_u32 %13, 0\n\ts_cbranch_scc1 .Lskip%=\n\t" STB24_SGPR_SETTLE
                      "global_load_dwordx2 %0, %7, %12\n\t"
                      "global_load_dwordx2 %1, %7, %12 offset:512\n\t"
                      "global_load_dwordx3 %2, %8, %12\n\t"
                      "global_load_dwordx3 %3, %9, %12\n\t"
                      "global_load_dwordx3 %4, %9, %12 offset:768\n\t"
                      "global_load_dwordx2 %5, %10, %12\n\t"
-                     "global_load_ushort %6, %11, %12"
-                     : "=&v"(d.m0), "=&v"(d.m1), "=&v"(d.s), "=&v"(d.r0), "=&v"(d.r1), "=&v"(d.sc), "=&v"(d.ar)
-                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "s"(image));
+                     "global_load_ushort %6, %11, %12\n"
+                     ".Lskip%=:"
+                     : "+&v"(d.m0), "+&v"(d.m1), "+&v"(d.s), "+&v"(d.r0), "+&v"(d.r1), "+&v"(d.sc), "+&v"(d.ar)
+                     : "v"(vm), "v"(vs), "v"(vr), "v"(vc), "v"(va), "s"(image), "s"(go)
+                     : "scc");
     }
 }
 
-template <int K>
-__device__ inline void wait24(Tile68& d) {
-    asm volatile("s_waitcnt vmcnt(%8)"
-                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar),
-                   "+v"(d.et)
-                 : "n"(K));
-}
-template <int K>
-__device__ inline void wait24_main(Tile68& d) {
-    asm volatile("s_waitcnt vmcnt(%7)"
-                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar)
-                 : "n"(K));
+template <int L>
+__device__ inline void wait24(Tile68& d, int later) {
+    asm volatile(STB24_WAIT_TILE
+                 : "+v"(d.m0), "+v"(d.m1), "+v"(d.s), "+v"(d.r0), "+v"(d.r1), "+v"(d.sc), "+v"(d.ar), "+v"(d.et)
+                 : [later] "s"(later), [three] "n"(3 * L), [two] "n"(2 * L), [one] "n"(L) : "scc");
 }
 
 // MODE of the kernel below: 2 = 2:4 layers on the sparse instruction; 4 / 6 = layers that keep 4 / 6 of 8 columns
@@ -198,44 +205,49 @@ __device__ inline void half_of(const Tile68& t, int h, HalfData<6>& d) {
     d.r[0] = h == 0 ? t.r0[0] : t.r1[0]; d.r[1] = h == 0 ? t.r0[1] : t.r1[1]; d.r[2] = h == 0 ? t.r0[2] : t.r1[2];
 }
 
-// expand_group of stb_tiled.hpp with the constants in registers (K3 = 0x03030303, K4 = 0x04000400,
-// KS = 0x80008000), so that every and-or is one compiler-scheduled instruction.
+// The kept weights of a half block as codes, four slots a register: byte j of Q[b] = id of slot 4 b + j | its sign bit << 2, which is
+// what v_perm_b32 takes as selectors for eight bytes (four scales, plus and minus).  16 slots at a time: rw = their ids, the half
+// `hi16` of sw their sign bits.  The fields are parted over all four bytes of a word at once and then transposed: 6 instructions for
+// four slots (9 with each pair of slots expanded on its own, of which a tile of 4:8 then took 394 vector instructions instead of 320,
+// one of 6:8 524 instead of 404).
+__device__ inline void slot_codes(uint32_t rw, uint32_t sw, bool hi16, uint32_t Q[4]) {
+    const uint32_t K3 = 0x03030303u, K4 = 0x04040404u;
+    const uint32_t t = perm(sw, sw, hi16 ? 0x0C030C02u : 0x0C010C00u);        // sign bits of slots 0..7 | 8..15 << 16
+    const uint32_t n = (t << 4) | t;                                          // low nibble of byte b: the signs of slots 4 b ..
+    const uint32_t E0 = and_or_v(n << 2, K4, rw & K3), E1 = and_or_v(n << 1, K4, (rw >> 2) & K3);
+    const uint32_t E2 = and_or_v(n, K4, (rw >> 4) & K3), E3 = and_or_v(n >> 1, K4, (rw >> 6) & K3);
+    const uint32_t a = perm(E1, E0, 0x05010400u), b = perm(E3, E2, 0x05010400u);
+    const uint32_t c = perm(E1, E0, 0x07030602u), d = perm(E3, E2, 0x07030602u);
+    Q[0] = perm(b, a, 0x05040100u); Q[1] = perm(b, a, 0x07060302u);
+    Q[2] = perm(d, c, 0x05040100u); Q[3] = perm(d, c, 0x07060302u);
+}
+
 template <int N8>
-__device__ inline void expand8(const HalfData<N8>& d, uint32_t TL, uint32_t TH, int t, const uint4& L,
-                               uint32_t K3, uint32_t K4, uint32_t KS, uint32_t out[4]) {
-    uint32_t W[3];
+__device__ inline void half_codes(const HalfData<N8>& d, uint32_t (&Q)[2 * N8]) {
+#pragma unroll
+    for (int w = 0; w < N8 / 2; w++) slot_codes(d.r[w], d.s[w >> 1], w & 1, Q + 4 * w);
+}
+
+// Expands columns 8t .. 8t+7 (t < 8) of a half block into four registers of fp16 pairs (negated weights).  TL / TH = low / high bytes
+// of the four scales (>= 0), TN = TH with the signs set; L = the group's scatter selectors: byte r of the low bytes, 4 + r of the high ones.
+template <int N8>
+__device__ inline void expand8(const uint32_t (&Q)[2 * N8], uint32_t TL, uint32_t TH, uint32_t TN, int t, const uint4& L, uint32_t out[4]) {
     if (N8 == 4) {
-        const uint32_t rw = d.r[t >> 2], r2 = rw >> 2;
-        const uint32_t b = t & 3;
-        const uint32_t Z = perm(r2, rw, b | (b << 8) | ((4 + b) << 16) | ((4 + b) << 24));
-        W[0] = perm(TH, TL, and_or_v(Z, K3, K4));
-        W[1] = perm(TH, TL, and_or_v(Z >> 4, K3, K4));
-        const uint32_t sw = d.s[0];
-        const uint32_t sb = (t >> 1) & 3;
-        const uint32_t X = perm(sw, sw, 0x000C000Cu | (sb << 8) | (sb << 24));     // halves = sign byte << 8
-        const int base = 4 * (t & 1);
-        W[0] = and_or_v(pk_shl(X, 7 - base, 6 - base), KS, W[0]);                   // scales are >= 0: their sign bit is clear
-        W[1] = and_or_v(pk_shl(X, 5 - base, 4 - base), KS, W[1]);
-        out[0] = perm(W[1], W[0], L.x);
-        out[1] = perm(W[1], W[0], L.y);
-        out[2] = perm(W[1], W[0], L.z);
-        out[3] = perm(W[1], W[0], L.w);
+        const uint32_t lo = perm(TL, TL, Q[t]), hi = perm(TN, TH, Q[t]);
+        out[0] = perm(hi, lo, L.x);
+        out[1] = perm(hi, lo, L.y);
+        out[2] = perm(hi, lo, L.z);
+        out[3] = perm(hi, lo, L.w);
     } else {
-        const uint32_t v = window32<3>(d.r, 12 * t), v2 = v >> 2;
-        const uint32_t Z = perm(v2, v, 0x04040000u);
-        const uint32_t Z1 = perm(v2, v, 0x05050101u);
-        W[0] = perm(TH, TL, and_or_v(Z, K3, K4));
-        W[1] = perm(TH, TL, and_or_v(Z >> 4, K3, K4));
-        W[2] = perm(TH, TL, and_or_v(Z1, K3, K4));
-        const uint32_t sv = window32<2>(d.s, 6 * t);
-        const uint32_t X = perm(sv, sv, 0x000C000Cu);                               // halves = (sign bits) << 8
-        W[0] = and_or_v(pk_shl(X, 7, 6), KS, W[0]);
-        W[1] = and_or_v(pk_shl(X, 5, 4), KS, W[1]);
-        W[2] = and_or_v(pk_shl(X, 3, 2), KS, W[2]);
-        out[0] = perm(W[1], W[0], L.x);
-        out[1] = perm(W[1], W[0], L.y);
-        out[2] = perm(W[2], W[1], L.z);
-        out[3] = perm(W[2], W[1], L.w);
+        // slots 6t ..: columns 0 to 3 hold slots 0 to 3 of the group, columns 4 to 7 slots 2 to 5
+        const int q = 6 * t / 4;
+        const uint32_t mid = perm(Q[q + 1], Q[q], 0x05040302u);
+        const uint32_t A = t & 1 ? mid : Q[q], B = t & 1 ? Q[q + 1] : mid;
+        const uint32_t loA = perm(TL, TL, A), hiA = perm(TN, TH, A), loB = perm(TL, TL, B), hiB = perm(TN, TH, B);
+        out[0] = perm(hiA, loA, L.x);
+        out[1] = perm(hiA, loA, L.y);
+        out[2] = perm(hiB, loB, L.z);
+        out[3] = perm(hiB, loB, L.w);
     }
 }
 
@@ -264,45 +276,104 @@ struct Res24 {
 // share their input, say): the grid is the layers' grids one after the other, and a workgroup finds its layer by its
 // index.  The descriptors travel by value in the kernel arguments, so a launch needs no table in device memory and can
 // be captured in a HIP graph.
+// What a workgroup needs before its first load fills two groups of 16 scalar registers, which it reads with one load each, both in
+// flight at once: read field by field as the compiler found registers for them, the descriptor cost eight scalar round
+// trips, 1.2 us of a 7.5 us call.
 struct Gemv24Layer {
-    TiledPlanes p;
     const char* image;        // lowest address of the streamed planes; their offsets from it (all below 4 GiB):
-    uint32_t off_mask, off_sign, off_region, off_scales, off_res_scale, off_res_t;
     const __half* x;
-    void* y;
-    float* ws_part;
-    uint32_t* ws_count;
-    int R, SPS, PHT, WREG, REC_OFF, PART_OFF, V, XS;
-    int G, S;                 // workgroups along the rows, column splits: the layer owns G * S workgroups ...
-    int block0;               // ... starting at this one
+    const uint32_t* sal_tab;
+    uint32_t off_mask, off_sign, off_region, off_scales, off_res_scale, off_res_t;
+    int k, nsb, nrt;
+    int R;
+    int SPS, PHT, WREG, REC_OFF, PART_OFF, V, XS;
+    int G, S;                 // workgroups along the rows, column splits: the layer owns G * S workgroups
     int variant;              // MODE | HAS_RES << 3 | MULTI << 4
+    int sal_chunks, n;
+    uint32_t g_magic;         // ceil(2^32 / G) where S > 1 (and then G > 1, or G = 1 and 0)
+    uint32_t pad;
+    void* y;
+    float* ws_part;           // read at the end only, as what follows
+    uint32_t* ws_count;
+    TiledPlanes p;
 };
+static_assert(offsetof(Gemv24Layer, R) == 60 && offsetof(Gemv24Layer, ws_part) == 128, "two groups of 16 words");
 constexpr int GROUP24_MAX = 8;
-struct Gemv24Group {
-    int n_layers, B, y_fp32, pad;
-    Gemv24Layer l[GROUP24_MAX];
+template <int CAP>
+struct Gemv24Args {
+    int block0[GROUP24_MAX];  // first workgroup of each layer, INT_MAX past the last
+    int B, y_fp32, waves, pad[5];
+    Gemv24Layer l[CAP];
 };
+typedef uint32_t uint16v __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(4))) char* kernarg_ptr;
+
+// What is needed late or seldom is read from the arguments there (the compiler would read it first and keep it in spilled registers).
+// Addresses made of scalar words are told to be global: a flat store makes the compiler drain all loads before it reuses a register.
+template <typename T>
+__device__ __forceinline__ T* global_at(uint64_t address) { return (T*)(__attribute__((address_space(1))) T*)address; }
+struct Scratch24 { float* part; uint32_t* count; };
+__device__ __forceinline__ Scratch24 scratch_of(kernarg_ptr layer) {
+    typedef uint64_t uint64v2 __attribute__((ext_vector_type(2)));
+    uint64v2 v;
+    asm volatile("s_load_dwordx4 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&s"(v) : "s"(layer), "n"(128));
+    return {global_at<float>(v[0]), global_at<uint32_t>(v[1])};
+}
+__device__ __forceinline__ TiledPlanes planes_of(kernarg_ptr layer) {
+    asm volatile("" : "+s"(layer));
+    TiledPlanes p;
+    __builtin_memcpy(&p, layer + offsetof(Gemv24Layer, p), sizeof(p));
+    return p;
+}
+
+// The scatter table (as build_luts makes it, with selectors for low and high bytes in a register each), made by the compiler: a workgroup copies it from memory straight to LDS, eight lanes an entry,
+// while its first loads are on their way (built by 256 threads of the workgroup it took 1000 cycles of all of them).
+constexpr uint32_t scatter_bits(uint32_t v) { uint32_t c = 0; for (; v; v &= v - 1) c++; return c; }
+template <int N8>
+struct ScatterTab {
+    uint32_t e[256][4];
+    constexpr ScatterTab() : e() {
+        for (uint32_t mb = 0; mb < 256; mb++)
+            for (int p = 0; p < 8; p++) {
+                uint32_t two = 0x0C0Cu;
+                if ((mb >> p) & 1u) {
+                    const uint32_t aug = scatter_bits(mb) == N8 - 1 ? (mb | (~mb & (mb + 1u))) : mb;
+                    int r = (int)scatter_bits(aug & ((1u << p) - 1u));
+                    if (N8 == 6 && p >= 4) r -= 2;
+                    r = r < 0 ? 0 : (r > 3 ? 3 : r);
+                    two = (uint32_t)r | ((uint32_t)(4 + r) << 8);
+                }
+                e[mb][p >> 1] |= two << (16 * (p & 1));
+            }
+    }
+};
+static __device__ const ScatterTab<4> scatter_tab4{};
+static __device__ const ScatterTab<6> scatter_tab6{};
 
 // Dynamic LDS of a workgroup: [0, 16) the ticket of the column splits; dense modes: the scatter table (32 KB); then one
 // region of WREG bytes per wavefront.
 constexpr int LDS24_HEAD = 16;
 
+// layer = its descriptor among the kernel arguments, ha / hb = the descriptor's first 32 words.
 template <int MODE, bool HAS_RES, bool MULTI>
-__device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, const int y_fp32, const int gr, const int ks,
-                                            char* const dyn) {
-    const TiledPlanes& p = d.p;
-    const __half* __restrict__ const x = d.x;
-    void* __restrict__ const y = d.y;
-    const int R = d.R, SPS = d.SPS, PHT = d.PHT, WREG = d.WREG, REC_OFF = d.REC_OFF, PART_OFF = d.PART_OFF, XS = d.XS;
-    float* __restrict__ const ws_part = d.ws_part;
-    uint32_t* __restrict__ const ws_count = d.ws_count;
+__device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint16v ha, const uint16v hb, const int B, const int y_fp32,
+                                            const int waves, const int local, char* const dyn) {
+    auto ptr = [](uint32_t lo, uint32_t hi) { return (uint64_t)lo | (uint64_t)hi << 32; };
+    const char* const image = global_at<const char>(ptr(ha[0], ha[1]));
+    const __half* __restrict__ const x = global_at<const __half>(ptr(ha[2], ha[3]));
+    const uint32_t* const sal_tab = global_at<const uint32_t>(ptr(ha[4], ha[5]));
+    const int K = (int)ha[12], nsb = (int)ha[13], nrt = (int)ha[14], R = (int)ha[15];
+    const int SPS = (int)hb[0], PHT = (int)hb[1], WREG = (int)hb[2], REC_OFF = (int)hb[3], PART_OFF = (int)hb[4], XS = (int)hb[6];
+    const int V = MULTI ? (int)hb[5] : 1;                        // visits per wavefront
+    const int G = (int)hb[7], S = (int)hb[8], sal_chunks = (int)hb[10], n = (int)hb[11];
+    const int ks = S == 1 ? 0 : G == 1 ? local : (int)(((uint64_t)(uint32_t)local * hb[12]) >> 32);    // local / G
+    const int gr = local - ks * G;
     uint32_t& ticket = *reinterpret_cast<uint32_t*>(dyn);
-    const int V = MULTI ? d.V : 1;                               // visits per wavefront
     constexpr int N8 = MODE == 6 ? 6 : 4;
     typedef typename TileOf<MODE>::type Tile;
     ScatterLds* const lut = reinterpret_cast<ScatterLds*>(dyn + LDS24_HEAD);      // dense modes: the scatter table, eight copies
     // Each wavefront owns a region of LDS of WREG bytes: its slice of x ([row][1040 bytes], B rows and one of zeros),
-    // its 16 salient-column records at REC_OFF, its partial products [PHT][256] fp32 at PART_OFF (with one visit
+    // its 16 salient-column records at REC_OFF, its partial products [PHT][16][B] fp32 at PART_OFF (with one visit
     // per wavefront: 0, on top of the x rows, which are in registers by then).  A wavefront stages all of it itself,
     // so nothing before the first reduction needs a barrier and every wavefront starts on its tiles as soon as its
     // data is there.
@@ -313,16 +384,15 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
     char* const lds_base = dyn + LDS24_HEAD + (MODE == 2 ? 0 : (int)sizeof(ScatterLds));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = lane & 15, g = lane >> 4;
-    const int nthr = blockDim.x;                                  // at least 64 * SPS: one wavefront per superblock of the split
-    const int S = d.S;
+    const int nthr = 64 * waves;                                  // at least 64 * SPS: one wavefront per superblock of the split
     const int sb = ks * SPS * V + wave;                           // superblock of the first visit
     const int r0 = gr * R;
-    const int r1 = r0 + R < p.nrt ? r0 + R : p.nrt;
+    const int r1 = r0 + R < nrt ? r0 + R : nrt;
     const int rl = r1 - 1;
-    const bool active = wave < SPS && sb < p.nsb;                 // uniform per wavefront (a launch of several layers has the widest layer's wavefronts)
-    const int Wa = p.nsb - ks * SPS * V < SPS ? p.nsb - ks * SPS * V : SPS;   // wavefronts with work
-    auto sb_of = [&](int v) { return sb + v * SPS < p.nsb ? sb + v * SPS : sb; };       // a visit past the last superblock re-reads the first
-    auto tile_of = [&](int rt, int v = 0) { return rt * p.nsb + sb_of(v); };
+    const bool active = wave < SPS && sb < nsb;                 // uniform per wavefront (a launch of several layers has the widest layer's wavefronts)
+    const int Wa = nsb - ks * SPS * V < SPS ? nsb - ks * SPS * V : SPS;   // wavefronts with work
+    auto sb_of = [&](int v) { return sb + v * SPS < nsb ? sb + v * SPS : sb; };       // a visit past the last superblock re-reads the first
+    auto tile_of = [&](int rt, int v = 0) { return rt * nsb + sb_of(v); };
     auto clamp = [&](int rt) { return rt < rl ? rt : rl; };
     const uint32_t o8 = (uint32_t)lane * 8u, o4 = (uint32_t)lane * 4u, o2 = (uint32_t)lane * 2u;
     constexpr int XROW = 1040;                                    // bytes per staged row; the 16-byte skew spreads rows over banks
@@ -330,61 +400,64 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
     float* const part = reinterpret_cast<float*>(wreg + PART_OFF);
     uint32_t* const recs = reinterpret_cast<uint32_t*>(wreg + REC_OFF);         // [visit][block g][half][record 0 / 1] x 12
 
-    // the scatter table is built while the first loads are in flight (wavefronts without work build it right away);
-    // arithmetic and LDS stores only, the barrier comes after the staging
-    if constexpr (MODE != 2) { if (!active) build_luts<N8>(lut); }
+    // lane l's group of 8 columns when a lane holds the x of one group: column order, or (2:4) the order in which a B operand
+    // takes them, see visit_setup
+    const int cg = MODE == 2 ? 16 * ((lane >> 5) + 2 * ((lane >> 3) & 1)) + 2 * (lane & 7) + ((lane >> 4) & 1) : lane;
+    const uint32_t lds_base_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_base;
+    // the scatter table: 8 entries a load, the loads dealt to all wavefronts
+    if constexpr (MODE != 2) {
+        const void* const tab = N8 == 6 ? (const void*)scatter_tab6.e : (const void*)scatter_tab4.e;
+        for (int u = wave; u < 32; u += waves)
+            load_to_lds24(lds_base_a - (uint32_t)sizeof(ScatterLds) + 1024u * (uint32_t)u, 128u * (uint32_t)u + 16u * (uint32_t)(lane >> 3), tab);
+        if (!active) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    }
     half16_t xr[8];                                              // MODE 2: B operands of the 8 steps of a block
     half8_t xd[16];                                              // dense modes: of the 16 steps
     Res24 inv[2];                                                // first record of the lane's block, per half
     ResSel sel2[2];                                              // second record (half blocks with 9..16 salient columns)
     uint32_t xs2[2][4];
     int nch0 = 0, nch1 = 0;
-    Tile t0 = {}, t1 = {}, t2 = {};
+    Tile t0 = {}, t1 = {}, t2 = {}, t3 = {};
     constexpr int LMAIN = TileOf<MODE>::lmain;
     constexpr int L = LMAIN + (HAS_RES ? LRES24 : 0);            // loads per tile in the streaming loop
-    const char* const image = d.image;
     const uint32_t o12 = o4 * 3u;
-    const LaneOff24 lo = {d.off_mask + o8, d.off_sign + (MODE == 6 ? o12 : o4), d.off_region + (MODE == 6 ? o12 : o8),
-                          d.off_scales + o8, d.off_res_scale + o2, d.off_res_t + o4};
-    auto fetch_tile = [&](Tile& t, int rt, int v) {
-        fetch24<HAS_RES>(t, image, tile_of(__builtin_amdgcn_readfirstlane(rt), __builtin_amdgcn_readfirstlane(v)), lo);
-    };
+    const LaneOff24 lo = {ha[6] + o8, ha[7] + (MODE == 6 ? o12 : o4), ha[8] + (MODE == 6 ? o12 : o8), ha[9] + o8, ha[10] + o2, ha[11] + o4};
+    uint4_t xq = {0u, 0u, 0u, 0u};                               // x of the lane's group cg (one row of x, one visit)
     if (MULTI && active) {
         // ---- several visits: the slices of x and the record sets go from global memory straight to LDS (no staging
         //      registers); rows of zeros, the zero pads behind the rows and the lanes past column k are stored first ----
         const uint4_t zero = {0u, 0u, 0u, 0u};
         for (int v = 0; v < V; v++) {
             const int sbv = sb + v * SPS;
-            if (sbv >= p.nsb) break;
+            if (sbv >= nsb) break;
             char* slice = wreg + v * XS;
-            if (sbv * 512 + 512 > p.k)
+            if (sbv * 512 + 512 > K)
                 for (int b = 0; b < B; b++) *reinterpret_cast<uint4_t*>(slice + b * XROW + lane * 16) = zero;
-            if (B < 16) *reinterpret_cast<uint4_t*>(slice + B * XROW + lane * 16) = zero;
+            if (B > 1 && B < 16) *reinterpret_cast<uint4_t*>(slice + B * XROW + lane * 16) = zero;
             if (HAS_RES && lane <= B && lane < 16) *reinterpret_cast<uint4_t*>(slice + lane * XROW + 1024) = zero;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
-        const uint32_t lds_w = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)wreg;
+        const uint32_t lds_w = lds_base_a + (uint32_t)(wave * WREG);
         for (int v = 0; v < V; v++) {
             const int sbv = sb + v * SPS;
-            if (sbv >= p.nsb) break;
+            if (sbv >= nsb) break;
             const int col = sbv * 512 + lane * 8;
-            if (col < p.k)
+            if (col < K)
                 for (int b = 0; b < B; b++)
-                    load_to_lds24(lds_w + v * XS + b * XROW, (uint32_t)(b * p.k + col) * 2u, x);
+                    load_to_lds24(lds_w + v * XS + b * XROW, (uint32_t)(b * K + col) * 2u, x);
             if (HAS_RES && lane < 48) {
                 const int rI = lane / 6, rc = (lane - 6 * rI) / 3, rpc = lane % 3;
-                const uint32_t off = (uint32_t)((((sbv * 8 + rI) * p.sal_chunks + (rc < p.sal_chunks ? rc : 0)) * 12 + 4 * rpc) * 4);
-                load_to_lds24(lds_w + REC_OFF + v * 768, off, p.sal_tab);
+                const uint32_t off = (uint32_t)((((sbv * 8 + rI) * sal_chunks + (rc < sal_chunks ? rc : 0)) * 12 + 4 * rpc) * 4);
+                load_to_lds24(lds_w + REC_OFF + v * 768, off, sal_tab);
             }
         }
-        fetch24<HAS_RES>(t0, image, tile_of(clamp(r0)), lo);
-        if constexpr (MODE != 2) build_luts<N8>(lut);
+        fetch24<HAS_RES>(t0, image, tile_of(clamp(r0)), lo, 1);
         asm volatile("s_waitcnt vmcnt(%0)" : : "n"(L) : "memory");
         if (HAS_RES && lane < 48 && lane % 3 == 2) {
             // the pieces with the column positions become byte offsets inside a staged row (see below)
             const uint32_t g2 = (uint32_t)(lane / 12) * (128u * 0x00010001u);
             for (int v = 0; v < V; v++) {
-                if (sb + v * SPS >= p.nsb) break;
+                if (sb + v * SPS >= nsb) break;
                 uint4_t sr = *reinterpret_cast<const uint4_t*>(&recs[v * 192 + 4 * lane]);
 #pragma unroll
                 for (int w = 0; w < 4; w++) {
@@ -400,11 +473,11 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
         // ---- all loads go out before the first wait: lane l brings columns 8l .. 8l+7 of the superblock for every
         //      batch row (one 16-byte load per row), lanes 0..47 the 16-byte pieces of the (block, half) records, then
         //      the packed planes of the first row tile ----
-        const int col = sb * 512 + lane * 8;
-        const bool col_ok = col < p.k;
+        const int col = sb * 512 + cg * 8;
+        const bool col_ok = col < K;
         const __half* xsrc = x + (col_ok ? col : 0);
         uint4_t sx0, sx1, sx2, sx3, sx4, sx5, sx6, sx7, sx8, sx9, sx10, sx11, sx12, sx13, sx14, sx15;
-#define STB24_LOAD(u, reg) { const __half* a = xsrc + (int64_t)(u) * p.k; asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(reg) : "v"(a)); }
+#define STB24_LOAD(u, reg) { const __half* a = xsrc + (int64_t)(u) * K; asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(reg) : "v"(a)); }
         // B loads per lane; the conditions are nested so that a small batch passes few of them
         STB24_LOAD(0, sx0)
         if (B > 1) STB24_LOAD(1, sx1)
@@ -418,11 +491,10 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
         uint4_t sr = {0u, 0u, 0u, 0u};
         if (HAS_RES && lane < 48) {                  // (block, half) lane / 6, record (lane % 6) / 3 of it, 16-byte piece lane % 3
             const int rI = lane / 6, rc = (lane - 6 * rI) / 3, rpc = lane % 3;
-            const uint32_t* src = p.sal_tab + (((int64_t)sb * 8 + rI) * p.sal_chunks + (rc < p.sal_chunks ? rc : 0)) * 12 + 4 * rpc;
+            const uint32_t* src = sal_tab + (((int64_t)sb * 8 + rI) * sal_chunks + (rc < sal_chunks ? rc : 0)) * 12 + 4 * rpc;
             asm volatile("global_load_dwordx4 %0, %1, off" : "+v"(sr) : "v"(src));
         }
-        fetch24<HAS_RES>(t0, image, tile_of(clamp(r0)), lo);
-        if constexpr (MODE != 2) build_luts<N8>(lut);
+        fetch24<HAS_RES>(t0, image, tile_of(clamp(r0)), lo, 1);
         // The second and third tile go out after the operands are in registers: a compute unit keeps a limited
         // number of loads in flight, and the other wavefront of the SIMD should get its first tile early too
         // (issuing them here instead was measured: no faster with one wavefront per SIMD, slower with two).
@@ -434,8 +506,9 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
                        "+v"(sr)
                      : "n"(L));
         {
-            char* dst = wreg + lane * 16;
+            char* dst = wreg + cg * 16;
             const uint4_t zero = {0u, 0u, 0u, 0u};
+            xq = col_ok ? sx0 : zero;
 #define STB24_STORE(u, reg) *reinterpret_cast<uint4_t*>(dst + (u) * XROW) = col_ok ? reg : zero;
             STB24_STORE(0, sx0)
             if (B > 1) STB24_STORE(1, sx1)
@@ -446,7 +519,7 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
                 if (B > 12) STB24_STORE(12, sx12) if (B > 13) STB24_STORE(13, sx13) if (B > 14) STB24_STORE(14, sx14) if (B > 15) STB24_STORE(15, sx15)
             }
 #undef STB24_STORE
-            if (B < 16) *reinterpret_cast<uint4_t*>(dst + B * XROW) = zero;     // row B: zeros, read by the lanes without a batch row
+            if (B > 1 && B < 16) *reinterpret_cast<uint4_t*>(dst + B * XROW) = zero;     // row B: zeros, read by the lanes without a batch row
             if (HAS_RES) {
                 // the 16 bytes after each row's 1024: zeros, the target of the table entries that hold no column
                 if (lane <= B && lane < 16) *reinterpret_cast<uint4_t*>(wreg + lane * XROW + 1024) = zero;
@@ -474,9 +547,40 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
     auto visit_setup = [&](int v) {
         const char* const xsl = wreg + v * XS;
         const uint32_t* const recv = recs + v * 192;
-        if constexpr (MODE == 2) {
+        const int brow = B == 1 ? 0 : i < B ? i : B;                            // the lane's staged row of x (or the zeros)
+        if (B == 1) {
+            // One row of x: only column 0 of the product is wanted, i.e. only lane 16g of a B operand matters, and its x is
+            // a few lanes up in the same row of 16 lanes: moves between registers instead of 16 LDS reads a wavefront, which all
+            // wavefronts of the workgroup made at once (1500 cycles of set-up).  Lane 16g' + u has group u of block g' or, for
+            // 2:4, elements 8 (u / 8) .. of step u % 8 (the columns named below).
+            if (MULTI) xq = *reinterpret_cast<const uint4_t*>(xsl + cg * 16);
+            auto up = [&](auto t) {
+                uint4 r;
+                constexpr int T = decltype(t)::value;
+                if constexpr (T == 0) r = make_uint4(xq[0], xq[1], xq[2], xq[3]);
+                else r = make_uint4(__builtin_amdgcn_update_dpp(0, xq[0], 0x100 + T, 15, 15, true), __builtin_amdgcn_update_dpp(0, xq[1], 0x100 + T, 15, 15, true),
+                                    __builtin_amdgcn_update_dpp(0, xq[2], 0x100 + T, 15, 15, true), __builtin_amdgcn_update_dpp(0, xq[3], 0x100 + T, 15, 15, true));
+                return r;
+            };
+            typedef uint32_t uint8_vec __attribute__((ext_vector_type(8)));
+            auto put = [&](auto t) {
+                constexpr int T = decltype(t)::value;
+                if constexpr (MODE != 2) xd[T] = __builtin_bit_cast(half8_t, up(t));
+                else if constexpr (T < 8) {
+                    const uint4 a = up(t), c = up(std::integral_constant<int, T + 8>());
+                    const uint8_vec w = {a.x, a.y, a.z, a.w, c.x, c.y, c.z, c.w};
+                    xr[T] = __builtin_bit_cast(half16_t, w);
+                }
+            };
+            put(std::integral_constant<int, 0>()); put(std::integral_constant<int, 1>()); put(std::integral_constant<int, 2>());
+            put(std::integral_constant<int, 3>()); put(std::integral_constant<int, 4>()); put(std::integral_constant<int, 5>());
+            put(std::integral_constant<int, 6>()); put(std::integral_constant<int, 7>()); put(std::integral_constant<int, 8>());
+            put(std::integral_constant<int, 9>()); put(std::integral_constant<int, 10>()); put(std::integral_constant<int, 11>());
+            put(std::integral_constant<int, 12>()); put(std::integral_constant<int, 13>()); put(std::integral_constant<int, 14>());
+            put(std::integral_constant<int, 15>());
+        } else if constexpr (MODE == 2) {
             // B lane 16*g + n: elements 0..7 <-> block g/2, elements 8..15 <-> block 2 + g/2, columns 16*s + 8*(g%2) ..
-            const char* xrow = xsl + (i < B ? i : B) * XROW + (g >> 1) * 256 + (g & 1) * 16;
+            const char* xrow = xsl + brow * XROW + (g >> 1) * 256 + (g & 1) * 16;
 #pragma unroll
             for (int s = 0; s < 8; s++) {
                 const uint4_t lo = *reinterpret_cast<const uint4_t*>(xrow + 32 * s);
@@ -487,12 +591,12 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             }
         } else {
             // B lane 16*g + n of step t: columns 8t .. 8t+7 of block g
-            const char* xrow = xsl + (i < B ? i : B) * XROW + g * 256;
+            const char* xrow = xsl + brow * XROW + g * 256;
 #pragma unroll
             for (int t = 0; t < 16; t++) xd[t] = __builtin_bit_cast(half8_t, *reinterpret_cast<const uint4_t*>(xrow + 16 * t));
         }
         if (HAS_RES) {
-            const char* xrow0 = xsl + (i < B ? i : B) * XROW;               // the lane's staged row of x (or the zeros)
+            const char* xrow0 = xsl + brow * XROW;
             auto gather = [&](const uint4_t& q, uint32_t out[4]) {          // x at the 8 byte offsets of a record
                 const uint32_t qw[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -522,7 +626,7 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             }
         }
     };
-    // producer side of the three tile buffers.  Order of the products of a workgroup: phase by phase (PHT row tiles),
+    // producer side of the tile buffers.  Order of the products of a workgroup: phase by phase (PHT row tiles),
     // inside a phase visit by visit, inside a visit row tile by row tile -- so that a wavefront takes the operands of a
     // visit (64 registers of x, the gathered salient x) once per phase and visit, not once per product.
     int p_ph0 = r0, p_n = r1 - r0 < PHT ? r1 - r0 : PHT, p_i = 0, p_v = 0;
@@ -532,13 +636,13 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             if (++p_v == V) { p_v = 0; p_ph0 += p_n; p_n = r1 - p_ph0 < PHT ? r1 - p_ph0 : PHT; }
         }
     };
-    auto fetch_next = [&](Tile& t) {
-        if (p_n > 0) {
-            fetch_tile(t, p_ph0 + p_i, p_v);
-            advance();
-        } else {
-            fetch_tile(t, rl, V - 1);                // past the end: the last one again (same number of loads on every path)
-        }
+    int left = (r1 - r0) * V;                        // products still to come
+    const int prio3 = __builtin_amdgcn_readfirstlane(left >> 1);
+    auto fetch_next = [&](Tile& t) {                 // (past the end: nothing)
+        const int rt = p_n > 0 ? p_ph0 + p_i : r0, v = p_n > 0 ? p_v : 0;
+        fetch24<HAS_RES>(t, image, tile_of(__builtin_amdgcn_readfirstlane(rt), __builtin_amdgcn_readfirstlane(v)), lo,
+                         __builtin_amdgcn_readfirstlane(p_n > 0 ? 1 : 0));
+        if (p_n > 0) advance();
     };
     if (active) {
         if (!MULTI) visit_setup(0);
@@ -554,13 +658,14 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
     uint32_t T0 = 0x09080404u, T1 = 0x0E0E0D0Cu, K7 = 0x07070707u, K3 = 0x03030303u, K4 = 0x04000400u, KS = 0x80008000u;
     asm volatile("" : "+v"(T0), "+v"(T1), "+v"(K7), "+v"(K3), "+v"(K4), "+v"(KS));
 
-    const int64_t n16 = (int64_t)p.nrt * 16;
+    const uint64_t y = ptr(hb[14], hb[15]);
+    const int64_t n16 = (int64_t)nrt * 16;
     const uint32_t b_magic = B > 1 ? (uint32_t)((0x100000000ull + (uint32_t)B - 1) / (uint32_t)B) : 0u;
     auto div_b = [&](int v) { return B > 1 ? (int)__umulhi((uint32_t)v, b_magic) : v; };     // v / B, v < 2^27
     auto store_y = [&](int row, int b, float s) {
-        if (b < B && row < p.n) {
-            if (y_fp32) reinterpret_cast<float*>(y)[(int64_t)b * p.n + row] = -s;
-            else reinterpret_cast<__half*>(y)[(int64_t)b * p.n + row] = __float2half(-s);
+        if (b < B && row < n) {
+            if (y_fp32) global_at<float>(y)[(int64_t)b * n + row] = -s;
+            else global_at<__half>(y)[(int64_t)b * n + row] = __float2half(-s);
         }
     };
 
@@ -602,6 +707,8 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             for (int h = 0; h < 2; h++) {
                 HalfData<N8> d;
                 half_of(tr, h, d);
+                uint32_t Q[2 * N8];
+                half_codes<N8>(d, Q);
                 constexpr int D = 4;                                  // table reads run D groups ahead
                 uint4 gl[D];
 #pragma unroll
@@ -611,13 +718,12 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
                     const uint4 cur = gl[t % D];
                     if (t + D < 8) gl[t % D] = lut_fetch<N8>(d, t + D, lut, lane & 7);
                     uint32_t o[4];
-                    expand8<N8>(d, TL, TH, t, cur, K3, K4, KS, o);
+                    expand8<N8>(Q, TL, TH, TH | 0x80808080u, t, cur, o);
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(o), xd[8 * h + t], acc, 0, 0, 0);
                 }
             }
         }
         if (HAS_RES) {
-            wait24_res<2 * L>(tr);                    // the tile's res_t word: younger than its packed planes
             const uint32_t ar1 = tr.ar & 0xFFFFu, ar2 = ar1 | (ar1 << 16);
 #pragma unroll
             for (int h = 0; h < 2; h++) {
@@ -634,27 +740,33 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             }
         }
     };
+    // partial products in LDS: [slot][row of the tile as 4 v + g][row of x]
     auto store_partial = [&](int slot) {
-        float* dst = part + (slot * 256 + lane);
+        float* dst = part + (slot * 16 + g) * B + i;
+        if (i < B) {
 #pragma unroll
-        for (int v = 0; v < 4; v++) dst[64 * v] = acc[v];
+            for (int v = 0; v < 4; v++) dst[4 * v * B] = acc[v];
+        }
         acc = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
 
     auto add_partial = [&](int slot) {
-        float* dst = part + (slot * 256 + lane);
+        float* dst = part + (slot * 16 + g) * B + i;
+        if (i < B) {
 #pragma unroll
-        for (int v = 0; v < 4; v++) dst[64 * v] += acc[v];
+            for (int v = 0; v < 4; v++) dst[4 * v * B] += acc[v];
+        }
         acc = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
 
     // Half blocks with more than 16 salient columns: the records after the second, outside the streaming loop (rare).
     auto extra_records = [&](int rt, int v) {
-        const int64_t rstride = (int64_t)p.res_words * 16;
-        const int q = 4 * sb_of(v) + g;
-        const bool live = i < B && q < p.nb;
-        const unsigned short* xg = reinterpret_cast<const unsigned short*>(x + (int64_t)(i < B ? i : B - 1) * p.k + (int64_t)(q < p.nb ? q : 0) * 128);
+        const int q = 4 * sb_of(v) + g, nb = K / 128;
+        const bool live = i < B && q < nb;
+        const unsigned short* xg = reinterpret_cast<const unsigned short*>(x + (int64_t)(i < B ? i : B - 1) * K + (int64_t)(q < nb ? q : 0) * 128);
         float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        const TiledPlanes p = planes_of(layer);
+        const int64_t rstride = (int64_t)p.res_words * 16;
         for (int h = 0; h < 2; h++) {
             const int nc = h == 0 ? nch0 : nch1;
             if (nc <= 2) continue;
@@ -662,7 +774,7 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
             load_half<N8>(p, (int64_t)tile_of(rt, v), lane_offsets<N8>(lane, h), h, d);
             const uint32_t ar2 = d.ar | (d.ar << 16);
             for (int c = 2; c < nc; c++) {
-                const uint32_t* rec = p.sal_tab + (((int64_t)q * 2 + h) * p.sal_chunks + c) * 12;
+                const uint32_t* rec = sal_tab + (((int64_t)q * 2 + h) * sal_chunks + c) * 12;
                 ResSel sel;
                 sel.sel0 = rec[0]; sel.sel1 = rec[1]; sel.bit0 = rec[2]; sel.bit1 = rec[3];
                 const uint32_t ord = rec[4];
@@ -685,24 +797,31 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
         return acc;
     };
 
-    // The R row tiles are taken in phases of PHT (a multiple of 3 unless it is R itself): the wavefronts stream
+    // The R row tiles are taken in phases of PHT (a multiple of TILES24 unless it is R itself): the wavefronts stream
     // PHT tiles each, the workgroup adds the partial products in a fixed order and stores them.  Three tiles are
-    // in flight per wavefront; a fetch past the last tile re-reads that tile, which keeps the number of loads
-    // between a fetch and its wait the same on every path.
+    // in flight per wavefront besides the one it works on; the wait for a tile counts those fetched after it.
     for (int ph = 0; ph < R; ph += PHT) {
         const int ph0 = r0 + ph;
         const int ph1 = ph0 + PHT < r1 ? ph0 + PHT : r1;
         if (active) {
-            // consumer side of the three tile buffers: the (visit, row tile) of the next product, in the producer's
+            // consumer side of the tile buffers: the (visit, row tile) of the next product, in the producer's
             // order.  The first visit stores a row tile's product, the others add theirs to it (LDS adds: the sum over
             // the visits is taken in visit order, whatever the launch shape of other layers).  A step past the phase's
             // last product only keeps the fetches going.
             const int cn = ph1 - ph0;
             int ci = 0, cv = cn > 0 ? 0 : V;
-            auto step = [&](Tile& t) {
-                wait24_main<2 * L + (HAS_RES ? LRES24 : 0)>(t);
+            auto step = [&](Tile& t, Tile& free) {             // free: the buffer of the step before
+                fetch_next(free);
+                // Of the two wavefronts of a SIMD the older one is served first and would be done with its tiles when the other has
+                // half of them left, which then waits out every latency alone: the one with more work left goes first.
+                asm volatile("s_cmp_gt_i32 %0, %1\n\ts_cbranch_scc1 .Lprio3%=\n\ts_cmp_gt_i32 %0, %2\n\ts_cbranch_scc1 .Lprio2%=\n\t"
+                             "s_cmp_gt_i32 %0, %3\n\ts_cbranch_scc1 .Lprio1%=\n\ts_setprio 0\n\ts_branch .Lpend%=\n.Lprio1%=:\n\ts_setprio 1\n\ts_branch .Lpend%=\n"
+                             ".Lprio2%=:\n\ts_setprio 2\n\ts_branch .Lpend%=\n.Lprio3%=:\n\ts_setprio 3\n.Lpend%=:"
+                             : : "s"(__builtin_amdgcn_readfirstlane(left)), "s"(prio3), "s"(prio3 >> 1), "s"(prio3 >> 2) : "scc");
+                --left;
+                wait24<L>(t, __builtin_amdgcn_readfirstlane(left));
                 if (cv < V) {
-                    if (sb + cv * SPS < p.nsb) {
+                    if (sb + cv * SPS < nsb) {
                         if (MULTI && ci == 0) visit_setup(cv);
                         product(t, ph0 + ci, ci);
                         if (MULTI && HAS_RES && (nch0 > 2 || nch1 > 2)) acc += extra_records(ph0 + ci, cv);
@@ -711,28 +830,26 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
                     }
                     if (++ci == cn) { ci = 0; ++cv; }
                 }
-                fetch_next(t);
             };
             while (cv < V) {
-                step(t0);
-                step(t1);
-                step(t2);
+                step(t0, t3);
+                step(t1, t0);
+                step(t2, t1);
+                step(t3, t2);
             }
             if (!MULTI && HAS_RES && (nch0 > 2 || nch1 > 2))
                 for (int rt = ph0; rt < ph1; rt++) {
-                    const float4_t e = extra_records(rt, 0);
-                    float* dst = part + ((rt - ph0) * 256 + lane);
-#pragma unroll
-                    for (int v = 0; v < 4; v++) dst[64 * v] += e[v];
+                    acc = extra_records(rt, 0);
+                    add_partial(rt - ph0);
                 }
         }
         __syncthreads();
         // outputs of this phase: (slot, b, row in tile), consecutive threads on consecutive rows
         const int total = (ph1 > ph0 ? ph1 - ph0 : 0) * B * 16;
+        float* const ws_part = S > 1 ? scratch_of(layer).part : nullptr;
         for (int o = threadIdx.x; o < total; o += nthr) {
             const int r16 = o & 15, j = div_b(o >> 4), b = (o >> 4) - j * B;
-            const int l = b + 16 * (r16 >> 2), v = r16 & 3;
-            const char* src = lds_base + PART_OFF + (j * 256 + 64 * v + l) * 4;
+            const char* src = lds_base + PART_OFF + ((j * 16 + 4 * (r16 & 3) + (r16 >> 2)) * B + b) * 4;
             float t[8];
 #pragma unroll
             for (int w = 0; w < 8; w++) t[w] = w < Wa ? *reinterpret_cast<const float*>(src + (int64_t)w * WREG) : 0.0f;   // fixed order of adds
@@ -745,12 +862,10 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
         }
         if (ph + PHT < R) __syncthreads();           // the next phase overwrites the partial products
     }
-    if (active) {
-        wait24<0>(t0);                               // drain: no load may still target a register that is reused
-        wait24<0>(t1);
-        wait24<0>(t2);
-    }
     if (S == 1) return;
+    const Scratch24 scratch = scratch_of(layer);
+    float* const ws_part = scratch.part;
+    uint32_t* const ws_count = scratch.count;
 
     // ---- several column splits: the partial sums are in the workspace [split][16][n16]; take a ticket.  They are
     //      written and read with agent-scope accesses, so no cache write-back or invalidate is needed: the stores
@@ -778,27 +893,45 @@ __device__ __forceinline__ void gemv24_body(const Gemv24Layer& d, const int B, c
     }
 }
 
-// The launch: workgroup b belongs to the layer whose range of workgroups holds b and runs that layer's variant of
-// the body.  Every variant fits two wavefronts per SIMD, so putting them into one kernel costs no occupancy.
-__global__ __launch_bounds__(512) void gemv24_group_kernel(const Gemv24Group a) {
+// 64 bytes of the arguments as one scalar load.
+__device__ __forceinline__ uint16v scalar16(kernarg_ptr p) {
+    return *(const __attribute__((address_space(4))) uint16v*)p;
+}
+
+// A launch of one layer.
+template <int MODE, bool RES, bool MULTI>
+__global__ __launch_bounds__(512) void gemv24_kernel(const Gemv24Args<1> a) {
     extern __shared__ __attribute__((aligned(16))) char dyn24[];
-    int li = 0;
-    for (int l = 1; l < a.n_layers; l++)
-        if ((int)blockIdx.x >= a.l[l].block0) li = l;
-    li = __builtin_amdgcn_readfirstlane(li);
-    // the descriptor comes out of the kernel-argument segment with scalar loads (indexing the by-value argument would
-    // make a private copy of it, and the plane pointers must sit in scalar registers)
-    typedef const __attribute__((address_space(4))) char* kernarg_ptr;
+    const kernarg_ptr ka = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr(), layer = ka + offsetof(Gemv24Args<1>, l);
+    uint16v ha = scalar16(layer), hb = scalar16(layer + 64);
+    int B = a.B, y_fp32 = a.y_fp32, waves = a.waves;
+    asm volatile("" : "+s"(ha), "+s"(hb), "+s"(B), "+s"(y_fp32), "+s"(waves));
+    gemv24_body<MODE, RES, MULTI>(layer, ha, hb, B, y_fp32, waves, (int)blockIdx.x, dyn24);
+}
+
+// A launch of several: a workgroup belongs to the layer whose range of workgroups holds its index and runs that layer's variant of
+// the body.  Every variant fits two wavefronts per SIMD, so putting them into one kernel costs no occupancy.
+__global__ __launch_bounds__(512) void gemv24_group_kernel(const Gemv24Args<GROUP24_MAX> a) {
+    extern __shared__ __attribute__((aligned(16))) char dyn24[];
     const kernarg_ptr ka = (kernarg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-    Gemv24Layer d;
-    __builtin_memcpy(&d, ka + offsetof(Gemv24Group, l) + (size_t)li * sizeof(Gemv24Layer), sizeof(Gemv24Layer));
-    const int local = (int)blockIdx.x - d.block0;
-    const int ks = local / d.G, gr = local - ks * d.G;
-    switch (d.variant) {
-#define STB24_CASE(MODE, RES, MULTI) case (MODE | (RES ? 8 : 0) | (MULTI ? 16 : 0)): gemv24_body<MODE, RES, MULTI>(d, a.B, a.y_fp32, gr, ks, dyn24); break;
-        STB24_CASE(2, false, false) STB24_CASE(2, true, false) STB24_CASE(2, false, true) STB24_CASE(2, true, true)
-        STB24_CASE(4, false, false) STB24_CASE(4, true, false) STB24_CASE(4, false, true) STB24_CASE(4, true, true)
-        STB24_CASE(6, false, false) STB24_CASE(6, true, false) STB24_CASE(6, false, true) STB24_CASE(6, true, true)
+    uint16v head = scalar16(ka);
+    asm volatile("" : "+s"(head));
+    int li = 0, first = 0;
+#pragma unroll
+    for (int l = 1; l < GROUP24_MAX; l++)
+        if ((int)blockIdx.x >= (int)head[l]) { li = l; first = (int)head[l]; }
+    li = __builtin_amdgcn_readfirstlane(li);
+    const kernarg_ptr layer = ka + offsetof(Gemv24Args<GROUP24_MAX>, l) + (size_t)li * sizeof(Gemv24Layer);
+    uint16v ha = scalar16(layer), hb = scalar16(layer + 64);
+    asm volatile("" : "+s"(ha), "+s"(hb));
+    const int local = (int)blockIdx.x - first, B = (int)head[8], y_fp32 = (int)head[9], waves = (int)head[10];
+    switch (hb[9]) {
+#define STB24_CASE(MODE, RES, MULTI) case (MODE | (RES ? 8 : 0) | (MULTI ? 16 : 0)): gemv24_body<MODE, RES, MULTI>(layer, ha, hb, B, y_fp32, waves, local, dyn24); break;
+#define STB24_ALL(X) \
+        X(2, false, false) X(2, true, false) X(2, false, true) X(2, true, true) \
+        X(4, false, false) X(4, true, false) X(4, false, true) X(4, true, true) \
+        X(6, false, false) X(6, true, false) X(6, false, true) X(6, true, true)
+        STB24_ALL(STB24_CASE)
 #undef STB24_CASE
         default: break;
     }
@@ -902,8 +1035,9 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
                                       void* const* ys, int y_fp32, void* const* counters, void* const* partials,
                                       const int64_t* partial_bytes, void* stream, int* hip_err) {
     if (n_layers < 1 || n_layers > GROUP24_MAX || B < 1 || B > 16) return STB_EUNSUPPORTED;
-    Gemv24Group a;
-    a.n_layers = n_layers; a.B = B; a.y_fp32 = y_fp32; a.pad = 0;
+    Gemv24Args<GROUP24_MAX> a;
+    std::memset(&a, 0, sizeof(a));
+    a.B = B; a.y_fp32 = y_fp32;
     const int xbytes = (B < 16 ? B + 1 : 16) * 1040;
     int blocks = 0, sps_max = 1;
     int64_t lds = 0;
@@ -913,7 +1047,7 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
     int64_t work[GROUP24_MAX], total_work = 0;
     for (int l = 0; l < n_layers; l++) {
         const bool sparse = Ls[l]->cfg.M == 4 && Ls[l]->cfg.N == 2;
-        const int per_tile = sparse ? 314 : stb_tiled_slots(&Ls[l]->cfg) == 6 ? 560 : 378;
+        const int per_tile = sparse ? 314 : stb_tiled_slots(&Ls[l]->cfg) == 6 ? 434 : 335;
         work[l] = (int64_t)Ls[l]->n_row_tiles * Ls[l]->n_super * per_tile;
         total_work += work[l];
     }
@@ -951,8 +1085,11 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
         d.S = plan[0]; d.R = plan[1]; d.SPS = plan[2]; d.V = plan[3]; d.WREG = plan[4]; d.REC_OFF = plan[5]; d.PART_OFF = plan[6];
         d.XS = xbytes;
         d.G = (d.p.nrt + d.R - 1) / d.R;
-        d.PHT = d.R < PHASE24 ? d.R : PHASE24;
-        d.block0 = blocks;
+        d.PHT = phase24(d.R, B);
+        d.g_magic = d.G > 1 ? (uint32_t)((0x100000000ull + (uint32_t)d.G - 1) / (uint32_t)d.G) : 0u;
+        d.k = d.p.k; d.n = d.p.n; d.nsb = d.p.nsb; d.nrt = d.p.nrt;
+        d.sal_tab = d.p.sal_tab; d.sal_chunks = d.p.sal_chunks;
+        a.block0[l] = blocks;
         d.variant = mode | (d.p.res_words > 0 ? 8 : 0) | (d.V > 1 ? 16 : 0);
         d.x = (const __half*)xs[l];
         d.y = ys[l];
@@ -969,14 +1106,32 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
         const int64_t need = LDS24_HEAD + (mode == 2 ? 0 : (int64_t)sizeof(ScatterLds)) + (int64_t)d.SPS * d.WREG;
         if (need > lds) lds = need;
     }
-    for (int l = n_layers; l < GROUP24_MAX; l++) a.l[l] = a.l[0];
+    for (int l = n_layers; l < GROUP24_MAX; l++) a.block0[l] = INT_MAX;
+    a.waves = sps_max;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute((const void*)gemv24_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS24 + LDS24_HEAD);
+        hipError_t e = hipFuncSetAttribute((const void*)gemv24_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS24 + LDS24_HEAD);
+#define STB24_ATTR(MODE, RES, MULTI) \
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)gemv24_kernel<MODE, RES, MULTI>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS24 + LDS24_HEAD);
+        STB24_ALL(STB24_ATTR)
+#undef STB24_ATTR
         if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(gemv24_group_kernel, dim3(blocks), dim3(64 * sps_max), (size_t)lds, (hipStream_t)stream, a);
+    const dim3 grid(blocks), threads(64 * sps_max);
+    if (n_layers == 1) {
+        Gemv24Args<1> one;
+        std::memcpy(&one, &a, sizeof(one));            // (the arguments of a launch of one are the head of the others')
+        switch (one.l[0].variant) {
+#define STB24_LAUNCH(MODE, RES, MULTI) case (MODE | (RES ? 8 : 0) | (MULTI ? 16 : 0)): \
+            hipLaunchKernelGGL((gemv24_kernel<MODE, RES, MULTI>), grid, threads, (size_t)lds, (hipStream_t)stream, one); break;
+            STB24_ALL(STB24_LAUNCH)
+#undef STB24_LAUNCH
+            default: return STB_EUNSUPPORTED;
+        }
+    } else {
+        hipLaunchKernelGGL(gemv24_group_kernel, grid, threads, (size_t)lds, (hipStream_t)stream, a);
+    }
     const hipError_t e = hipGetLastError();
     *hip_err = (int)e;
     return e == hipSuccess ? STB_OK : STB_EHIP;

@@ -520,6 +520,42 @@ def test_gemv_small(small_case, torch_cuda, B, y_fp32):
             _within_bound(yd.float().cpu().numpy(), y_ref, bound, f"gemv B={B} ({visits} visits per wavefront)")
 
 
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (6, 8)])
+@pytest.mark.parametrize("tiles", [1, 2, 3, 4, 5, 8, 13, 17, 241])
+def test_gemv_with_any_number_of_tiles_a_wavefront(tiles, N, M, torch_cuda):
+    """A wavefront keeps up to four row tiles on their way and adds up in phases: every remainder of both, for one row of x (its
+    operands move between registers), two and sixteen (through LDS).  1 to 241 row tiles a wavefront on 256 workgroups of one,
+    against float64 on the dequantised weights; the tolerance is that of the other products."""
+    torch = torch_cuda
+    n, k = 16 * 256 * (tiles - 1) + 5, 384
+    g = torch.Generator(device="cuda").manual_seed(tiles)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    xnorm = torch.rand(k, generator=g, device="cuda") + 0.5
+    bits = np.zeros(k, dtype=np.uint8)
+    bits[[2, 77, 130, 290] + list(range(200, 230))] = 1           # more than 8 and more than 16 in a half block
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 0)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    _say(f"[case] gemv {n}x{k} {N}:{M}, {tiles} tiles a wavefront")
+    S.stb_pack_device(W, xnorm, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    for B in (1, 2, 16):
+        x = torch.randn((B, k), generator=g, device="cuda").half()
+        y = torch.full((B, n), float("nan"), dtype=torch.float32, device="cuda")
+        ws = S.new_device_scratch(S.stb_gemv_workspace_bytes(cfg, B), zero=True)
+        S.stb_gemv(tl, x, B, y, True, ws)
+        torch.cuda.synchronize()
+        ref = x.double() @ What.double().t()
+        bound = x.double().abs() @ What.double().abs().t()
+        assert bool(((y.double() - ref).abs() <= 2e-3 * bound).all()), (tiles, B)
+        assert float((y.double() - ref).norm() / ref.norm()) < 2e-6, (tiles, B)      # (fp32 sums of 384 exact products)
+
+
 def test_gemv_with_planes_more_than_4_gib_apart(torch_cuda):
     """The default decode kernel addresses the streamed planes of a layer from one scalar base with 32-bit offsets, so
     it takes a layout only if its planes lie within 4 GiB of each other; any other layout (planes bound one by one to
