@@ -205,52 +205,6 @@ __device__ inline void half_of(const Tile68& t, int h, HalfData<6>& d) {
     d.r[0] = h == 0 ? t.r0[0] : t.r1[0]; d.r[1] = h == 0 ? t.r0[1] : t.r1[1]; d.r[2] = h == 0 ? t.r0[2] : t.r1[2];
 }
 
-// The kept weights of a half block as codes, four slots a register: byte j of Q[b] = id of slot 4 b + j | its sign bit << 2, which is
-// what v_perm_b32 takes as selectors for eight bytes (four scales, plus and minus).  16 slots at a time: rw = their ids, the half
-// `hi16` of sw their sign bits.  The fields are parted over all four bytes of a word at once and then transposed: 6 instructions for
-// four slots (9 with each pair of slots expanded on its own, of which a tile of 4:8 then took 394 vector instructions instead of 320,
-// one of 6:8 524 instead of 404).
-__device__ inline void slot_codes(uint32_t rw, uint32_t sw, bool hi16, uint32_t Q[4]) {
-    const uint32_t K3 = 0x03030303u, K4 = 0x04040404u;
-    const uint32_t t = perm(sw, sw, hi16 ? 0x0C030C02u : 0x0C010C00u);        // sign bits of slots 0..7 | 8..15 << 16
-    const uint32_t n = (t << 4) | t;                                          // low nibble of byte b: the signs of slots 4 b ..
-    const uint32_t E0 = and_or_v(n << 2, K4, rw & K3), E1 = and_or_v(n << 1, K4, (rw >> 2) & K3);
-    const uint32_t E2 = and_or_v(n, K4, (rw >> 4) & K3), E3 = and_or_v(n >> 1, K4, (rw >> 6) & K3);
-    const uint32_t a = perm(E1, E0, 0x05010400u), b = perm(E3, E2, 0x05010400u);
-    const uint32_t c = perm(E1, E0, 0x07030602u), d = perm(E3, E2, 0x07030602u);
-    Q[0] = perm(b, a, 0x05040100u); Q[1] = perm(b, a, 0x07060302u);
-    Q[2] = perm(d, c, 0x05040100u); Q[3] = perm(d, c, 0x07060302u);
-}
-
-template <int N8>
-__device__ inline void half_codes(const HalfData<N8>& d, uint32_t (&Q)[2 * N8]) {
-#pragma unroll
-    for (int w = 0; w < N8 / 2; w++) slot_codes(d.r[w], d.s[w >> 1], w & 1, Q + 4 * w);
-}
-
-// Expands columns 8t .. 8t+7 (t < 8) of a half block into four registers of fp16 pairs (negated weights).  TL / TH = low / high bytes
-// of the four scales (>= 0), TN = TH with the signs set; L = the group's scatter selectors: byte r of the low bytes, 4 + r of the high ones.
-template <int N8>
-__device__ inline void expand8(const uint32_t (&Q)[2 * N8], uint32_t TL, uint32_t TH, uint32_t TN, int t, const uint4& L, uint32_t out[4]) {
-    if (N8 == 4) {
-        const uint32_t lo = perm(TL, TL, Q[t]), hi = perm(TN, TH, Q[t]);
-        out[0] = perm(hi, lo, L.x);
-        out[1] = perm(hi, lo, L.y);
-        out[2] = perm(hi, lo, L.z);
-        out[3] = perm(hi, lo, L.w);
-    } else {
-        // slots 6t ..: columns 0 to 3 hold slots 0 to 3 of the group, columns 4 to 7 slots 2 to 5
-        const int q = 6 * t / 4;
-        const uint32_t mid = perm(Q[q + 1], Q[q], 0x05040302u);
-        const uint32_t A = t & 1 ? mid : Q[q], B = t & 1 ? Q[q + 1] : mid;
-        const uint32_t loA = perm(TL, TL, A), hiA = perm(TN, TH, A), loB = perm(TL, TL, B), hiB = perm(TN, TH, B);
-        out[0] = perm(hiA, loA, L.x);
-        out[1] = perm(hiA, loA, L.y);
-        out[2] = perm(hiB, loB, L.z);
-        out[3] = perm(hiB, loB, L.w);
-    }
-}
-
 // Index register for 32 columns: every mask nibble (two bits set) becomes the positions of its two kept
 // weights, low one in bits 1:0, high one in bits 3:2.  (nibble >> 1) & 7 is 1..6 for the six valid nibbles
 // and addresses an 8-byte table through v_perm_b32; a nibble of the zero padding maps to positions 0, 1.
@@ -326,30 +280,6 @@ __device__ __forceinline__ TiledPlanes planes_of(kernarg_ptr layer) {
     return p;
 }
 
-// The scatter table (as build_luts makes it, with selectors for low and high bytes in a register each), made by the compiler: a workgroup copies it from memory straight to LDS, eight lanes an entry,
-// while its first loads are on their way (built by 256 threads of the workgroup it took 1000 cycles of all of them).
-constexpr uint32_t scatter_bits(uint32_t v) { uint32_t c = 0; for (; v; v &= v - 1) c++; return c; }
-template <int N8>
-struct ScatterTab {
-    uint32_t e[256][4];
-    constexpr ScatterTab() : e() {
-        for (uint32_t mb = 0; mb < 256; mb++)
-            for (int p = 0; p < 8; p++) {
-                uint32_t two = 0x0C0Cu;
-                if ((mb >> p) & 1u) {
-                    const uint32_t aug = scatter_bits(mb) == N8 - 1 ? (mb | (~mb & (mb + 1u))) : mb;
-                    int r = (int)scatter_bits(aug & ((1u << p) - 1u));
-                    if (N8 == 6 && p >= 4) r -= 2;
-                    r = r < 0 ? 0 : (r > 3 ? 3 : r);
-                    two = (uint32_t)r | ((uint32_t)(4 + r) << 8);
-                }
-                e[mb][p >> 1] |= two << (16 * (p & 1));
-            }
-    }
-};
-static __device__ const ScatterTab<4> scatter_tab4{};
-static __device__ const ScatterTab<6> scatter_tab6{};
-
 // Dynamic LDS of a workgroup: [0, 16) the ticket of the column splits; dense modes: the scatter table (32 KB); then one
 // region of WREG bytes per wavefront.
 constexpr int LDS24_HEAD = 16;
@@ -406,9 +336,8 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
     const uint32_t lds_base_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds_base;
     // the scatter table: 8 entries a load, the loads dealt to all wavefronts
     if constexpr (MODE != 2) {
-        const void* const tab = N8 == 6 ? (const void*)scatter_tab6.e : (const void*)scatter_tab4.e;
         for (int u = wave; u < 32; u += waves)
-            load_to_lds24(lds_base_a - (uint32_t)sizeof(ScatterLds) + 1024u * (uint32_t)u, 128u * (uint32_t)u + 16u * (uint32_t)(lane >> 3), tab);
+            load_to_lds24(lds_base_a - (uint32_t)sizeof(ScatterLds) + 1024u * (uint32_t)u, 128u * (uint32_t)u + 16u * (uint32_t)(lane >> 3), scatter_tab<N8>());
         if (!active) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
     }
     half16_t xr[8];                                              // MODE 2: B operands of the 8 steps of a block
@@ -718,7 +647,7 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
                     const uint4 cur = gl[t % D];
                     if (t + D < 8) gl[t % D] = lut_fetch<N8>(d, t + D, lut, lane & 7);
                     uint32_t o[4];
-                    expand8<N8>(Q, TL, TH, TH | 0x80808080u, t, cur, o);
+                    expand_codes<N8>(Q, TL, TH, TH | 0x80808080u, t, cur, o);
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(o), xd[8 * h + t], acc, 0, 0, 0);
                 }
             }
