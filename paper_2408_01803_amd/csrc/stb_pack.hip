@@ -13,6 +13,7 @@
 
 #include <new>
 #include <type_traits>
+#include <type_traits>
 #include <vector>
 
 #include "stb_f16.h"
@@ -609,10 +610,11 @@ __device__ inline void candidate(int t, double mx, double& q1, double& q2, bool&
 // 11008 x 4096 4:8 of one magnitude 7.6 ms, now 1.0; of two 7.7 and 1.8; 28672 x 8192 of 15 9.3 and 3.2.)  Where several are left
 // k_exact_errors / k_exact_pick evaluate D_t for those alone, in the defined order.
 constexpr int SC_NV = 70;                  // candidates that are not skipped when the block has a non-zero weight: 2 c_t <= 0.9
-constexpr int SC_ROWS = 32;                // rows whose histograms are in LDS at a time
-constexpr int SC_STEPS = 8;                // ... and how often: rows per workgroup = SC_ROWS * SC_STEPS
-constexpr int SC_SEG = 36;                 // bins per lane of the suffix sums (four lanes a row)
-constexpr int SC_BINS = 4 * SC_SEG + 1;    // bin b: the value exceeds b of the 2 SC_NV break points (141 bins; the row stride is odd)
+constexpr int SC_ROWS = 64;                // rows whose histograms are in LDS at a time: a lane a row
+constexpr int SC_WAVES = 8;
+constexpr int SC_STEPS = 8;                // ... and how often at most: rows per workgroup = SC_ROWS * steps
+constexpr int SC_SEG = 18;                 // bins per lane of the suffix sums (SC_WAVES lanes a row)
+constexpr int SC_BINS = SC_WAVES * SC_SEG + 1;    // bin b: the value exceeds b of the 2 SC_NV break points (141 bins; the row stride is odd)
 constexpr int SC_MASKW = 8;                // words of a block's candidate mask (CAND bits)
 
 // The largest fp32 not above p >= 0: for an fp32 value a, a > p iff a > that.
@@ -621,134 +623,157 @@ __device__ inline float round_down_f32(double p) {
     return (double)f > p ? __uint_as_float(__float_as_uint(f) - 1u) : f;
 }
 
+// The break points in ascending order.  In steps of the candidates' grid p1(t) lies at 19.875 + t and p2(t) at 39.75 + 2 t, an
+// eighth of a step apart at least, and rounding keeps an order (it can only make neighbours equal): their ranks among all
+// 2 SC_NV are known.
+__device__ constexpr int rank_p1(int t) { return t + (t < 20 ? 0 : (t - 18) >> 1); }
+__device__ constexpr int rank_p2(int t) { return t + (2 * t + 20 < SC_NV ? 2 * t + 20 : SC_NV); }
+
 // Number of the ascending break points that a exceeds; tau[0] = -1, tau[b + 1] = break point b, tau[2 SC_NV + 1] = inf.
-// The guess comes from the spacing of the break points, in fp32: its error is below 160 * 2^-22 steps, and break points are
-// at least an eighth of a step apart (0.1 / step = 19.875), so it is off by one at most.  TINY: the block's magnitudes are so
+// The guess comes from the spacing of the break points, in fp32: its error is below 160 * 2^-22 steps; `go` is 2^-10 steps too
+// high, so it is the number itself or one more.  TINY: the block's magnitudes are so
 // small that the spacing itself may be lost; then the loops walk as far as it takes and end at the ends of the table.
 template <bool TINY>
 __device__ inline int search_bin(float a, float gs, float go, const float* tau) {
-    const float g1 = fminf(fmaxf(a * gs + go, 0.0f), (float)SC_NV);
-    const float g2 = fminf(fmaxf(0.5f * gs * a + go, 0.0f), (float)SC_NV);
-    int g = (int)(floorf(g1) + floorf(g2));
+    const float g1 = __builtin_amdgcn_fmed3f(__builtin_fmaf(a, gs, go), 0.0f, (float)SC_NV);
+    const float g2 = __builtin_amdgcn_fmed3f(__builtin_fmaf(a, 0.5f * gs, go), 0.0f, (float)SC_NV);
+    int g = (int)g1 + (int)g2;
     if (TINY) {
         while (g > 0 && !(a > tau[g])) g--;
         while (g < 2 * SC_NV && a > tau[g + 1]) g++;
         return g;
     }
-    const float below = tau[g], above = tau[g + 1];
-    return g + (a > above) - (a <= below);     // (0 for a NaN, as tau[0] is below and tau[2 SC_NV + 1] above everything)
+    return g - (a <= tau[g]);              // (tau[0] is below everything)
 }
 
-// A workgroup takes SC_ROWS * SC_STEPS rows of one block.  Per step: 256 threads bin 32 rows x 128 columns (magnitudes as
-// 36-bit fractions of the block's largest, the count in bits 44 up: one 64-bit LDS atomic a value), 128 threads make the
-// suffix sums, 280 threads evaluate 70 candidates x 4 rows at a time and keep their G_t in a register.
+// A workgroup takes SC_ROWS * steps rows of one block.  Per step: all threads bin 64 rows x 128 columns (magnitudes as
+// 36-bit fractions of the block's largest, the count in bits 44 up: one 64-bit LDS atomic a value), then a wavefront takes 18
+// bins of the 64 rows, a lane a row (the row stride is odd: no two lanes share a bank), for the suffix sums, and every eighth
+// candidate, whose G_t over its lane's rows it keeps in a register.  The next step's weights load meanwhile.
 // Error bound, with K = count * mx^2 >= sum a^2 and u = 2^-53: the fractions move G_t by at most 2^-36 K, float64
 // rounding of G_t and of D_t (sequential sums over n rows of sums over 128 values) by less than (4 n + 200) u K.
 // A load instruction covers 8 rows x 128 bytes, so that few lanes of one atomic instruction share a row's bin (with 2 rows
-// x 512 bytes and a histogram for either break point: 1281 us).  Bound by LDS accesses (about 200 cycles a row and block).
-// 28672 x 8192 at 4:8: 0.81 ms (1.14 with loops around every bin search), against 21.7 ms for evaluating every candidate in the defined order.
-__global__ __launch_bounds__(320) void k_search_gain(PK a, double* __restrict__ gain, unsigned long long* __restrict__ above) {
-    __shared__ unsigned long long hist[SC_ROWS * SC_BINS];
+// x 512 bytes and a histogram for either break point: 1281 us).  Bound by LDS accesses and vector instructions.
+// 28672 x 8192 at 4:8: 0.44 ms (0.82 with 32 rows a step, suffix sums by 128 of 320 threads and a lane a candidate, which meet in
+// banks; 1.14 with loops around every bin search), against 21.7 ms for evaluating every candidate in the defined order.
+__global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int steps, double* __restrict__ gain, unsigned long long* __restrict__ above) {
+    __shared__ __attribute__((aligned(16))) unsigned long long hist[SC_ROWS * SC_BINS];
+    __shared__ unsigned long long seg[SC_WAVES][SC_ROWS];
     __shared__ double inv[256];            // 1 / count (a count is at most 128; 8 bits are read)
     __shared__ float tau[2 * SC_NV + 2];
-    double* const part = reinterpret_cast<double*>(hist);      // (after the last step)
-    uint32_t* const part_n = reinterpret_cast<uint32_t*>(part + 4 * SC_NV);
-    const int tid = threadIdx.x, q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
+    constexpr int THREADS = 64 * SC_WAVES, PER = (SC_NV + SC_WAVES - 1) / SC_WAVES;
+    static_assert(SC_ROWS * SC_BINS % 2 == 0, "cleared 16 bytes at a time");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
     const float mxf = __uint_as_float(a.mxbits[q]);
     if (mxf == 0.0f) return;               // nothing kept and non-salient, or all zero: every candidate is the same
     const double mx = (double)mxf;
-    const int t = tid % SC_NV, rg = tid / SC_NV;
-    // rank of the thread's two break points among all of them: the p1(t) ascend, and so do the p2(t)
-    float* const own = reinterpret_cast<float*>(hist);         // [2][SC_NV], before the histograms are cleared
-    {
+    const int r0 = tid >> 3;
+    float4 v[4];
+    uint32_t m[4];
+    auto load = [&](int i) {
+        if (i >= a.n) i = a.n - 1;         // (counted for rows of the matrix only)
+        const uint4 m4 = *reinterpret_cast<const uint4*>(a.mask + (size_t)i * a.mask_stride + 16 * q);
+        const float4* w4 = reinterpret_cast<const float4*>(a.W + (size_t)i * a.k + q * STB_BLOCK);
+#pragma unroll
+        for (int it = 0; it < 4; it++) v[it] = w4[8 * it + (tid & 7)];
+        m[0] = m4.x; m[1] = m4.y; m[2] = m4.z; m[3] = m4.w;
+    };
+    const int first = chunk * steps * SC_ROWS;
+    load(first + r0);
+    if (tid < SC_NV) {
         double p1, p2;
         bool skip;
-        candidate(t, mx, p1, p2, skip);
-        if (tid < SC_NV) { own[t] = round_down_f32(p1); own[SC_NV + t] = round_down_f32(p2); }
+        candidate(tid, mx, p1, p2, skip);
+        tau[rank_p1(tid) + 1] = round_down_f32(p1);
+        tau[rank_p2(tid) + 1] = round_down_f32(p2);
     }
-    __syncthreads();
-    const float f1 = own[t], f2 = own[SC_NV + t];
-    int pos1 = 0, pos2 = 0;                // number of p2 below f1, of p1 not above f2
-    for (int d = 64; d > 0; d >>= 1) {
-        if (pos1 + d <= SC_NV && own[SC_NV + pos1 + d - 1] < f1) pos1 += d;
-        if (pos2 + d <= SC_NV && own[pos2 + d - 1] <= f2) pos2 += d;
-    }
-    pos1 += t;
-    pos2 += t;
-    if (tid < SC_NV) { tau[pos1 + 1] = f1; tau[pos2 + 1] = f2; }
     if (tid == 0) { tau[0] = -1.0f; tau[2 * SC_NV + 1] = __builtin_inff(); }
-    __syncthreads();
     if (tid < 256) inv[tid] = tid > 0 ? 1.0 / (double)tid : 0.0;
-    for (int e = tid; e < SC_ROWS * SC_BINS; e += 320) hist[e] = 0;
-    __syncthreads();
+    uint32_t sal[4];
+#pragma unroll
+    for (int it = 0; it < 4; it++) sal[it] = a.sal[4 * q + it];
     const double scale = 68719476736.0 / mx;                   // 2^36
     const double step = (0.9 - 0.1) / 159.0;
     const bool tiny = !(mxf > 1e-30f);     // (or not a number: the loops end all the same)
-    double g_t = 0.0;
-    uint32_t n_t = 0;                      // values above p1(t) and above p2(t)
-    const float gs = (float)(1.0 / (step * mx)), go = (float)(1.0 - 0.1 / step);
-    for (int st = 0; st < SC_STEPS; st++) {
-        const int i0 = (chunk * SC_STEPS + st) * SC_ROWS;
-        if (i0 >= a.n) break;                                  // uniform
-        const int r0 = tid >> 3, i = i0 + r0;
-        if (tid < 256 && i < a.n) {
-            const uint4 m4 = *reinterpret_cast<const uint4*>(a.mask + (size_t)i * a.mask_stride + 16 * q);
-            const uint32_t m[4] = {m4.x, m4.y, m4.z, m4.w};
-            const float4* w4 = reinterpret_cast<const float4*>(a.W + (size_t)i * a.k + q * STB_BLOCK);
-            float4 v[4];
+    const float gs = (float)(1.0 / (step * mx)), go = (float)(1.0 + 0.0009765625 - 0.1 / step);
+    double g_t[PER];
+    uint32_t n_t[PER];                     // values above p1(t) and above p2(t)
 #pragma unroll
-            for (int it = 0; it < 4; it++) v[it] = w4[8 * it + (tid & 7)];
+    for (int j = 0; j < PER; j++) { g_t[j] = 0.0; n_t[j] = 0; }
+    unsigned long long* const row = hist + lane * SC_BINS;
+    for (int st = 0; st < steps; st++) {
+        const int i0 = first + st * SC_ROWS;
+        if (i0 >= a.n) break;                                  // uniform
+        for (int e = tid; e < SC_ROWS * SC_BINS / 2; e += THREADS) reinterpret_cast<uint4*>(hist)[e] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+        const bool live = i0 + r0 < a.n;
+        auto count = [&](auto any_size) {
 #pragma unroll
             for (int it = 0; it < 4; it++) {
-                const uint32_t keep = (m[it] & ~a.sal[4 * q + it]) >> (4 * (tid & 7));
+                const uint32_t keep = live ? (m[it] & ~sal[it]) >> (4 * (tid & 7)) : 0u;
                 const float e[4] = {fabsf(v[it].x), fabsf(v[it].y), fabsf(v[it].z), fabsf(v[it].w)};
+                int b[4];
+                unsigned long long fx[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    const int b = tiny ? search_bin<true>(e[u], gs, go, tau) : search_bin<false>(e[u], gs, go, tau);
+                    b[u] = search_bin<decltype(any_size)::value>(e[u], gs, go, tau);
                     // 2^52 + the fraction, rounded to a whole number: its low words are that number below 2^52's exponent
-                    const unsigned long long fx = (unsigned long long)__double_as_longlong(__builtin_fma((double)e[u], scale, 4503599627370496.0));
-                    if ((keep >> u) & 1u) atomicAdd(&hist[r0 * SC_BINS + b], fx - (0x4330000000000000ull - (1ull << 44)));
+                    fx[u] = (unsigned long long)__double_as_longlong(__builtin_fma((double)e[u], scale, 4503599627370496.0)) - (0x4330000000000000ull - (1ull << 44));
                 }
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if ((keep >> u) & 1u) atomicAdd(&hist[r0 * SC_BINS + b[u]], fx[u]);
             }
+        };
+        if (tiny) count(std::true_type{});
+        else count(std::false_type{});
+        if (st + 1 < steps) load(i0 + SC_ROWS + r0);
+        __syncthreads();
+        {
+            unsigned long long h[SC_SEG], run = 0;
+#pragma unroll
+            for (int b = 0; b < SC_SEG; b++) { h[b] = row[wave * SC_SEG + b]; run += h[b]; }
+            seg[wave][lane] = run;
+            __syncthreads();
+            run = 0;
+#pragma unroll
+            for (int w = 1; w < SC_WAVES; w++)
+                if (w > wave) run += seg[w][lane];
+#pragma unroll
+            for (int b = SC_SEG - 1; b >= 0; b--) { run += h[b]; row[wave * SC_SEG + b] = run; }
         }
         __syncthreads();
-        if (tid < 4 * SC_ROWS) {
-            unsigned long long* h = hist + (tid >> 2) * SC_BINS + (tid & 3) * SC_SEG;
-            unsigned long long v[SC_SEG], sum = 0, run = 0;
+        auto sum_of = [](unsigned long long s) {               // the low 44 bits as a double
+            return __longlong_as_double((long long)((s & 0xFFFFFFFFFFFull) | 0x4330000000000000ull)) - 4503599627370496.0;
+        };
+        auto inv_of = [&](unsigned long long s) { return inv[(s >> 44) & 255]; };
+        const unsigned long long all = row[0];
 #pragma unroll
-            for (int b = 0; b < SC_SEG; b++) { v[b] = h[b]; sum += v[b]; }
-#pragma unroll
-            for (int d = 1; d < 4; d++) {
-                const unsigned long long o = __shfl_down(sum, d, 4);
-                run += (tid & 3) + d < 4 ? o : 0ull;
-            }
-#pragma unroll
-            for (int b = SC_SEG - 1; b >= 0; b--) { run += v[b]; h[b] = run; }
-        }
-        __syncthreads();
-        if (tid < 4 * SC_NV) {
-            auto sum_of = [](unsigned long long v) {           // the low 44 bits as a double
-                return __longlong_as_double((long long)((v & 0xFFFFFFFFFFFull) | 0x4330000000000000ull)) - 4503599627370496.0;
-            };
-#pragma unroll 4
-            for (int r = rg; r < SC_ROWS; r += 4) {
-                const unsigned long long* h = hist + r * SC_BINS;
-                const unsigned long long all = h[0], above1 = h[pos1 + 1], above2 = h[pos2 + 1];
+        for (int j = 0; j < PER; j++) {
+            const int t = wave + SC_WAVES * j;
+            if (t < SC_NV) {                                   // uniform
+                const unsigned long long above1 = row[rank_p1(t) + 1], above2 = row[rank_p2(t) + 1];
                 const unsigned long long mid = above1 - above2, low = all - above1;
-                n_t += (uint32_t)(above1 >> 44) + (uint32_t)(above2 >> 44);
+                n_t[j] += (uint32_t)(above1 >> 44) + (uint32_t)(above2 >> 44);
                 const double s0 = sum_of(low), s1 = sum_of(mid), s2 = sum_of(above2);
-                g_t += s0 * s0 * inv[(low >> 44) & 255] + s1 * s1 * inv[(mid >> 44) & 255] + s2 * s2 * inv[(above2 >> 44) & 255];
+                g_t[j] += s0 * s0 * inv_of(low) + s1 * s1 * inv_of(mid) + s2 * s2 * inv_of(above2);
             }
         }
-        __syncthreads();
-        for (int e = tid; e < SC_ROWS * SC_BINS; e += 320) hist[e] = 0;
         __syncthreads();
     }
-    if (tid < 4 * SC_NV) { part[tid] = g_t; part_n[tid] = n_t; }
-    __syncthreads();
-    if (tid < SC_NV) {                                         // in units of (mx / 2^36)^2
-        unsafeAtomicAdd(gain + (size_t)q * SC_NV + tid, part[tid] + part[SC_NV + tid] + part[2 * SC_NV + tid] + part[3 * SC_NV + tid]);
-        atomicAdd(above + (size_t)q * SC_NV + tid, (unsigned long long)part_n[tid] + part_n[SC_NV + tid] + part_n[2 * SC_NV + tid] + part_n[3 * SC_NV + tid]);
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const int t = wave + SC_WAVES * j;
+        if (t >= SC_NV) break;                                 // uniform
+        double g = g_t[j];
+        uint32_t cnt = n_t[j];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) { g += __shfl_xor(g, d); cnt += __shfl_xor(cnt, d); }
+        if (lane == 0) {                                       // in units of (mx / 2^36)^2
+            unsafeAtomicAdd(gain + (size_t)q * SC_NV + t, g);
+            atomicAdd(above + (size_t)q * SC_NV + t, (unsigned long long)cnt);
+        }
     }
 }
 
@@ -1272,8 +1297,10 @@ static int search_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream
     uint32_t* const left = a.hist;                             // (nb * 512 words; the tertile split alone uses them otherwise)
     unsigned long long* const above = (unsigned long long*)(err + (size_t)a.nb * SC_NV);       // behind the gains
     ok(hipMemsetAsync(err, 0, (size_t)a.nb * SC_NV * 16, st));
-    const int rows = SC_ROWS * SC_STEPS;
-    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(320), 0, st, a, err, above);
+    // two workgroups a compute unit: four rounds of them at least before a workgroup takes more rows for its set-up
+    const int64_t tiles = (int64_t)((a.n + SC_ROWS - 1) / SC_ROWS) * a.nb;
+    const int steps = tiles >= 2048 * SC_STEPS ? SC_STEPS : tiles < 2048 ? 1 : (int)(tiles / 2048), rows = SC_ROWS * steps;
+    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(64 * SC_WAVES), 0, st, a, steps, err, above);
     hipLaunchKernelGGL(k_search_narrow, dim3((a.nb + 63) / 64), dim3(64), 0, st, a, err, above, left);
     ok(hipGetLastError());
     std::vector<uint32_t> mask((size_t)a.nb * SC_MASKW);
