@@ -777,35 +777,45 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     }
 }
 
-// One thread per block: the candidates whose G_t is within the error bounds (taken four times over) of the largest, the first of
+// A wavefront per block, two candidates a lane: those whose G_t is within the error bounds (taken four times over) of the largest, the first of
 // those that part the values alike.  One left: it is the answer.  Several: their bits go to the block's mask for the exact
 // evaluation.
-__global__ void k_search_narrow(PK a, const double* __restrict__ gain, const unsigned long long* __restrict__ above, uint32_t* __restrict__ left) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.nb) return;
+__global__ __launch_bounds__(64) void k_search_narrow(PK a, const double* __restrict__ gain, const unsigned long long* __restrict__ above, uint32_t* __restrict__ left) {
+    const int q = blockIdx.x, lane = threadIdx.x;
     uint32_t* mask = left + (size_t)q * SC_MASKW;
-    for (int u = 0; u < SC_MASKW; u++) mask[u] = 0;
     const double mx = (double)__uint_as_float(a.mxbits[q]);
-    a.p12[2 * q] = a.p12[2 * q + 1] = 0.0;                     // candidate 0 of a block without a non-zero weight
+    if (mx == 0.0 && lane < SC_MASKW) mask[lane] = 0;
+    if (lane == 0) a.p12[2 * q] = a.p12[2 * q + 1] = 0.0;      // candidate 0 of a block without a non-zero weight
     if (mx == 0.0) return;
-    const double* g = gain + (size_t)q * SC_NV;
-    double best = 0.0;
-    for (int t = 0; t < SC_NV; t++) best = g[t] > best ? g[t] : best;
+    const bool two = lane + 64 < SC_NV;
+    const double g0 = gain[(size_t)q * SC_NV + lane], g1 = two ? gain[(size_t)q * SC_NV + 64 + lane] : 0.0;
+    double best = g0 > g1 ? g0 : g1;
+    best = best > 0.0 ? best : 0.0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const double o = __shfl_xor(best, d);
+        best = o > best ? o : best;
+    }
     const double K = (double)a.cnt[q] * 4722366482869645213696.0;                                  // 2^72
     const double slack = 4.0 * (1.0 / 68719476736.0 + (4.0 * (double)a.n + 200.0) / 9007199254740992.0) * K;
+    unsigned long long close0 = __ballot(g0 >= best - slack), close1 = __ballot(two && g1 >= best - slack);
     int many = 0, first = 0;
     unsigned long long kept = 0;
-    for (int t = 0; t < SC_NV; t++) {
+    uint32_t bits[3] = {0u, 0u, 0u};
+    while (close0 | close1) {                                  // (almost always once)
+        const int t = close0 ? __ffsll(close0) - 1 : 63 + __ffsll(close1);
+        if (close0) close0 &= close0 - 1; else close1 &= close1 - 1;
         const unsigned long long n = above[(size_t)q * SC_NV + t];
-        if (!(g[t] >= best - slack) || (many > 0 && n == kept)) continue;
+        if (many > 0 && n == kept) continue;
         if (many++ == 0) first = t;
         kept = n;
-        mask[t >> 5] |= 1u << (t & 31);
+#pragma unroll
+        for (int u = 0; u < 3; u++) bits[u] |= t >> 5 == u ? 1u << (t & 31) : 0u;
     }
-    if (many == 1) {
+    if (lane < SC_MASKW) mask[lane] = many == 1 ? 0u : lane == 0 ? bits[0] : lane == 1 ? bits[1] : lane == 2 ? bits[2] : 0u;
+    if (lane == 0 && many == 1) {
         bool skip;
         candidate(first, mx, a.p12[2 * q], a.p12[2 * q + 1], skip);
-        for (int u = 0; u < SC_MASKW; u++) mask[u] = 0;
     }
 }
 
@@ -970,16 +980,18 @@ __global__ __launch_bounds__(64) void k_select_step(PK a, int pass) {
 // A lane walks its (row, block) from left to right (the sums are sequential); a wavefront is 8 rows x 8 blocks, so that what
 // it reads and writes of a row is contiguous (64 to 512 bytes).  The weights come through LDS 32 columns at a time, sign and
 // id bits leave through it.  Only the kept columns are walked (all 128 with
-// predicates: 0.81 ms).  28672 x 8192 at 4:8: 0.33 ms, against 0.65 + 0.99 ms with one thread per (row, block) that reads and
+// predicates: 0.81 ms), without a branch for a value's region (0.32 ms with them and the chunks unrolled: a wait for LDS a value, two
+// wavefronts a SIMD).  Bound by vector instructions (about 30 a kept weight) beside a pass over the weights (0.18).  28672 x 8192 at 4:8:
+// 0.27 ms, against 0.65 + 0.99 ms with one thread per (row, block) that reads and
 // writes its own 512 and 24 bytes, once here and once for the salient columns.
 // LDS keeps a wavefront's accesses in order; the compiler has to as well where lanes read what others wrote.
 __device__ inline void wave_order() {
     asm volatile("" : : : "memory");
     __builtin_amdgcn_wave_barrier();
 }
-constexpr int AS_COLS = 32, AS_STRIDE = AS_COLS + 1;
+constexpr int AS_COLS = 32, AS_STRIDE = AS_COLS + 1, AS_SAL = 8;
 template <int N8>                                              // kept weights of 8 columns
-__global__ __launch_bounds__(256) void k_assign(PK a) {
+__global__ __launch_bounds__(256, 3) void k_assign(PK a) {
     __shared__ float tile[4][64 * AS_STRIDE];
     __shared__ __attribute__((aligned(16))) uint8_t bits[4][8 * 8 * 48];          // per wavefront: 8 rows x 8 blocks x (16 + 32) bytes
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -997,7 +1009,7 @@ __global__ __launch_bounds__(256) void k_assign(PK a) {
     const uint4 s4 = make_uint4(a.sal[4 * qc], a.sal[4 * qc + 1], a.sal[4 * qc + 2], a.sal[4 * qc + 3]);
     const float p1 = round_down_f32(a.p12[2 * qc]), p2 = round_down_f32(a.p12[2 * qc + 1]);
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, so = 0.0;
-    int c0 = 0, c1 = 0, c2 = 0, co = 0;
+    int c1 = 0, c2 = 0;
     uint64_t sacc = 0;
     bool odd = false;
     // the wavefront's loads: row i0 + u, 8 lanes a block
@@ -1011,6 +1023,7 @@ __global__ __launch_bounds__(256) void k_assign(PK a) {
         }
     };
     load(0);
+#pragma unroll 1
     for (int ch = 0; ch < STB_BLOCK / AS_COLS; ch++) {
 #pragma unroll
         for (int u = 0; u < 8; u++) {
@@ -1022,67 +1035,98 @@ __global__ __launch_bounds__(256) void k_assign(PK a) {
         const uint32_t m = ch == 0 ? m4.x : ch == 1 ? m4.y : ch == 2 ? m4.z : m4.w;
         const uint32_t sb = ch == 0 ? s4.x : ch == 1 ? s4.y : ch == 2 ? s4.z : s4.w;
         uint64_t racc = 0;
+        uint32_t gsacc = 0;
 #pragma unroll
         for (int g = 0; g < AS_COLS / 8; g++) {
-            uint32_t left = (m >> (8 * g)) & 0xFFu, gs = 0, gid = 0;
+            uint32_t left = (m >> (8 * g)) & 0xFFu, gid = 0;
             odd |= __popc(left) != n8;
+            int c[n8];
+            float w[n8];
 #pragma unroll
             for (int r = 0; r < n8; r++) {                     // the group's kept columns, in slot order
-                const int c = 8 * g + (__ffs(left | 0x80u) - 1);
+                c[r] = 8 * g + (__ffs(left | 0x80u) - 1);
                 left &= left - 1;
-                const float wf = x[lane * AS_STRIDE + c], av = fabsf(wf);
-                const uint32_t id = (sb >> c) & 1u ? 3u : av > p2 ? 2u : av > p1 ? 1u : 0u;
-                so += (double)(id == 3u ? av : 0.0f);
-                s2 += (double)(id == 2u ? av : 0.0f);
-                s1 += (double)(id == 1u ? av : 0.0f);
-                s0 += (double)(id == 0u ? av : 0.0f);
-                c2 += id == 2u;
-                c1 += id == 1u;
-                co += id == 3u;
-                gs |= wf >= 0.0f ? 1u << r : 0u;
+                w[r] = x[lane * AS_STRIDE + c[r]];
+            }
+#pragma unroll
+            for (int r = 0; r < n8; r++) {
+                // a sum takes 1 * |w| or 0 * |w| (exact products: the addition rounds as it would alone), without a branch.
+                // one = the high word of 1.0; p1 <= p2
+                constexpr uint32_t one = 0x3FF00000u;
+                const float av = fabsf(w[r]);
+                const bool is3 = ((sb >> c[r]) & 1u) != 0, over1 = av > p1, over2 = av > p2;
+                const double d = (double)(is3 ? 0.0f : av);
+                so += (double)(is3 ? av : 0.0f);
+                const uint32_t h1 = over1 ? one : 0u, h2 = over2 ? one : 0u;
+                s2 = __builtin_fma(__hiloint2double((int)h2, 0), d, s2);
+                s1 = __builtin_fma(__hiloint2double((int)(h1 ^ h2), 0), d, s1);
+                s0 = __builtin_fma(__hiloint2double((int)(h1 ^ one), 0), d, s0);
+                const uint32_t id = is3 ? 3u : (uint32_t)over1 + (uint32_t)over2;
+                gsacc |= w[r] >= 0.0f ? 1u << (g * n8 + r) : 0u;
                 gid |= id << (2 * r);
             }
-            sacc |= (uint64_t)gs << ((4 * (ch & 1) + g) * n8);
             racc |= (uint64_t)gid << (2 * g * n8);
         }
+        const uint64_t lo = racc & 0x5555555555555555ull, hi = (racc >> 1) & 0x5555555555555555ull;
+        c2 += __popcll(hi & ~lo);
+        c1 += __popcll(lo & ~hi);
+        sacc |= (uint64_t)gsacc << ((ch & 1) * 4 * n8);
+        typedef std::conditional_t<n8 % 4 == 0, uint32_t, std::conditional_t<n8 % 2 == 0, uint16_t, uint8_t>> unit;
+        constexpr int us = sizeof(unit);
 #pragma unroll
-        for (int u = 0; u < n8; u++) rout[ch * n8 + u] = (uint8_t)(racc >> (8 * u));        // 8 n8 id bits
+        for (int u = 0; u < n8; u += us) *reinterpret_cast<unit*>(rout + ch * n8 + u) = (unit)(racc >> (8 * u));        // 8 n8 id bits
         if (ch & 1) {                                                                      // 8 n8 sign bits
 #pragma unroll
-            for (int u = 0; u < n8; u++) sout[(ch >> 1) * n8 + u] = (uint8_t)(sacc >> (8 * u));
+            for (int u = 0; u < n8; u += us) *reinterpret_cast<unit*>(sout + (ch >> 1) * n8 + u) = (unit)(sacc >> (8 * u));
             sacc = 0;
         }
         wave_order();
     }
-    c0 = STB_BLOCK / 8 * n8 - c1 - c2 - co;
+    const uint64_t sal[2] = {s4.x | (uint64_t)s4.y << 32, s4.z | (uint64_t)s4.w << 32}, kept[2] = {m4.x | (uint64_t)m4.y << 32, m4.z | (uint64_t)m4.w << 32};
+    const int co = __popcll(sal[0] & kept[0]) + __popcll(sal[1] & kept[1]), c0 = STB_BLOCK / 8 * n8 - c1 - c2 - co;
     if (live && odd) atomicOr(a.status, ST_GROUP);                 // a group that does not keep N: scores that do not order (NaN)
-    // residual binarisation of the kept salient weights (Eq. 4)
+    // residual binarisation of the kept salient weights (Eq. 4), from left to right; AS_SAL of them are loaded together and put
+    // into LDS (one after the other each waits for memory)
     const uint16_t ao16 = stb_f64_to_f16_bits(co > 0 ? so / (double)co : 0.0);
     double sr = 0.0;
     if (live && co > 0) {
         const double ao = (double)stb_f16_bits_to_f32(ao16);
         const float* w = a.W + (size_t)i * a.k + q * STB_BLOCK;
         uint32_t* trow = a.res_sign + (size_t)i * (a.res_stride / 4);
-        uint32_t u = a.prefix[q], word = 0;                            // index of the block's first salient column among all of them
-        const uint32_t mw[4] = {m4.x, m4.y, m4.z, m4.w}, sw[4] = {s4.x, s4.y, s4.z, s4.w};
+        const uint32_t u0 = a.prefix[q];                           // index of the block's first salient column among all of them
+        uint32_t word = 0, at = u0 >> 5;
+        uint64_t l0 = sal[0] & kept[0], l1 = sal[1] & kept[1];     // still to be looked at
+        for (int left = co; left > 0; left -= AS_SAL) {
+            uint64_t f0 = l0, f1 = l1;
+            float wv[AS_SAL];
 #pragma unroll
-        for (int ch = 0; ch < 4; ch++) {
-            for (uint32_t left = sw[ch]; left; left &= left - 1) {
-                const int c = __ffs(left) - 1;
-                if ((mw[ch] >> c) & 1u) {
-                    const float wf = w[32 * ch + c];
-                    const double res = (double)wf - ao * (wf >= 0.0f ? 1.0 : -1.0);
-                    sr += fabs(res);
-                    word |= res >= 0.0 ? 1u << (u & 31) : 0u;
-                }
-                u++;
-                if ((u & 31) == 0) {                                   // neighbouring blocks share words
-                    if (word) atomicOr(trow + (u >> 5) - 1, word);
+            for (int e = 0; e < AS_SAL; e++) {                     // (past the last: a column that is not looked at)
+                wv[e] = w[f0 ? __ffsll((unsigned long long)f0) - 1 : f1 ? 63 + __ffsll((unsigned long long)f1) : 0];
+                f1 = f0 ? f1 : f1 & (f1 - 1);
+                f0 &= f0 - 1;
+            }
+#pragma unroll
+            for (int e = 0; e < AS_SAL; e++) x[lane * AS_STRIDE + e] = wv[e];
+            const int count = left < AS_SAL ? left : AS_SAL;
+            for (int e = 0; e < count; e++) {
+                const float wf = x[lane * AS_STRIDE + e];
+                const double res = (double)wf - ao * (wf >= 0.0f ? 1.0 : -1.0);
+                sr += fabs(res);
+                // rank of the column among the block's salient ones, kept or not
+                const bool second = l0 == 0;
+                const uint64_t l = second ? l1 : l0, below = (l & (0ull - l)) - 1;
+                const uint32_t u = u0 + (second ? __popcll(sal[0]) + __popcll(sal[1] & below) : __popcll(sal[0] & below));
+                l1 = second ? l1 & (l1 - 1) : l1;
+                l0 &= l0 - 1;
+                if ((u >> 5) != at) {                              // neighbouring blocks share words
+                    if (word) atomicOr(trow + at, word);
                     word = 0;
+                    at = u >> 5;
                 }
+                word |= res >= 0.0 ? 1u << (u & 31) : 0u;
             }
         }
-        if (word) atomicOr(trow + (u >> 5), word);
+        if (word) atomicOr(trow + at, word);
     }
     if (live) {
         const uint32_t h0 = stb_f64_to_f16_bits(c0 > 0 ? s0 / (double)c0 : 0.0), h1 = stb_f64_to_f16_bits(c1 > 0 ? s1 / (double)c1 : 0.0);
@@ -1301,7 +1345,7 @@ static int search_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream
     const int64_t tiles = (int64_t)((a.n + SC_ROWS - 1) / SC_ROWS) * a.nb;
     const int steps = tiles >= 2048 * SC_STEPS ? SC_STEPS : tiles < 2048 ? 1 : (int)(tiles / 2048), rows = SC_ROWS * steps;
     hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(64 * SC_WAVES), 0, st, a, steps, err, above);
-    hipLaunchKernelGGL(k_search_narrow, dim3((a.nb + 63) / 64), dim3(64), 0, st, a, err, above, left);
+    hipLaunchKernelGGL(k_search_narrow, dim3(a.nb), dim3(64), 0, st, a, err, above, left);
     ok(hipGetLastError());
     std::vector<uint32_t> mask((size_t)a.nb * SC_MASKW);
     ok(hipMemcpyAsync(mask.data(), left, mask.size() * 4, hipMemcpyDeviceToHost, st));

@@ -214,6 +214,30 @@ def test_device_packer_mask_where_scores_are_close(n, k, N, M, values, torch_cud
         assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n,k,N,M", [(1, 128, 4, 8), (63, 1152, 8, 8), (64, 256, 3, 8), (65, 1024, 6, 8), (4099, 128, 4, 8), (577, 2944, 4, 4)])
+def test_device_packer_values_on_break_points_and_crowded_blocks(n, k, N, M, mode, torch_cuda):
+    """Magnitudes that are the search's own break points, or the fp32 numbers next to them (p1 and p2 lie between the bins), and
+    blocks with 0, 7, 8, 9, 41 and 128 salient columns, at the edges of the 64-row histograms and 32-row tiles: the oracle's bytes."""
+    rng = np.random.default_rng(n + k)
+    c = 0.1 + np.arange(160) * ((0.9 - 0.1) / 159.0)
+    points = np.concatenate([c, 2 * c]).astype(np.float32)
+    points = np.concatenate([points, np.nextafter(points, np.float32(0)), np.nextafter(points, np.float32(9))])
+    points = np.append(points[points <= 1.0], np.float32(1.0))
+    W = rng.choice(points, (n, k)) * rng.choice(np.array([-1, 1], dtype=np.float32), (n, k))
+    W[:, 0] = 1.0
+    W[rng.random((n, k)) < 0.03] = -0.0
+    chosen = np.zeros(k, dtype=bool)
+    for q, count in zip(range(k // 128), (9, 0, 8, 128, 41, 7, 1, 9)):
+        chosen[q * 128 + rng.permutation(127)[:count] + 1 if count < 128 else slice(q * 128, q * 128 + 128)] = True
+    bitmap = np.packbits(chosen, bitorder="little").view("<u4")
+    xnorm = np.abs(1 + 0.3 * rng.standard_normal(k)).astype(np.float32)
+    _say(f"[case] break points {n}x{k} {N}:{M} mode {mode}")
+    pm = _pack_on_device(torch_cuda, W, xnorm, bitmap, N, M, mode)
+    for name, v in O.pack(W, xnorm, bitmap, N, M, mode).items():
+        assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+
+
 @pytest.mark.parametrize("levels", [1, 2, 15])
 def test_device_packer_takes_no_longer_where_candidates_tie(levels, torch_cuda):
     """A layer of few distinct magnitudes, on which most candidates of the break-point search part the weights alike: the host's
