@@ -60,10 +60,6 @@ int stb_tiled_gemm(const stb_layout_t* L, const void* X, int T, void* Y, int y_f
 int64_t stb_tiled_gemm_workspace(const stb_layout_t* L, int T);
 // What that call runs in workspace_bytes bytes (an aligned workspace).
 void stb_tiled_gemm_form(const stb_layout_t* L, int T, int y_fp32, int64_t workspace_bytes, stb_gemm_form_t* out);
-// Host: the derived tables of the tiled order (padded bitmap and prefix, table of salient columns, maxima) from the
-// row-major bitmap and prefix; the output arrays hold tl->salmap_bytes, tl->salprefix_bytes, tl->saltab_bytes.
-int stb_host_tiled_tables(const stb_layout_t* tl, const uint32_t* bitmap, const uint32_t* prefix, uint32_t* bitmap_out,
-                          uint32_t* prefix_out, uint32_t* sal_tab_out, int* max_block, int* max_half);
 // stb_tile with both images in device memory (stb_pack.hip); sets dst->max_sal_block / max_sal_half; waits for the stream.
 int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* stream, int* hip_err);
 // The packer on the GPU (stb_pack.hip): `out` is a checked row-major layout bound to device memory, the workspace holds

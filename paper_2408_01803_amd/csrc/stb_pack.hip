@@ -11,8 +11,8 @@
 // root of float64 are correctly rounded on this hardware, as on the host.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <new>
-#include <type_traits>
 #include <type_traits>
 #include <vector>
 
@@ -25,7 +25,8 @@ namespace {
 
 constexpr int CAND = 160;                  // break-point candidates of Alg. 2
 constexpr int MK_ROWS = 256;               // rows of one block that a workgroup of the mask kernels takes
-constexpr uint32_t ST_NONFINITE = 1u, ST_SALIENT = 2u, ST_GROUP = 4u, ST_UNDECIDED = 8u;
+constexpr uint32_t ST_NONFINITE = 1u, ST_SALIENT = 2u, ST_GROUP = 4u, ST_UNDECIDED = 8u,
+                   ST_CLOSE = 16u;         // a block's break points need the exact evaluation
 
 struct PK {
     const float* W;
@@ -41,17 +42,23 @@ struct PK {
     uint32_t* sal_out;
     uint32_t* prefix;
     int64_t mask_stride, sign_stride, region_stride, res_stride;
-    uint32_t* status;       // [0] error bits
+    uint32_t* status;       // [0] error bits, [1] [2] of k_layer_mean
     double* rs;             // [n][nbS] row sums of |W| (whole row, or per block)
     double2* cols;          // [k] column sums of |W| and their reciprocals
     double* rowacc;         // [n][nbS]
-    double* stats;          // [nbS][2] mean, deviation (k_layer_mean: mean, 1 if the scores may be compared in fp32)
+    double* stats;          // [nbS][2] mean, deviation (of the sums in the defined order)
     uint32_t* mxbits;       // [nb] largest kept non-salient magnitude of the block (fp32 bits)
     uint32_t* cnt;          // [nb] number of kept non-salient weights of the block
     double* p12;            // [nb][2] break points
     uint32_t* hist;         // [nb][2][256]
     uint32_t* sel;          // [nb][2][2] prefix, remaining rank of the two order statistics
 };
+
+// Whether an earlier kernel found what the host has to look at first: a wrong bitmap, numbers that are none, a mask or break points
+// that the bounds leave open.
+__device__ inline bool given_up(const PK& a) {
+    return (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & (ST_SALIENT | ST_NONFINITE | ST_UNDECIDED | ST_CLOSE)) != 0;
+}
 
 __device__ inline bool sal_bit(const uint32_t* bm, int j) { return (bm[j >> 5] >> (j & 31)) & 1u; }
 
@@ -127,29 +134,29 @@ __global__ __launch_bounds__(256, 3) void k_layer_sums(PK a, int rows) {
     if (top >= 0x7F800000u) atomicOr(a.status, ST_NONFINITE);              // an infinity or a NaN
 }
 
-// One workgroup: the mean of mu from the numbers of non-zero rows and columns, the check of xnorm, and whether all sums and
-// norms are of a size that fp32 scores cannot leave the fp32 range with.
-__global__ __launch_bounds__(1024) void k_layer_mean(PK a) {
-    __shared__ uint32_t total, wide;
-    if (threadIdx.x == 0) { total = 0; wide = 0; }
-    __syncthreads();
-    uint32_t nonzero = 0, far = 0, bad = 0;
+// The numbers of non-zero rows and columns, from which the mean of mu follows (status[1]), the check of xnorm, and whether any sum or
+// norm is of a size that fp32 scores could leave the fp32 range with (status[2]).  A thread a row or column (one workgroup: 21 us).
+__global__ __launch_bounds__(256) void k_layer_mean(PK a) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     auto odd = [](double v) { return v != 0.0 && !(v >= 0x1p-40 && v <= 0x1p40); };
-    for (int i = threadIdx.x; i < a.n; i += 1024) { const double v = a.rs[i]; nonzero += v != 0.0; far |= odd(v); }
-    for (int j = threadIdx.x; j < a.k; j += 1024) {
-        const double v = a.cols[j].x;
-        const float x = a.xnorm[j];
-        nonzero += v != 0.0;
-        far |= odd(v) || odd((double)x);
-        bad |= !(x >= 0.0f) || !__builtin_isfinite(x);
+    bool nonzero = false, far = false, bad = false;
+    if (i < a.n) {
+        const double v = a.rs[i];
+        nonzero = v != 0.0;
+        far = odd(v);
+    } else if (i < (int64_t)a.n + a.k) {
+        const double v = a.cols[i - a.n].x;
+        const float x = a.xnorm[i - a.n];
+        nonzero = v != 0.0;
+        far = odd(v) || odd((double)x);
+        bad = !(x >= 0.0f) || !__builtin_isfinite(x);
     }
-    if (nonzero) atomicAdd(&total, nonzero);
-    if (far) atomicOr(&wide, 1u);
-    if (bad) atomicOr(a.status, ST_NONFINITE);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    a.stats[0] = (double)total / ((double)a.n * (double)a.k);
-    a.stats[1] = wide ? 0.0 : 1.0;
+    const uint32_t count = (uint32_t)__popcll(__ballot(nonzero));
+    const bool any_far = __any(far), any_bad = __any(bad);
+    if ((threadIdx.x & 63) != 0) return;
+    if (count) atomicAdd(a.status + 1, count);
+    if (any_far) atomicOr(a.status + 2, 1u);
+    if (any_bad) atomicOr(a.status, ST_NONFINITE);
 }
 
 // Which N of every M scores are kept (bit p of the result), the left one of equals first.
@@ -223,12 +230,12 @@ __device__ inline void around_cut(const float (&s)[8], int h, float& low, float&
 // in float64.  Also the largest kept non-salient magnitude and their number per block.
 template <int M, int N>
 __global__ __launch_bounds__(256) void k_layer_mask(PK a) {
-    if (__hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ST_UNDECIDED) return;     // (the layer goes the other way)
+    if (given_up(a)) return;               // (the layer goes the other way)
     const int q = (int)(blockIdx.x % (unsigned)a.nb), g = threadIdx.x & 15, r = threadIdx.x >> 4;
     const int ibeg = (int)(blockIdx.x / (unsigned)a.nb) * MK_ROWS + r, j0 = q * STB_BLOCK + 8 * g;
     const int iend = (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS < a.n ? (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS : a.n;
-    const double mean = a.stats[0];
-    const bool narrow = a.stats[1] != 0.0;
+    const double mean = (double)a.status[1] / ((double)a.n * (double)a.k);
+    const bool narrow = a.status[2] == 0;
     float x[8], cx[8], mx8[8], mxtop = 0.0f;       // xnorm, xnorm / column sum, mean * xnorm
     uint32_t normal[8];                            // all ones where the column is not salient
 #pragma unroll
@@ -663,6 +670,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     __shared__ float tau[2 * SC_NV + 2];
     constexpr int THREADS = 64 * SC_WAVES, PER = (SC_NV + SC_WAVES - 1) / SC_WAVES;
     static_assert(SC_ROWS * SC_BINS % 2 == 0, "cleared 16 bytes at a time");
+    if (given_up(a)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
     const float mxf = __uint_as_float(a.mxbits[q]);
@@ -813,6 +821,7 @@ __global__ __launch_bounds__(64) void k_search_narrow(PK a, const double* __rest
         for (int u = 0; u < 3; u++) bits[u] |= t >> 5 == u ? 1u << (t & 31) : 0u;
     }
     if (lane < SC_MASKW) mask[lane] = many == 1 ? 0u : lane == 0 ? bits[0] : lane == 1 ? bits[1] : lane == 2 ? bits[2] : 0u;
+    if (lane == 0 && many > 1) atomicOr(a.status, ST_CLOSE);
     if (lane == 0 && many == 1) {
         bool skip;
         candidate(first, mx, a.p12[2 * q], a.p12[2 * q + 1], skip);
@@ -913,6 +922,7 @@ __global__ void k_select_init(PK a) {
 constexpr int SH_COPIES = 16, SH_STRIDE = 2 * 256 + 1;
 __global__ __launch_bounds__(256) void k_select_hist(PK a, int pass) {
     __shared__ uint32_t h[SH_COPIES * SH_STRIDE];
+    if (given_up(a)) return;
     const int q = (int)(blockIdx.x % (unsigned)a.nb), i0 = (int)(blockIdx.x / (unsigned)a.nb) * MK_ROWS, g = threadIdx.x & 15;
     const int iend = a.n - i0 < MK_ROWS ? a.n : i0 + MK_ROWS;
     for (int e = threadIdx.x; e < SH_COPIES * SH_STRIDE; e += 256) h[e] = 0;
@@ -994,6 +1004,7 @@ template <int N8>                                              // kept weights o
 __global__ __launch_bounds__(256, 3) void k_assign(PK a) {
     __shared__ float tile[4][64 * AS_STRIDE];
     __shared__ __attribute__((aligned(16))) uint8_t bits[4][8 * 8 * 48];          // per wavefront: 8 rows x 8 blocks x (16 + 32) bytes
+    if (given_up(a)) return;               // (res_sign is indexed by the bitmap)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int qtiles = (a.nb + 7) / 8;
     const int i0 = ((int)(blockIdx.x / (unsigned)qtiles) * 4 + wave) * 8, q0 = (int)(blockIdx.x % (unsigned)qtiles) * 8;
@@ -1333,20 +1344,24 @@ extern "C" int stb_pack_obc_gpu(const float* W, const double* Hc, const float* x
     return rc;
 }
 
-// Break points of every block (region_mode 0).  Waits for the stream once, to read which candidates are left.
-static int search_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream_t st, int* hip_err) {
-    hipError_t e = hipSuccess;
-    auto ok = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; return e == hipSuccess; };
-    double* const err = (double*)(ws + wp.err);
-    uint32_t* const left = a.hist;                             // (nb * 512 words; the tertile split alone uses them otherwise)
-    unsigned long long* const above = (unsigned long long*)(err + (size_t)a.nb * SC_NV);       // behind the gains
-    ok(hipMemsetAsync(err, 0, (size_t)a.nb * SC_NV * 16, st));
+// Break points of every block (region_mode 0) by bounds; ST_CLOSE if some block needs exact_breakpoints.  The gains start at zero.
+static void bound_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream_t st) {
+    double* const gain = (double*)(ws + wp.err);
+    unsigned long long* const above = (unsigned long long*)(gain + (size_t)a.nb * SC_NV);      // behind the gains
     // two workgroups a compute unit: four rounds of them at least before a workgroup takes more rows for its set-up
     const int64_t tiles = (int64_t)((a.n + SC_ROWS - 1) / SC_ROWS) * a.nb;
     const int steps = tiles >= 2048 * SC_STEPS ? SC_STEPS : tiles < 2048 ? 1 : (int)(tiles / 2048), rows = SC_ROWS * steps;
-    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(64 * SC_WAVES), 0, st, a, steps, err, above);
-    hipLaunchKernelGGL(k_search_narrow, dim3(a.nb), dim3(64), 0, st, a, err, above, left);
-    ok(hipGetLastError());
+    hipLaunchKernelGGL(k_search_gain, dim3((unsigned)((int64_t)((a.n + rows - 1) / rows) * a.nb)), dim3(64 * SC_WAVES), 0, st, a, steps, gain, above);
+    // (the masks of candidates left: nb * 512 words, which the tertile split alone uses otherwise)
+    hipLaunchKernelGGL(k_search_narrow, dim3(a.nb), dim3(64), 0, st, a, gain, above, a.hist);
+}
+
+// ... of the blocks in which several candidates are left: waits for the stream to read which.
+static int exact_breakpoints(const PK& a, const WsPlan& wp, char* ws, hipStream_t st, int* hip_err) {
+    hipError_t e = hipSuccess;
+    auto ok = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; return e == hipSuccess; };
+    double* const err = (double*)(ws + wp.err);
+    uint32_t* const left = a.hist;
     std::vector<uint32_t> mask((size_t)a.nb * SC_MASKW);
     ok(hipMemcpyAsync(mask.data(), left, mask.size() * 4, hipMemcpyDeviceToHost, st));
     ok(hipStreamSynchronize(st));
@@ -1406,37 +1421,16 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
 
     hipError_t e = hipSuccess;
     auto ok = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; return e == hipSuccess; };
-    // everything that is accumulated into starts at zero
-    ok(hipMemsetAsync(ws, 0, (size_t)wp.err, st));
+    // everything that is accumulated into starts at zero, the gains of the search (behind the rest) among it
+    ok(hipMemsetAsync(ws, 0, (size_t)(wp.err + (a.region_mode == 0 ? (int64_t)a.nb * SC_NV * 16 : 0)), st));
     if (out->res_bytes) ok(hipMemsetAsync(out->res_sign, 0, (size_t)out->res_bytes, st));
     if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
 
     const int T = 256;
-    // the salient bitmap must hold exactly cfg.n_salient columns before anything indexes the res_sign rows by it
+    // the salient bitmap must hold exactly cfg.n_salient columns before anything indexes the res_sign rows by it (k_assign looks)
     hipLaunchKernelGGL(k_salient_tables, dim3(1), dim3(64), 0, st, a);
     const dim3 mask_grid((unsigned)((int64_t)((a.n + MK_ROWS - 1) / MK_ROWS) * a.nb));
-    if (!a.per_block) {
-        const int64_t chunks = (a.k + FS_COLS - 1) / FS_COLS, rows = (a.n * chunks + FS_WGS * FS_BATCH - 1) / (FS_WGS * FS_BATCH) * FS_BATCH;
-        hipLaunchKernelGGL(k_layer_sums, dim3((unsigned)((a.n + rows - 1) / rows * chunks)), dim3(T), 0, st, a, (int)rows);
-        hipLaunchKernelGGL(k_layer_mean, dim3(1), dim3(1024), 0, st, a);
-        switch (a.M * 16 + a.N) {
-#define STB_MASK(M, N) case M * 16 + N: hipLaunchKernelGGL((k_layer_mask<M, N>), mask_grid, dim3(T), 0, st, a); break;
-            STB_MASK(4, 1) STB_MASK(4, 2) STB_MASK(4, 3) STB_MASK(4, 4)
-            STB_MASK(8, 1) STB_MASK(8, 2) STB_MASK(8, 3) STB_MASK(8, 4) STB_MASK(8, 5) STB_MASK(8, 6) STB_MASK(8, 7) STB_MASK(8, 8)
-#undef STB_MASK
-            default: return STB_EINVAL;
-        }
-    }
-    uint32_t status = 0;
-    ok(hipGetLastError());
-    ok(hipMemcpyAsync(&status, a.status, 4, hipMemcpyDeviceToHost, st));
-    ok(hipStreamSynchronize(st));
-    if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
-    if (status & ST_SALIENT) return STB_EINVAL;
-    if (status & ST_NONFINITE) return STB_ENONFINITE;
-    if (a.per_block || (status & ST_UNDECIDED)) {
-        if (status) ok(hipMemsetAsync(ws + wp.mxbits, 0, (size_t)(wp.p12 - wp.mxbits), st));       // maxima and counts of the mask by bounds
-        if (status) ok(hipMemsetAsync(a.status, 0, 4, st));
+    auto ordered_mask = [&]() {                                // importance from the sums in the defined order
         const unsigned row_wgs = (unsigned)((a.n + RC_ROWS - 1) / RC_ROWS);
         hipLaunchKernelGGL(k_abs_sums, dim3(a.k / CC_COLS + row_wgs), dim3(CHAIN_THREADS), 0, st, a);
         hipLaunchKernelGGL(k_mu_sums<1>, dim3(row_wgs), dim3(CHAIN_THREADS), 0, st, a);
@@ -1445,38 +1439,75 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
         hipLaunchKernelGGL(k_total<1>, dim3(a.nbS), dim3(64), 0, st, a);
         if (a.M == 4) hipLaunchKernelGGL(k_mask<4>, mask_grid, dim3(T), 0, st, a);
         else hipLaunchKernelGGL(k_mask<8>, mask_grid, dim3(T), 0, st, a);
-    }
-    if (a.region_mode == 0) {
-        try {
-            const int rc = search_breakpoints(a, wp, ws, st, hip_err);
-            if (rc != STB_OK) return rc;
-        } catch (const std::bad_alloc&) { *hip_err = (int)hipErrorOutOfMemory; return STB_EHIP; }
-    } else {
+    };
+    auto break_points = [&]() {
+        if (a.region_mode == 0) { bound_breakpoints(a, wp, ws, st); return; }
         hipLaunchKernelGGL(k_select_init, dim3((a.nb + 63) / 64), dim3(64), 0, st, a);
         for (int pass = 0; pass < 4; pass++) {
             hipLaunchKernelGGL(k_select_hist, mask_grid, dim3(T), 0, st, a, pass);
             hipLaunchKernelGGL(k_select_step, dim3(2 * a.nb), dim3(64), 0, st, a, pass);
         }
-    }
-    const dim3 assign_grid((unsigned)((int64_t)((a.n + 31) / 32) * ((a.nb + 7) / 8)));
-    switch (8 * a.N / a.M) {
-        case 1: hipLaunchKernelGGL(k_assign<1>, assign_grid, dim3(T), 0, st, a); break;
-        case 2: hipLaunchKernelGGL(k_assign<2>, assign_grid, dim3(T), 0, st, a); break;
-        case 3: hipLaunchKernelGGL(k_assign<3>, assign_grid, dim3(T), 0, st, a); break;
-        case 4: hipLaunchKernelGGL(k_assign<4>, assign_grid, dim3(T), 0, st, a); break;
-        case 5: hipLaunchKernelGGL(k_assign<5>, assign_grid, dim3(T), 0, st, a); break;
-        case 6: hipLaunchKernelGGL(k_assign<6>, assign_grid, dim3(T), 0, st, a); break;
-        case 7: hipLaunchKernelGGL(k_assign<7>, assign_grid, dim3(T), 0, st, a); break;
-        default: hipLaunchKernelGGL(k_assign<8>, assign_grid, dim3(T), 0, st, a); break;
-    }
-    ok(hipGetLastError());
-    ok(hipMemcpyAsync(&status, a.status, 4, hipMemcpyDeviceToHost, st));
-    ok(hipStreamSynchronize(st));
-    *hip_err = (int)e;
-    if (e != hipSuccess) return STB_EHIP;
+    };
+    auto assign = [&]() {
+        const dim3 grid((unsigned)((int64_t)((a.n + 31) / 32) * ((a.nb + 7) / 8)));
+        switch (8 * a.N / a.M) {
+            case 1: hipLaunchKernelGGL(k_assign<1>, grid, dim3(T), 0, st, a); break;
+            case 2: hipLaunchKernelGGL(k_assign<2>, grid, dim3(T), 0, st, a); break;
+            case 3: hipLaunchKernelGGL(k_assign<3>, grid, dim3(T), 0, st, a); break;
+            case 4: hipLaunchKernelGGL(k_assign<4>, grid, dim3(T), 0, st, a); break;
+            case 5: hipLaunchKernelGGL(k_assign<5>, grid, dim3(T), 0, st, a); break;
+            case 6: hipLaunchKernelGGL(k_assign<6>, grid, dim3(T), 0, st, a); break;
+            case 7: hipLaunchKernelGGL(k_assign<7>, grid, dim3(T), 0, st, a); break;
+            default: hipLaunchKernelGGL(k_assign<8>, grid, dim3(T), 0, st, a); break;
+        }
+    };
+    uint32_t status = 0;
+    auto finish = [&]() {                                      // waits for the stream and reads the status
+        ok(hipGetLastError());
+        ok(hipMemcpyAsync(&status, a.status, 4, hipMemcpyDeviceToHost, st));
+        ok(hipStreamSynchronize(st));
+        return e == hipSuccess;
+    };
+    if (!a.per_block) {
+        const int64_t chunks = (a.k + FS_COLS - 1) / FS_COLS, rows = (a.n * chunks + FS_WGS * FS_BATCH - 1) / (FS_WGS * FS_BATCH) * FS_BATCH;
+        hipLaunchKernelGGL(k_layer_sums, dim3((unsigned)((a.n + rows - 1) / rows * chunks)), dim3(T), 0, st, a, (int)rows);
+        hipLaunchKernelGGL(k_layer_mean, dim3((unsigned)(((int64_t)a.n + a.k + 255) / 256)), dim3(T), 0, st, a);
+        switch (a.M * 16 + a.N) {
+#define STB_MASK(M, N) case M * 16 + N: hipLaunchKernelGGL((k_layer_mask<M, N>), mask_grid, dim3(T), 0, st, a); break;
+            STB_MASK(4, 1) STB_MASK(4, 2) STB_MASK(4, 3) STB_MASK(4, 4)
+            STB_MASK(8, 1) STB_MASK(8, 2) STB_MASK(8, 3) STB_MASK(8, 4) STB_MASK(8, 5) STB_MASK(8, 6) STB_MASK(8, 7) STB_MASK(8, 8)
+#undef STB_MASK
+            default: return STB_EINVAL;
+        }
+    } else ordered_mask();
+    // Almost always the whole call: what a later kernel must not work on (an unchecked bitmap, a mask or break points that the bounds
+    // leave open) makes it return at once, and the host sees why.  (28672 x 8192 4:8, packing and tiling: 1390 us with a look after the mask,
+    // one after the search and the small tables of the tiled order made on the host, 1262 like this.)
+    break_points();
+    assign();
+    if (!finish()) { *hip_err = (int)e; return STB_EHIP; }
+    if (status & ST_SALIENT) return STB_EINVAL;
     if (status & ST_NONFINITE) return STB_ENONFINITE;
-    if (status & ~ST_NONFINITE) return STB_EINVAL;
-    return STB_OK;
+    if (status & ST_UNDECIDED) {
+        ok(hipMemsetAsync(ws + wp.mxbits, 0, (size_t)(wp.p12 - wp.mxbits), st));       // maxima and counts of the mask by bounds
+        ok(hipMemsetAsync(a.status, 0, 4, st));
+        ordered_mask();
+        break_points();
+        assign();
+        if (!finish()) { *hip_err = (int)e; return STB_EHIP; }
+        if (status & ST_NONFINITE) return STB_ENONFINITE;
+    }
+    if (status & ST_CLOSE) {
+        try {
+            const int rc = exact_breakpoints(a, wp, ws, st, hip_err);
+            if (rc != STB_OK) return rc;
+        } catch (const std::bad_alloc&) { *hip_err = (int)hipErrorOutOfMemory; return STB_EHIP; }
+        ok(hipMemsetAsync(a.status, 0, 4, st));
+        assign();
+        if (!finish()) { *hip_err = (int)e; return STB_EHIP; }
+    }
+    *hip_err = (int)e;
+    return status ? STB_EINVAL : STB_OK;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1586,6 +1617,66 @@ __global__ __launch_bounds__(256) void k_tile_records(TK a) {
     a.tres_scale[idx] = rs;
 }
 
+// The tables that depend on the salient bitmap alone.  Workgroup 0: bitmap and prefix padded to whole superblocks, and whether they
+// describe cfg.n_salient columns (*status: 0 or 8); the others: a thread per record of sal_tab, 8 salient columns of a half
+// block, as the host routine fills it.
+__global__ __launch_bounds__(256) void k_tile_tables(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix, int n_salient, int chunks,
+                                                     uint32_t* __restrict__ bitmap_out, uint32_t* __restrict__ prefix_out, uint32_t* __restrict__ tab) {
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        for (int u = tid; u < a.nsb * 16; u += 256) bitmap_out[u] = u < a.nb * 4 ? bitmap[u] : 0u;
+        for (int q = tid; q <= a.nsb * 4; q += 256) prefix_out[q] = prefix[q < a.nb ? q : a.nb];
+        if (tid >= 64) return;
+        uint32_t run = 0;
+        bool bad = false;
+        for (int q0 = 0; q0 < a.nb; q0 += 64) {
+            const int q = q0 + tid;
+            uint32_t own = 0;
+            if (q < a.nb)
+                for (int u = 0; u < 4; u++) own += (uint32_t)__popc(bitmap[4 * q + u]);
+            uint32_t upto = own;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = __shfl_up(upto, d);
+                if (tid >= d) upto += o;
+            }
+            if (q < a.nb) bad |= prefix[q] != run + upto - own;
+            run += __shfl(upto, 63);
+        }
+        bad = __any(bad) || prefix[a.nb] != run || run != (uint32_t)n_salient;
+        if (tid == 0) *a.status = bad ? 8u : 0u;
+        return;
+    }
+    const int rec = ((int)blockIdx.x - 1) * 256 + tid;
+    if (rec >= a.nsb * 8 * chunks) return;
+    const int c = rec % chunks, q = rec / chunks >> 1, h = rec / chunks & 1;
+    auto half = [&](int b, int u) { return b < a.nb ? bitmap[4 * b + 2 * u] | (uint64_t)bitmap[4 * b + 2 * u + 1] << 32 : 0ull; };
+    int need = 0;                                              // records of the fullest of the superblock's four halves
+    for (int g = 0; g < 4; g++) {
+        const int r = (__popcll(half((q & ~3) + g, h)) + 7) / 8;
+        need = r > need ? r : need;
+    }
+    uint64_t left = half(q, h);
+    for (int u = 0; u < 8 * c; u++) left &= left - 1;
+    uint32_t sel[2] = {0u, 0u}, bit[2] = {0u, 0u}, pos[4] = {0u, 0u, 0u, 0u}, cnt = 0;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const bool valid = left != 0;
+        const uint32_t col = valid ? (uint32_t)(64 * h + __ffsll((unsigned long long)left) - 1) : 0xFFFFu;
+        left &= left - 1;
+        sel[e >> 2] |= (valid ? (col >> 3) & 7u : 0x0Cu) << (8 * (e & 3));
+        bit[e >> 2] |= valid ? (1u << (col & 7u)) << (8 * (e & 3)) : 0u;
+        pos[e >> 1] |= col << (16 * (e & 1));
+        cnt += valid;
+    }
+    const uint32_t ord = prefix[q < a.nb ? q : a.nb] + (h ? (uint32_t)__popcll(half(q, 0)) : 0u) + 8u * (uint32_t)c;
+    uint32_t* const out = tab + (int64_t)rec * 12;             // [block][half][chunk]
+    out[0] = sel[0]; out[1] = sel[1]; out[2] = bit[0]; out[3] = bit[1];
+    out[4] = ord; out[5] = (uint32_t)need; out[6] = cnt; out[7] = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; e++) out[8 + e] = pos[e];
+}
+
 // res_sign: the row strings cut into 32-bit words and transposed inside each 16-row tile; one thread per word, padding rows
 // included
 __global__ void k_tile_res(TK a) {
@@ -1596,7 +1687,8 @@ __global__ void k_tile_res(TK a) {
 }
 
 // res_t: per (row, block) the res_sign bits of the first 16 salient columns of each half block; one thread per record
-__global__ void k_tile_res_t(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix,
+// (ord < n_salient in all that k_tile_tables finds right)
+__global__ void k_tile_res_t(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix, int n_salient,
                              uint32_t* __restrict__ res_t) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)a.nrt * a.nsb * 64) return;
@@ -1611,7 +1703,7 @@ __global__ void k_tile_res_t(TK a, const uint32_t* __restrict__ bitmap, const ui
             uint32_t bits = bitmap[4 * q + 2 * h + u];
             while (bits) {
                 bits &= bits - 1;
-                if (e < 16 && ((row[ord >> 5] >> (ord & 31)) & 1u)) word |= 1u << (16 * h + e);
+                if (e < 16 && ord < (uint32_t)n_salient && ((row[ord >> 5] >> (ord & 31)) & 1u)) word |= 1u << (16 * h + e);
                 e++;
                 ord++;
             }
@@ -1628,27 +1720,6 @@ extern "C" int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* st
     hipError_t e = hipSuccess;
     auto ok = [&](hipError_t r) { if (e == hipSuccess && r != hipSuccess) e = r; return e == hipSuccess; };
     const int k = src->cfg.k_in, nb = src->n_blocks;
-    // the derived tables depend on the salient bitmap only: they are made on the host and copied
-    std::vector<uint32_t> bitmap((size_t)k / 32), prefix((size_t)nb + 1);
-    ok(hipMemcpyAsync(bitmap.data(), src->sal_bitmap, (size_t)k / 8, hipMemcpyDeviceToHost, st));
-    ok(hipMemcpyAsync(prefix.data(), src->sal_block_prefix, 4 * ((size_t)nb + 1), hipMemcpyDeviceToHost, st));
-    ok(hipStreamSynchronize(st));
-    if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
-    {   // the kernels index the res_sign rows through these tables: they must describe cfg.n_salient columns
-        uint32_t run = 0;
-        for (int q = 0; q < nb; q++) {
-            if (prefix[q] != run) return STB_EINVAL;
-            for (int u = 0; u < 4; u++) run += (uint32_t)__builtin_popcount(bitmap[4 * q + u]);
-        }
-        if (prefix[nb] != run || run != (uint32_t)src->cfg.n_salient) return STB_EINVAL;
-    }
-    std::vector<uint32_t> bm_out((size_t)dst->salmap_bytes / 4), pf_out((size_t)dst->salprefix_bytes / 4),
-        tab((size_t)dst->saltab_bytes / 4 + 1, 0u);
-    int mx = 0, mh = 0;
-    stb_host_tiled_tables(dst, bitmap.data(), prefix.data(), bm_out.data(), pf_out.data(), tab.data(), &mx, &mh);
-    ok(hipMemcpyAsync(dst->sal_bitmap, bm_out.data(), (size_t)dst->salmap_bytes, hipMemcpyHostToDevice, st));
-    ok(hipMemcpyAsync(dst->sal_block_prefix, pf_out.data(), (size_t)dst->salprefix_bytes, hipMemcpyHostToDevice, st));
-    if (dst->saltab_bytes) ok(hipMemcpyAsync(dst->sal_tab, tab.data(), (size_t)dst->saltab_bytes, hipMemcpyHostToDevice, st));
     TK a;
     a.rmask = (const uint8_t*)src->mask; a.rsign = (const uint8_t*)src->sign; a.rreg = (const uint8_t*)src->region;
     a.rscales = src->scales; a.rres_scale = src->res_scale; a.rres_sign = (const uint32_t*)src->res_sign;
@@ -1663,8 +1734,10 @@ extern "C" int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* st
     uint32_t* status_dev = nullptr;
     ok(hipGetSymbolAddress((void**)&status_dev, HIP_SYMBOL(tile_status)));
     if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
-    ok(hipMemsetAsync(status_dev, 0, 4, st));
     a.status = status_dev;
+    const int recs_tab = a.nsb * 8 * dst->sal_chunks;
+    hipLaunchKernelGGL(k_tile_tables, dim3((unsigned)(1 + (recs_tab + 255) / 256)), dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix, src->cfg.n_salient,
+                       dst->sal_chunks, dst->sal_bitmap, dst->sal_block_prefix, dst->sal_tab);
     const int64_t recs = (int64_t)a.nrt * a.nsb * 64;
     const dim3 rec_grid((unsigned)((recs + 255) / 256));
     switch (8 * src->cfg.N / src->cfg.M) {
@@ -1680,15 +1753,25 @@ extern "C" int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* st
     if (a.res_words > 0) {
         const int64_t words = (int64_t)a.nrt * 16 * a.res_words;
         hipLaunchKernelGGL(k_tile_res, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, a);
-        hipLaunchKernelGGL(k_tile_res_t, rec_grid, dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix, dst->res_t);
+        hipLaunchKernelGGL(k_tile_res_t, rec_grid, dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix, src->cfg.n_salient, dst->res_t);
     }
     ok(hipGetLastError());
+    // the two maxima follow from the bitmap
+    std::vector<uint32_t> bitmap((size_t)k / 32);
     uint32_t status = 0;
+    ok(hipMemcpyAsync(bitmap.data(), src->sal_bitmap, (size_t)k / 8, hipMemcpyDeviceToHost, st));
     ok(hipMemcpyAsync(&status, status_dev, 4, hipMemcpyDeviceToHost, st));
-    ok(hipStreamSynchronize(st));          // also: the host arrays of the tables must outlive their copies
+    ok(hipStreamSynchronize(st));
     *hip_err = (int)e;
     if (e != hipSuccess) return STB_EHIP;
     if (status) return STB_EINVAL;
+    int mx = 0, mh = 0;
+    for (int q = 0; q < nb; q++) {
+        int of[2];
+        for (int h = 0; h < 2; h++) of[h] = __builtin_popcount(bitmap[4 * q + 2 * h]) + __builtin_popcount(bitmap[4 * q + 2 * h + 1]);
+        mh = std::max(mh, std::max(of[0], of[1]));
+        mx = std::max(mx, of[0] + of[1]);
+    }
     dst->max_sal_block = mx;
     dst->max_sal_half = mh;
     return STB_OK;

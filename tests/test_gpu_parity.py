@@ -236,6 +236,20 @@ def test_device_packer_values_on_break_points_and_crowded_blocks(n, k, N, M, mod
     pm = _pack_on_device(torch_cuda, W, xnorm, bitmap, N, M, mode)
     for name, v in O.pack(W, xnorm, bitmap, N, M, mode).items():
         assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+    # its tables of salient columns, against the host's; a prefix that does not fit the bitmap is refused
+    tl_host, timg_host = pm.tiled()
+    rimg, timg = torch_cuda.from_numpy(pm.host_image).cuda(), S.new_device_scratch(tl_host.image_bytes)
+    rlay, tlay = pm.clone_layout_for(rimg.data_ptr(), False), S.stb_tiled_sizes(pm.cfg)
+    S.stb_layout_bind(tlay, timg.data_ptr())
+    S.stb_tile_device(rlay, tlay)
+    assert (tlay.max_sal_block, tlay.max_sal_half) == (tl_host.max_sal_block, tl_host.max_sal_half)
+    got = timg.cpu().numpy()
+    for name, off, size in S.PLANE_FIELDS + (("sal_tab", "off_saltab", "saltab_bytes"), ("res_t", "off_res_t", "res_t_bytes")):
+        o, sz = getattr(tl_host, off), getattr(tl_host, size)
+        assert (got[o:o + sz] == timg_host[o:o + sz]).all(), name
+    rimg[rlay.off_salprefix + 4 * (k // 128 - 1)] ^= 1
+    with pytest.raises(S.StbError):
+        S.stb_tile_device(rlay, tlay)
 
 
 @pytest.mark.parametrize("levels", [1, 2, 15])
