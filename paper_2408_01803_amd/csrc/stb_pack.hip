@@ -24,6 +24,7 @@
 namespace {
 
 constexpr int CAND = 160;                  // break-point candidates of Alg. 2
+constexpr int SH_COPIES = 16, LAYER_MASK_LDS = SH_COPIES * 257 * 4;      // copies of the tertile split's counts in LDS
 constexpr int MK_ROWS = 256;               // rows of one block that a workgroup of the mask kernels takes
 constexpr uint32_t ST_NONFINITE = 1u, ST_SALIENT = 2u, ST_GROUP = 4u, ST_UNDECIDED = 8u,
                    ST_CLOSE = 16u;         // a block's break points need the exact evaluation
@@ -227,10 +228,19 @@ __device__ inline void around_cut(const float (&s)[8], int h, float& low, float&
 // A workgroup takes 256 rows of one block: 16 rows at a time, a thread 8 columns, whose column sums and norms stay in
 // registers.  Scores in fp32, whose error is below 2^-20 xnorm (mu + mean): where the N-th largest of a group is further than
 // both errors above the next, the scores not below it are kept; the few groups in a million where it is not are taken again
-// in float64.  Also the largest kept non-salient magnitude and their number per block.
+// in float64.  Also the largest kept non-salient magnitude and their number per block, and for the tertile split
+// the counts of their leading bytes (k_select_hist's first pass, in LAYER_MASK_LDS bytes of dynamic LDS: 28672 x 8192 6:8 198 us without, 200 with them, against 219 for a pass of its own).
 template <int M, int N>
 __global__ __launch_bounds__(256) void k_layer_mask(PK a) {
-    if (given_up(a)) return;               // (the layer goes the other way)
+    extern __shared__ uint32_t digits[];           // [SH_COPIES][257]
+    const bool tertiles = a.region_mode != 0;
+    // (the layer goes the other way: a wavefront by itself, or all of a workgroup that shares counts)
+    if (tertiles ? __syncthreads_or(given_up(a)) != 0 : given_up(a)) return;
+    uint32_t* const own = digits + (threadIdx.x & (SH_COPIES - 1)) * 257;
+    if (tertiles) {
+        for (int e = threadIdx.x; e < SH_COPIES * 257; e += 256) digits[e] = 0;
+        __syncthreads();
+    }
     const int q = (int)(blockIdx.x % (unsigned)a.nb), g = threadIdx.x & 15, r = threadIdx.x >> 4;
     const int ibeg = (int)(blockIdx.x / (unsigned)a.nb) * MK_ROWS + r, j0 = q * STB_BLOCK + 8 * g;
     const int iend = (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS < a.n ? (int)(blockIdx.x / (unsigned)a.nb + 1) * MK_ROWS : a.n;
@@ -283,6 +293,11 @@ __global__ __launch_bounds__(256) void k_layer_mask(PK a) {
             const uint32_t bits = kept ? __float_as_uint(e[p]) & normal[p] : 0u;      // magnitudes order like their bit patterns
             mx = bits > mx ? bits : mx;
         }
+        if (tertiles) {
+#pragma unroll
+            for (int p = 0; p < 8; p++)
+                if ((byte & normal8) >> p & 1u) atomicAdd(own + (__float_as_uint(e[p]) >> 24), 1u);
+        }
         a.mask[(size_t)i * a.mask_stride + (j0 >> 3)] = (uint8_t)byte;
         members += (uint32_t)__popc(byte & normal8);
     };
@@ -305,11 +320,22 @@ __global__ __launch_bounds__(256) void k_layer_mask(PK a) {
         for (int p = 0; p < 8; p++) {
             const uint32_t bits = (byte >> p) & 1u ? __float_as_uint(e[p]) & normal[p] : 0u;
             mx = bits > mx ? bits : mx;
+            if (tertiles && ((byte & normal8) >> p & 1u)) atomicAdd(own + (__float_as_uint(e[p]) >> 24), 1u);
         }
         a.mask[(size_t)i * a.mask_stride + (j0 >> 3)] = (uint8_t)byte;
         members += (uint32_t)__popc(byte & normal8);
     }
     if (undecided) atomicOr(a.status, ST_UNDECIDED);
+    if (tertiles) {                                // both statistics start from the same counts
+        __syncthreads();
+        uint32_t sum = 0;
+#pragma unroll
+        for (int c = 0; c < SH_COPIES; c++) sum += digits[c * 257 + threadIdx.x];
+        if (sum) {
+            atomicAdd(a.hist + (size_t)q * 512 + threadIdx.x, sum);
+            atomicAdd(a.hist + (size_t)q * 512 + 256 + threadIdx.x, sum);
+        }
+    }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
         const uint32_t om = __shfl_xor(mx, d);
@@ -919,7 +945,7 @@ __global__ void k_select_init(PK a) {
 // block (a thread 8 columns of every 16th row) and counts in LDS, in 16 copies that lanes next to each other do not share
 // (a block's magnitudes have few leading bytes); only its sums go to memory.  5120 x 8704: 0.21 ms for the four passes; 5120 x 13824 took
 // 12.5 ms with an atomic in memory for every value.
-constexpr int SH_COPIES = 16, SH_STRIDE = 2 * 256 + 1;
+constexpr int SH_STRIDE = 2 * 256 + 1;
 __global__ __launch_bounds__(256) void k_select_hist(PK a, int pass) {
     __shared__ uint32_t h[SH_COPIES * SH_STRIDE];
     if (given_up(a)) return;
@@ -1440,11 +1466,11 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
         if (a.M == 4) hipLaunchKernelGGL(k_mask<4>, mask_grid, dim3(T), 0, st, a);
         else hipLaunchKernelGGL(k_mask<8>, mask_grid, dim3(T), 0, st, a);
     };
-    auto break_points = [&]() {
+    auto break_points = [&](bool first_counts) {               // first_counts: the mask kernel left them
         if (a.region_mode == 0) { bound_breakpoints(a, wp, ws, st); return; }
         hipLaunchKernelGGL(k_select_init, dim3((a.nb + 63) / 64), dim3(64), 0, st, a);
         for (int pass = 0; pass < 4; pass++) {
-            hipLaunchKernelGGL(k_select_hist, mask_grid, dim3(T), 0, st, a, pass);
+            if (pass > 0 || !first_counts) hipLaunchKernelGGL(k_select_hist, mask_grid, dim3(T), 0, st, a, pass);
             hipLaunchKernelGGL(k_select_step, dim3(2 * a.nb), dim3(64), 0, st, a, pass);
         }
     };
@@ -1473,7 +1499,7 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
         hipLaunchKernelGGL(k_layer_sums, dim3((unsigned)((a.n + rows - 1) / rows * chunks)), dim3(T), 0, st, a, (int)rows);
         hipLaunchKernelGGL(k_layer_mean, dim3((unsigned)(((int64_t)a.n + a.k + 255) / 256)), dim3(T), 0, st, a);
         switch (a.M * 16 + a.N) {
-#define STB_MASK(M, N) case M * 16 + N: hipLaunchKernelGGL((k_layer_mask<M, N>), mask_grid, dim3(T), 0, st, a); break;
+#define STB_MASK(M, N) case M * 16 + N: hipLaunchKernelGGL((k_layer_mask<M, N>), mask_grid, dim3(T), a.region_mode ? LAYER_MASK_LDS : 0, st, a); break;
             STB_MASK(4, 1) STB_MASK(4, 2) STB_MASK(4, 3) STB_MASK(4, 4)
             STB_MASK(8, 1) STB_MASK(8, 2) STB_MASK(8, 3) STB_MASK(8, 4) STB_MASK(8, 5) STB_MASK(8, 6) STB_MASK(8, 7) STB_MASK(8, 8)
 #undef STB_MASK
@@ -1483,7 +1509,7 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
     // Almost always the whole call: what a later kernel must not work on (an unchecked bitmap, a mask or break points that the bounds
     // leave open) makes it return at once, and the host sees why.  (28672 x 8192 4:8, packing and tiling: 1390 us with a look after the mask,
     // one after the search and the small tables of the tiled order made on the host, 1262 like this.)
-    break_points();
+    break_points(!a.per_block);
     assign();
     if (!finish()) { *hip_err = (int)e; return STB_EHIP; }
     if (status & ST_SALIENT) return STB_EINVAL;
@@ -1492,7 +1518,7 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
         ok(hipMemsetAsync(ws + wp.mxbits, 0, (size_t)(wp.p12 - wp.mxbits), st));       // maxima and counts of the mask by bounds
         ok(hipMemsetAsync(a.status, 0, 4, st));
         ordered_mask();
-        break_points();
+        break_points(false);                                   // (k_select_step has cleared the counts)
         assign();
         if (!finish()) { *hip_err = (int)e; return STB_EHIP; }
         if (status & ST_NONFINITE) return STB_ENONFINITE;
