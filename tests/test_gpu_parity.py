@@ -754,6 +754,45 @@ def test_an_fp32_sum_runs_over_no_more_columns_than_fill_the_chip(n, k, N, M, T,
     assert 1 <= ns - int(kept[0, 0]) <= longest, (ns, float(kept[0, 0]), longest)
 
 
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (6, 8)])
+@pytest.mark.parametrize("n,k", [(13824, 5120), (13801, 4736)])
+@pytest.mark.parametrize("T", [29, 64, 101])
+def test_gemm_with_k_groups_that_begin_inside_a_superblock(T, n, k, N, M, torch_cuda):
+    """20 passes of half a superblock in 4 groups of 5 (the small dense kernel, folded and not, the small 2:4 one, and those of 128 tokens),
+    with half blocks of 0 to 40 salient columns and a last superblock of one block, against float64 on the dequantised weights.  An
+    fp32 sum of k exact products is off by less than k 2^-24 of the sum of magnitudes; a pass left out or taken twice by 40 times that."""
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(T + n)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    xnorm = torch.rand(k, generator=g, device="cuda") + 0.5
+    bits = np.zeros(k, dtype=np.uint8)
+    bits[::29] = 1
+    bits[700:740] = bits[2690:2702] = 1
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 1)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    _say(f"[case] gemm {n}x{k} {N}:{M} T={T}")
+    S.stb_pack_device(W, xnorm, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    x = torch.randn((T, k), generator=g, device="cuda").half()
+    ref = x.double() @ What.double().t()
+    bound = x.double().abs() @ What.double().abs().t()
+    for fp32 in (True, False):
+        y = torch.full((T, n), float("nan"), dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+        if T <= 32:
+            S.stb_gemv(tl, x, T, y, fp32, S.new_device_scratch(S.stb_gemv_workspace_bytes(cfg, T), zero=True))
+        else:
+            S.stb_gemm(tl, x, T, y, fp32, S.new_device_scratch(S.stb_gemm_workspace_bytes(tl, T)))
+        torch.cuda.synchronize()
+        slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+        assert bool(((y.double() - ref).abs() <= slack).all()), fp32
+
+
 def test_gemm_runs_in_the_scratch_that_the_smaller_form_asks_for(torch_cuda):
     """A program that does not want to hold expanded weights asks stb_gemm_form for the other form's scratch: the call runs in
     exactly that, and is refused with less."""
