@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void k_layer_mask(PK a) {
         uint32_t byte = 0;
 #pragma unroll
         for (int p = 0; p < 8; p++) {
-            const bool kept = s[p] >= (sure ? low[p / 4] : __builtin_inff());
+            const bool kept = s[p] >= (sure ? low[p / 4] : __builtin_nanf(""));       // (not sure: none, an infinite score neither)
             byte |= kept ? 1u << p : 0u;
             const uint32_t bits = kept ? __float_as_uint(e[p]) & normal[p] : 0u;      // magnitudes order like their bit patterns
             mx = bits > mx ? bits : mx;

@@ -215,6 +215,34 @@ def test_device_packer_mask_where_scores_are_close(n, k, N, M, values, torch_cud
 
 
 @pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("values", ["dead row", "dead column", "largest pruned"])
+@pytest.mark.parametrize("n,k,N,M", [(300, 1024, 4, 8), (257, 1152, 2, 4)])
+def test_device_packer_counts_a_row_that_is_taken_again_once(n, k, N, M, values, mode, torch_cuda):
+    """fp32 scores that are no numbers (a sum whose reciprocal, or a norm over a sum that, leaves the fp32 range): the group is decided in float64,
+    and what the fp32 scores said of it enters neither the block's largest kept magnitude nor the counts of the tertile split."""
+    rng = np.random.default_rng(n + k)
+    W = rng.standard_normal((n, k)).astype(np.float32)
+    xnorm = np.abs(1 + 0.3 * rng.standard_normal(k)).astype(np.float32)
+    if values == "dead row":                       # a row of subnormal numbers among ordinary ones
+        W[n // 2] = (np.round(W[n // 2] * 20) * 1.4012984643e-45).astype(np.float32)
+    elif values == "dead column":
+        W[:, k // 2 + 3] = (np.round(W[:, k // 2 + 3] * 20) * 1.4012984643e-45).astype(np.float32)
+    else:                                          # column 3 holds the largest magnitudes of its block, below the mean importance: a norm
+        W[:, :128] *= np.float32(0.001)            # of 3e38 prunes them all
+        W[:, 3] = np.float32(0.01)
+        W *= np.float32(1e-4)
+        xnorm[3] = np.float32(3e38)
+    none = np.zeros(k // 32, dtype=np.uint32)
+    ref = O.pack(W, xnorm, none, N, M, mode)
+    if values == "largest pruned":
+        assert not (ref["mask"][:, 0] & 8).any()
+    _say(f"[case] rows taken again {n}x{k} {N}:{M} {values} mode {mode}")
+    pm = _pack_on_device(torch_cuda, W, xnorm, none, N, M, mode)
+    for name, v in ref.items():
+        assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+
+
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("n,k,N,M", [(1, 128, 4, 8), (63, 1152, 8, 8), (64, 256, 3, 8), (65, 1024, 6, 8), (4099, 128, 4, 8), (577, 2944, 4, 4)])
 def test_device_packer_values_on_break_points_and_crowded_blocks(n, k, N, M, mode, torch_cuda):
     """Magnitudes that are the search's own break points, or the fp32 numbers next to them (p1 and p2 lie between the bins), and
