@@ -1541,15 +1541,13 @@ extern "C" int stb_pack_gpu(const float* W, const float* xnorm, const uint32_t* 
 // ------------------------------------------------------------------------------------------------
 namespace {
 
-static __device__ uint32_t tile_status;
-
 struct TK {
     const uint8_t* rmask; const uint8_t* rsign; const uint8_t* rreg; const uint16_t* rscales; const uint16_t* rres_scale;
     const uint32_t* rres_sign;
     uint8_t* tmask; uint8_t* tsign; uint8_t* treg; uint16_t* tscales; uint16_t* tres_scale; uint32_t* tres_sign;
     int64_t rmask_stride, rsign_stride, rreg_stride, rres_stride;
     int n, nb, nrt, nsb, res_words;
-    uint32_t* status;
+    uint32_t* finding;      // a mask byte that a padded layout cannot hold makes it non-zero; see stb_tile_gpu
 };
 
 // the WORDS words of a record: whole, or cut in two halves stored [tile][half][lane] when they are an even number
@@ -1628,7 +1626,7 @@ __global__ __launch_bounds__(256) void k_tile_records(TK a) {
                 put_bits(sg, T8 * g, T8, (s & slow) | ((s & ~slow) << 1));
                 put_bits(id, 2 * T8 * g, 2 * T8, (v & vlow) | ((v & ~vlow) << 2));
             }
-            if (bad) { atomicOr(a.status, 4u); return; }
+            if (bad) { atomicOr(a.finding, 1u); return; }
         }
     }
     put_record(a.tmask, tile, lane, m);
@@ -1643,34 +1641,14 @@ __global__ __launch_bounds__(256) void k_tile_records(TK a) {
     a.tres_scale[idx] = rs;
 }
 
-// The tables that depend on the salient bitmap alone.  Workgroup 0: bitmap and prefix padded to whole superblocks, and whether they
-// describe cfg.n_salient columns (*status: 0 or 8); the others: a thread per record of sal_tab, 8 salient columns of a half
-// block, as the host routine fills it.
-__global__ __launch_bounds__(256) void k_tile_tables(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix, int n_salient, int chunks,
+// The tables that depend on the salient bitmap alone.  Workgroup 0: bitmap and prefix padded to whole superblocks; the others: a
+// thread per record of sal_tab, 8 salient columns of a half block, as the host routine fills it.
+__global__ __launch_bounds__(256) void k_tile_tables(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix, int chunks,
                                                      uint32_t* __restrict__ bitmap_out, uint32_t* __restrict__ prefix_out, uint32_t* __restrict__ tab) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
         for (int u = tid; u < a.nsb * 16; u += 256) bitmap_out[u] = u < a.nb * 4 ? bitmap[u] : 0u;
         for (int q = tid; q <= a.nsb * 4; q += 256) prefix_out[q] = prefix[q < a.nb ? q : a.nb];
-        if (tid >= 64) return;
-        uint32_t run = 0;
-        bool bad = false;
-        for (int q0 = 0; q0 < a.nb; q0 += 64) {
-            const int q = q0 + tid;
-            uint32_t own = 0;
-            if (q < a.nb)
-                for (int u = 0; u < 4; u++) own += (uint32_t)__popc(bitmap[4 * q + u]);
-            uint32_t upto = own;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const uint32_t o = __shfl_up(upto, d);
-                if (tid >= d) upto += o;
-            }
-            if (q < a.nb) bad |= prefix[q] != run + upto - own;
-            run += __shfl(upto, 63);
-        }
-        bad = __any(bad) || prefix[a.nb] != run || run != (uint32_t)n_salient;
-        if (tid == 0) *a.status = bad ? 8u : 0u;
         return;
     }
     const int rec = ((int)blockIdx.x - 1) * 256 + tid;
@@ -1713,7 +1691,7 @@ __global__ void k_tile_res(TK a) {
 }
 
 // res_t: per (row, block) the res_sign bits of the first 16 salient columns of each half block; one thread per record
-// (ord < n_salient in all that k_tile_tables finds right)
+// (ord < n_salient wherever bitmap and prefix are right, which the host sees after the call's one wait)
 __global__ void k_tile_res_t(TK a, const uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ prefix, int n_salient,
                              uint32_t* __restrict__ res_t) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1755,14 +1733,11 @@ extern "C" int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* st
     a.rres_stride = src->res_stride;
     a.n = src->cfg.n_out; a.nb = nb; a.nrt = dst->n_row_tiles; a.nsb = dst->n_super;
     a.res_words = (int)(src->res_stride / 4);
-    // what the kernel finds (a mask byte with the wrong number of bits in a padded layout) comes back through a word
-    // of the library's own device memory; calls that overlap on one GPU share it
-    uint32_t* status_dev = nullptr;
-    ok(hipGetSymbolAddress((void**)&status_dev, HIP_SYMBOL(tile_status)));
-    if (e != hipSuccess) { *hip_err = (int)e; return STB_EHIP; }
-    a.status = status_dev;
+    // What the record kernel finds (a mask byte with the wrong number of bits in a padded layout) goes into the first word of the prefix that the
+    // table kernel has written before it: 0 in every valid image, and the call's own, so calls on other streams do not meet it.
+    a.finding = dst->sal_block_prefix;
     const int recs_tab = a.nsb * 8 * dst->sal_chunks;
-    hipLaunchKernelGGL(k_tile_tables, dim3((unsigned)(1 + (recs_tab + 255) / 256)), dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix, src->cfg.n_salient,
+    hipLaunchKernelGGL(k_tile_tables, dim3((unsigned)(1 + (recs_tab + 255) / 256)), dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix,
                        dst->sal_chunks, dst->sal_bitmap, dst->sal_block_prefix, dst->sal_tab);
     const int64_t recs = (int64_t)a.nrt * a.nsb * 64;
     const dim3 rec_grid((unsigned)((recs + 255) / 256));
@@ -1782,22 +1757,28 @@ extern "C" int stb_tile_gpu(const stb_layout_t* src, stb_layout_t* dst, void* st
         hipLaunchKernelGGL(k_tile_res_t, rec_grid, dim3(256), 0, st, a, src->sal_bitmap, src->sal_block_prefix, src->cfg.n_salient, dst->res_t);
     }
     ok(hipGetLastError());
-    // the two maxima follow from the bitmap
-    std::vector<uint32_t> bitmap((size_t)k / 32);
-    uint32_t status = 0;
-    ok(hipMemcpyAsync(bitmap.data(), src->sal_bitmap, (size_t)k / 8, hipMemcpyDeviceToHost, st));
-    ok(hipMemcpyAsync(&status, status_dev, 4, hipMemcpyDeviceToHost, st));
+    // the two maxima follow from the bitmap; bitmap and prefix must describe cfg.n_salient columns
+    std::vector<uint32_t> words;
+    try { words.resize((size_t)k / 32 + (size_t)nb + 1); } catch (const std::bad_alloc&) { e = hipErrorOutOfMemory; }
+    uint32_t *const bitmap = words.data(), *const prefix = bitmap + (size_t)k / 32;
+    if (e == hipSuccess) {
+        ok(hipMemcpyAsync(bitmap, src->sal_bitmap, (size_t)k / 8, hipMemcpyDeviceToHost, st));
+        ok(hipMemcpyAsync(prefix, dst->sal_block_prefix, 4 * ((size_t)nb + 1), hipMemcpyDeviceToHost, st));
+    }
     ok(hipStreamSynchronize(st));
     *hip_err = (int)e;
     if (e != hipSuccess) return STB_EHIP;
-    if (status) return STB_EINVAL;
     int mx = 0, mh = 0;
+    uint32_t run = 0;
     for (int q = 0; q < nb; q++) {
         int of[2];
         for (int h = 0; h < 2; h++) of[h] = __builtin_popcount(bitmap[4 * q + 2 * h]) + __builtin_popcount(bitmap[4 * q + 2 * h + 1]);
         mh = std::max(mh, std::max(of[0], of[1]));
         mx = std::max(mx, of[0] + of[1]);
+        if (prefix[q] != run) return STB_EINVAL;
+        run += (uint32_t)(of[0] + of[1]);
     }
+    if (prefix[nb] != run || run != (uint32_t)src->cfg.n_salient) return STB_EINVAL;
     dst->max_sal_block = mx;
     dst->max_sal_half = mh;
     return STB_OK;

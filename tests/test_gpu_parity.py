@@ -8,6 +8,7 @@ import hashlib
 import json
 import os
 import sys
+import threading
 import time
 
 import numpy as np
@@ -443,6 +444,55 @@ def test_device_packer_and_tiling_on_random_shapes(torch_cuda):
         for name, off, size in S.PLANE_FIELDS + (("sal_tab", "off_saltab", "saltab_bytes"), ("res_t", "off_res_t", "res_t_bytes")):
             o, sz = getattr(tl_host, off), getattr(tl_host, size)
             assert (got[o:o + sz] == timg_host[o:o + sz]).all(), (case, name)
+
+
+def test_tilings_that_overlap_keep_their_own_verdicts(torch_cuda):
+    """stb_tile_device from four threads on four streams at once: of a good layer, of one whose prefix does not fit its bitmap, of a good
+    padded one (5:8) and of one with a mask byte that keeps four.  Every call gets its own verdict, every good image is the host's."""
+    torch = torch_cuda
+
+    def layer(N, M, spoil):
+        L = make_layer(40, 640, 700 + N)
+        pm = S.PackedMatrix.pack(L["W"], L["xnorm"], L["sal_bitmap"], N, M, 0)
+        tl, timg = pm.tiled()
+        image = pm.host_image.copy()
+        spoil(pm.host_layout, image)
+        rimg, out = torch.from_numpy(image).cuda(), S.new_device_scratch(tl.image_bytes)
+        dst = S.stb_tiled_sizes(pm.cfg)
+        S.stb_layout_bind(dst, out.data_ptr())
+        return dict(src=pm.clone_layout_for(rimg.data_ptr(), False), dst=dst, out=out, want=timg, rimg=rimg, stream=torch.cuda.Stream(), verdicts=[])
+
+    def prefix(lay, image):
+        image[lay.off_salprefix + 4 * 3] ^= 1
+
+    def mask(lay, image):
+        byte = image[lay.off_mask + 7 * lay.mask_stride + 11]
+        image[lay.off_mask + 7 * lay.mask_stride + 11] = byte & (byte - 1)
+
+    layers = [layer(4, 8, lambda *a: None), layer(4, 8, prefix), layer(5, 8, lambda *a: None), layer(5, 8, mask)]
+    torch.cuda.synchronize()
+
+    def work(c):
+        for _ in range(300):
+            try:
+                S.stb_tile_device(c["src"], c["dst"], c["stream"].cuda_stream)
+                c["verdicts"].append(S.STB_OK)
+            except S.StbError as e:
+                c["verdicts"].append(e.status)
+
+    _say("[case] four threads tile at once")
+    threads = [threading.Thread(target=work, args=(c,)) for c in layers]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for c, want in zip(layers, (S.STB_OK, S.STB_EINVAL, S.STB_OK, S.STB_EINVAL)):
+        assert c["verdicts"] == [want] * 300
+        if want == S.STB_OK:
+            got = c["out"].cpu().numpy()
+            for name, off, size in S.PLANE_FIELDS + (("sal_tab", "off_saltab", "saltab_bytes"), ("res_t", "off_res_t", "res_t_bytes")):
+                o, sz = getattr(c["dst"], off), getattr(c["dst"], size)
+                assert (got[o:o + sz] == c["want"][o:o + sz]).all(), name
 
 
 def test_device_packer_edge_cases_and_errors(torch_cuda):
