@@ -314,6 +314,37 @@ def test_device_packer_takes_no_longer_where_candidates_tie(levels, torch_cuda):
     assert times["few"] <= 3.0 * times["normal"], times
 
 
+def test_device_packer_of_one_magnitude_takes_little_longer_than_its_ordered_sums(torch_cuda):
+    """A layer of one magnitude, whose mask only the sums in the defined order decide: the host's bytes, and within 1.25 times the time of a call that
+    starts with those sums (importance per block; with two passes over the weights and a float64 retake of every row before them 1.37, without 1.10)."""
+    torch = torch_cuda
+    n, k = 11008, 4096
+    L = make_layer(n, k, 43)
+    W = np.where(L["W"] >= 0, np.float32(0.75), np.float32(-0.75))
+    _say(f"[case] pack {n}x{k} of one magnitude")
+    Wd, xd = torch.from_numpy(W).cuda(), torch.from_numpy(L["xnorm"]).cuda()
+    bd = torch.from_numpy(L["sal_bitmap"].view(np.int32)).cuda()
+    cfg = S.make_cfg(n, k, 4, 8, len(L["sal_cols"]), 0)
+    lay = S.stb_layout_sizes(cfg)
+    img = S.new_device_scratch(lay.image_bytes)
+    S.stb_layout_bind(lay, img.data_ptr())
+    best = {}
+    for per_block in (True, False):
+        ws, each = S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg, per_block)), []
+        for _ in range(12):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            S.stb_pack_device(Wd, xd, bd, lay, per_block, ws)             # (waits for its kernels)
+            each.append(time.perf_counter() - t0)
+        best[per_block] = min(each)
+    host = S.PackedMatrix.pack(W, L["xnorm"], L["sal_bitmap"], 4, 8, 0)
+    got = img.cpu().numpy()
+    for field, off, size in S.PLANE_FIELDS:
+        o, sz = getattr(lay, off), getattr(lay, size)
+        assert (got[o:o + sz] == host.plane(field)).all(), field
+    assert best[False] <= 1.25 * best[True], best
+
+
 TILE_CASES = [c for c in PACK_CASES if _tiled_ok(c[2], c[3])]
 
 
