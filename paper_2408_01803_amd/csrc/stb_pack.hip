@@ -1020,7 +1020,8 @@ __global__ __launch_bounds__(64) void k_select_step(PK a, int pass) {
 // predicates: 0.81 ms), without a branch for a value's region (0.32 ms with them and the chunks unrolled: a wait for LDS a value, two
 // wavefronts a SIMD).  Bound by vector instructions (about 30 a kept weight) beside a pass over the weights (0.18).  28672 x 8192 at 4:8:
 // 0.27 ms, against 0.65 + 0.99 ms with one thread per (row, block) that reads and
-// writes its own 512 and 24 bytes, once here and once for the salient columns.
+// writes its own 512 and 24 bytes, once here and once for the salient columns.  Three workgroups a compute unit, two where all 8 are kept, which
+// takes more registers than three leave (11008 x 4096 8:8: 79 us, 88 with 15 of them in scratch).
 // LDS keeps a wavefront's accesses in order; the compiler has to as well where lanes read what others wrote.
 __device__ inline void wave_order() {
     asm volatile("" : : : "memory");
@@ -1028,7 +1029,7 @@ __device__ inline void wave_order() {
 }
 constexpr int AS_COLS = 32, AS_STRIDE = AS_COLS + 1, AS_SAL = 8;
 template <int N8>                                              // kept weights of 8 columns
-__global__ __launch_bounds__(256, 3) void k_assign(PK a) {
+__global__ __launch_bounds__(256, N8 == 8 ? 2 : 3) void k_assign(PK a) {
     __shared__ float tile[4][64 * AS_STRIDE];
     __shared__ __attribute__((aligned(16))) uint8_t bits[4][8 * 8 * 48];          // per wavefront: 8 rows x 8 blocks x (16 + 32) bytes
     if (given_up(a)) return;               // (res_sign is indexed by the bitmap)

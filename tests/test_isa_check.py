@@ -1,6 +1,7 @@
 """The static check that build() runs on the generated gfx950 code: its logic on small hand-written listings, and
 the package's own device sources (compiled to ISA text here: no GPU is needed)."""
 import os
+import re
 from concurrent.futures import ThreadPoolExecutor
 
 from paper_2408_01803_amd import build as stb_build
@@ -163,3 +164,12 @@ def test_the_device_sources_of_the_package_are_clean(tmp_path):
     with ThreadPoolExecutor(max_workers=len(srcs)) as pool:
         found = list(pool.map(lambda s: isa_check.check_source(s, str(tmp_path), stb_build.HIPCC, [*stb_build.DEVICE_FLAGS, *inc]), srcs))
     assert all(f == [] for f in found), [f[:3] for f in found if f]
+
+
+def test_the_kernels_of_the_packer_keep_their_values_in_registers(tmp_path):
+    """None of them has scratch memory: an occupancy bound that one ratio's assignment kernel does not fit shows here."""
+    text = isa_check.compile_to_isa(os.path.join(stb_build.CSRC, "stb_pack.hip"), str(tmp_path / "pack.s"), stb_build.HIPCC,
+                                    [*stb_build.DEVICE_FLAGS, "-I" + os.path.join(stb_build.ROOT, "include"), "-I" + stb_build.CSRC])
+    sizes = {name: int(size) for name, size in re.findall(r"^\s*\.name:\s*(_Z\S*)\n\s*\.private_segment_fixed_size:\s*(\d+)", text, re.M)}
+    assert any("k_assign" in name for name in sizes)
+    assert {name: size for name, size in sizes.items() if size} == {}
