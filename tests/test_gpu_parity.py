@@ -244,6 +244,36 @@ def test_device_packer_counts_a_row_that_is_taken_again_once(n, k, N, M, values,
 
 
 @pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("values", ["twin columns", "twin columns of one magnitude", "one magnitude", "zeros", "subnormal"])
+@pytest.mark.parametrize("n,k,N,M", [(1, 128, 5, 8), (65, 1152, 1, 4), (300, 1024, 3, 8)])
+def test_device_packer_mask_that_the_bounds_leave_open(n, k, N, M, values, mode, torch_cuda):
+    """Twin columns on both sides of the cut (N is odd) tie by definition and only the sums in the defined order say so: the call starts over after the mask
+    kernel, with maxima, counts and the tertile split's first counts of the first attempt partly made.  Layers of one magnitude start over before
+    it.  The oracle's bytes in both region modes."""
+    rng = np.random.default_rng(n + N)
+    W = rng.standard_normal((n, k)).astype(np.float32)
+    xnorm = np.abs(1 + 0.3 * rng.standard_normal(k)).astype(np.float32)
+    if values == "zeros":
+        W[rng.random((n, k)) < 0.7] = 0.0
+        xnorm[:] = 1.0
+    elif values == "one magnitude":
+        W = np.where(W >= 0, np.float32(0.75), np.float32(-0.75))
+    elif values == "subnormal":
+        W = (np.round(W * 20) * 1.4012984643e-45).astype(np.float32)
+    else:
+        if values != "twin columns":               # (but for one row, which the look at a few weights meets)
+            W[1:] = np.where(W[1:] >= 0, np.float32(0.75), np.float32(-0.75))
+        W[:, 1::2], xnorm[1::2] = -W[:, 0::2], xnorm[0::2]
+    chosen = np.zeros(k, dtype=bool)
+    chosen[3::31] = True
+    bitmap = np.packbits(chosen, bitorder="little").view("<u4")
+    _say(f"[case] mask left open {n}x{k} {N}:{M} {values} mode {mode}")
+    pm = _pack_on_device(torch_cuda, W, xnorm, bitmap, N, M, mode)
+    for name, v in O.pack(W, xnorm, bitmap, N, M, mode).items():
+        assert (pm.plane(name) == np.ascontiguousarray(v).view(np.uint8).ravel()).all(), name
+
+
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("n,k,N,M", [(1, 128, 4, 8), (63, 1152, 8, 8), (64, 256, 3, 8), (65, 1024, 6, 8), (4099, 128, 4, 8), (577, 2944, 4, 4)])
 def test_device_packer_values_on_break_points_and_crowded_blocks(n, k, N, M, mode, torch_cuda):
     """Magnitudes that are the search's own break points, or the fp32 numbers next to them (p1 and p2 lie between the bins), and
@@ -701,6 +731,41 @@ def test_gemv_with_any_number_of_tiles_a_wavefront(tiles, N, M, torch_cuda):
         bound = x.double().abs() @ What.double().abs().t()
         assert bool(((y.double() - ref).abs() <= 2e-3 * bound).all()), (tiles, B)
         assert float((y.double() - ref).norm() / ref.norm()) < 2e-6, (tiles, B)      # (fp32 sums of 384 exact products)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (6, 8)])
+@pytest.mark.parametrize("tiles,B", [(17, 16), (25, 16), (33, 9)])
+def test_gemv_with_several_visits_in_several_phases(tiles, B, N, M, torch_cuda):
+    """Row tiles that no longer fit one phase (12 at 16 rows of x, 24 at 9) with two and three visits a wavefront, the second of which one wavefront has
+    not: the tile buffers run on across phases and visits.  Against float64 on the dequantised weights; an fp32 sum of k exact products is
+    off by less than k 2^-24 of the sum of magnitudes."""
+    torch = torch_cuda
+    n, k = 16 * 256 * (tiles - 1) + 5, 1152
+    g = torch.Generator(device="cuda").manual_seed(tiles)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    xnorm = torch.rand(k, generator=g, device="cuda") + 0.5
+    bits = np.zeros(k, dtype=np.uint8)
+    bits[[2, 77, 130, 290, 1100] + list(range(600, 630))] = 1         # more than 8 and more than 16 in a half block
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 1)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    S.stb_pack_device(W, xnorm, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    x = torch.randn((B, k), generator=g, device="cuda").half()
+    ref = x.double() @ What.double().t()
+    bound = x.double().abs() @ What.double().abs().t()
+    for visits in (2, 3):
+        _say(f"[case] gemv {n}x{k} {N}:{M} B={B}, {visits} visits")
+        y = torch.full((B, n), float("nan"), dtype=torch.float32, device="cuda")
+        with forced(gemv_visits=visits):
+            S.stb_gemv(tl, x, B, y, True, S.new_device_scratch(S.stb_gemv_workspace_bytes(cfg, B), zero=True))
+            torch.cuda.synchronize()
+        assert bool(((y.double() - ref).abs() <= k * 2.0 ** -24 * bound).all()), visits
 
 
 def test_gemv_with_planes_more_than_4_gib_apart(torch_cuda):
