@@ -234,10 +234,12 @@ int stb_pack_obc_hybrid(const float* W, const double* Hc, const float* xnorm, co
                         stb_layout_t* out, int32_t n_threads, void* workspace, int64_t workspace_bytes, void* stream);
 
 /* stb_pack on the GPU (Eq. 1-6, Sec. 3.1, Alg. 2 as in stb_pack): weights, feature norms and the salient bitmap in
- * device memory in, the STB1 planes in device memory out, bit for bit what stb_pack writes for the same inputs.  Every
- * float64 sum is taken in the order stb_pack takes it (a row's columns from left to right, the rows from the top
- * down, one lane per sum); rows, columns and blocks run side by side.  The break-point candidates of Alg. 2 are compared by
- * bounds first, and only those that could be the minimum are evaluated in that order.
+ * device memory in, the STB1 planes in device memory out, bit for bit what stb_pack writes for the same inputs.  Whatever
+ * is stored comes from float64 sums in the order stb_pack takes them (a row's columns from left to right, the rows from the
+ * top down, one lane per sum); rows, columns and blocks run side by side.  Which weights are kept (with si_per_block = 0) and which
+ * break-point candidate of Alg. 2 is best follow from sums in any order with proven error bounds; what the bounds leave open
+ * is decided in the defined order (the call then takes up to two and a half times as long; layers of one magnitude always, of normal
+ * weights one in a hundred or fewer).
  * W: device, n x k row-major fp32, 16-byte aligned.  xnorm: device, k values >= 0.  sal_bitmap: device, k/32 words.
  * out: row-major layout (stb_layout_sizes) bound to device memory; every byte of every plane is written.
  * si_per_block: 0 = Standardized Importance over the whole layer (Eq. 3, as stb_pack); 1 = over each 128-column slice

@@ -911,7 +911,9 @@ extern "C" int stb_tiled_gemv24_plan(int nrt, int nsb, int B, int mode, int max_
     // R * V products for each of the ceil(SPS / 4) wavefronts of a SIMD, times the rounds the grid needs on `cus`
     // compute units (256 for a layer that has the chip to itself; a layer's share of them when several layers run as
     // one launch); adding the column splits up through the workspace costs ~3000 plus ~90 per split and batch row.
-    // Ties go to the fewest splits.
+    // Ties go to the fewest splits.  The constants were fitted to the kernel that expanded pairs of slots and added up every 15 row
+    // tiles (its choices were then within 1.5 % of the best forced shape).  They are estimates on the high side now: a dense product
+    // issues 335 or 434 instructions against 307 of a sparse one, and phases are longer at few rows of x (phase24).
     // LDS of one wavefront: per visit the x rows (B rows and one of zeros, 1040 bytes each) and 16 records; the PHT
     // partial tiles lie on top of the x rows when there is one visit, behind everything otherwise.
     const int xbytes = (B < 16 ? B + 1 : 16) * 1040;
@@ -971,8 +973,9 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
     int blocks = 0, sps_max = 1;
     int64_t lds = 0;
     // every layer gets a share of the 256 compute units in proportion to its work, so that the layers of a launch run
-    // side by side and end together instead of each being cut for the whole chip (work of a (row tile, superblock):
-    // the vector instructions its product issues, as counted on the three kinds of layer)
+    // side by side and end together instead of each being cut for the whole chip.  Work of a (row tile, superblock): the vector
+    // instructions of its product (the loop issues 307, 335 and 434 with one record of salient columns a half block; with a wavefront's
+    // set-up dealt to its 4 to 28 products 317, 341 and 502 to 513 on the 70B-shaped layer)
     int64_t work[GROUP24_MAX], total_work = 0;
     for (int l = 0; l < n_layers; l++) {
         const bool sparse = Ls[l]->cfg.M == 4 && Ls[l]->cfg.N == 2;

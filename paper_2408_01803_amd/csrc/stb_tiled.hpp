@@ -358,8 +358,8 @@ __device__ inline void expand_group(const HalfData<N8>& d, uint32_t TL, uint32_t
 // The kept weights of a half block as codes, four slots a register: byte j of Q[b] = id of slot 4 b + j | its sign bit << 2, which is
 // what v_perm_b32 takes as selectors for eight bytes (four scales, plus and minus).  16 slots at a time: rw = their ids, the half
 // `hi16` of sw their sign bits.  The fields are parted over all four bytes of a word at once and then transposed: 6 instructions for
-// four slots (9 with each pair of slots expanded on its own, of which a tile of 4:8 then took 394 vector instructions instead of 320,
-// one of 6:8 524 instead of 404).
+// four slots, 9 with each pair of slots expanded on its own (vector instructions a product of the decode kernel, set-up included, on
+// the 70B-shaped layer: 4:8 378 -> 341, 6:8 560 -> 502).
 __device__ inline void slot_codes(uint32_t rw, uint32_t sw, bool hi16, uint32_t Q[4]) {
     const uint32_t K3 = 0x03030303u, K4 = 0x04040404u;
     const uint32_t t = perm(sw, sw, hi16 ? 0x0C030C02u : 0x0C010C00u);        // sign bits of slots 0..7 | 8..15 << 16
