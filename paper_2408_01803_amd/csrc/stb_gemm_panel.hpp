@@ -416,24 +416,298 @@ __global__ __launch_bounds__(256, 2) void gemm_panel_kernel(const char* __restri
     }
 }
 
-template <bool SPARSE, bool SPLIT>
+// ---- 2:4 layers, tiles of 256 rows x 256 tokens ------------------------------------------------------------------------
+// A K step of 64 columns costs a sparse product half the matrix instructions of a dense one and the same bytes of X: two workgroups of
+// gemm_panel_kernel bring 68 KB a stage to a compute unit whose matrix instructions take 1024 cycles, and run at the rate of those
+// bytes (pipes 0.50 busy).  One workgroup of 256 x 256 whose A' goes through LDS as well brings 50: four wavefronts, one a SIMD, of 128 x
+// 128 each, three stages of X and A' in LDS, the loads of a stage two stages ahead.  256 accumulator registers a wavefront: the matrix
+// instructions are asm statements that keep them in AGPRs (left to the compiler, the loop holds up to 484 register copies).  A lone
+// wavefront issues everything in its one stream, so loads and LDS reads are dealt out one or two behind a matrix instruction.
+// Same order of additions as gemm_panel_kernel: the same bits.  8192 x 28672 at T = 2048: pipes 0.61 busy, the call 673 -> 577 us; 8192 x
+// 8192 at 2048 175 -> 160, 4096 x 4096 at 4096 99 -> 93.5.  The 32 x 32 x 32 form of the instruction: 583, 161 and 96.  Dense layers gain
+// nothing (8192 x 8192 6:8 at 2048 250 -> 248, 8192 x 8192 4:8 at 8192 798 -> 796, 11008 x 4096 4:8 at 8192 592 -> 616).
+constexpr int SQ_TOK = 256, SQ_X = SQ_TOK * 128, SQ_A = 16384, SQ_STAGE = SQ_X + SQ_A, SQ_BUFS = 3;
+constexpr int SQ_I = SQ_BUFS * SQ_STAGE;                        // index words of two stage pairs, behind the stages
+constexpr int SQ_LDS = SQ_I + 2 * 4096;
+static_assert(2 * (SQ_X + 2 * SQ_A) <= SQ_LDS && 4 * ST_AREA <= SQ_LDS, "two stages of residual columns; the output tiles");
+
+// at most K vector-memory operations still on their way
+template <int K> __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(K) : "memory"); }
+
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef float4_t SquareAcc[8][8];               // 16 x 16 tiles of a wavefront: [row tile][token tile]
+__device__ __forceinline__ void dense_into(float4_t& acc, u32x4 a, u32x4 b) { asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b)); }
+template <int SECOND> __device__ __forceinline__ void sparse_into(float4_t& acc, u32x4 a, u32x8 b, uint32_t x) {
+    if (SECOND) asm volatile("v_smfmac_f32_16x16x64_f16 %0, %1, %2, %3 abid:1" : "+a"(acc) : "v"(a), "v"(b), "v"(x));
+    else asm volatile("v_smfmac_f32_16x16x64_f16 %0, %1, %2, %3" : "+a"(acc) : "v"(a), "v"(b), "v"(x));
+}
+// The compiler does not know that the statements above are matrix instructions: nothing may read their accumulators before this
+// (32 wait states, more than a 16 x 16 instruction takes to write back), and nothing but LDS reads may write their operands right before
+// them (index words are moved at the end of a turn of the loop: the wait states at its start).
+__device__ __forceinline__ void settle(SquareAcc& acc) {
+#pragma unroll
+    for (int r = 0; r < 8; r++)
+        asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[r][0]), "+a"(acc[r][1]), "+a"(acc[r][2]), "+a"(acc[r][3]), "+a"(acc[r][4]), "+a"(acc[r][5]), "+a"(acc[r][6]), "+a"(acc[r][7]));
+}
+
+// load_to_lds at base + OFF in LDS
+template <int OFF> __device__ __forceinline__ void load_to_lds_at(uint32_t lds_base, uint32_t voff, const void* base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(base), "n"(OFF) : "memory", "m0", "scc");
+}
+
+// What a wavefront loads of a stage: 64 of its 256 token rows of 64 columns, and its share of A'.  An LDS row is a token's 128 bytes; its
+// 16-byte piece p sits at p ^ (row / 2 % 8), which spreads the rows that one cycle of a 16-byte LDS read takes over all banks.
+struct SquareLoads {
+    const char* xt;                             // token rows of the workgroup, from the first
+    const char* group;                          // A' of its two row groups
+    int64_t group_bytes;
+    uint32_t lds0;
+    uint32_t xoff[8], aoff[8];
+    int wave, lane;
+    __device__ SquareLoads(const char* rows, uint32_t stride, int T, int t0, const char* group_, int64_t group_bytes_, char* lds, int wave_, int lane_)
+        : xt(rows + (int64_t)t0 * stride), group(group_), group_bytes(group_bytes_),
+          lds0((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds), wave(wave_), lane(lane_) {
+        const uint32_t last = (uint32_t)(T - 1 - t0);
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const uint32_t row = (uint32_t)(64 * wave + 8 * u + (lane >> 3));
+            xoff[u] = __umul24(row < last ? row : last, stride) + ((((uint32_t)lane & 7u) ^ (row >> 1 & 7u)) * 16u);
+            aoff[u] = (uint32_t)(lane * 16 + 1024 * u);
+        }
+    }
+    // row i, piece g of the 16 rows of an operand
+    __device__ uint32_t b_lane() const { return (uint32_t)(wave & 1) * 16384u + (uint32_t)((lane & 15) * 128 + ((lane >> 4) ^ (lane >> 1 & 7)) * 16); }
+    __device__ uint32_t a_lane() const { return SQ_X + (uint32_t)(wave >> 1) * 8192u + (uint32_t)lane * 16u; }
+};
+
+// acc += A' X' over the stages [s0, s1) (an even number) of kept weights.  Stage s: 8 token tiles of 8 matrix instructions; the B operand of a
+// tile is read four tiles ahead.  Behind tile 4 all of the stage's LDS reads are back: the wait and the barrier there say that stage s + 1 is in
+// LDS and that nobody reads stage s any more, so that the loads of stage s + 3 go out in its place and the operands of s + 1 are read.
+__device__ __forceinline__ void square_sparse(SquareAcc& acc, char* lds, const SquareLoads& pq, int s0, int s1) {
+    // the wavefront's share of a stage: 8 loads of X, 4 of A', and (even stages) one of the pair's index words
+    const char* const own = pq.group + (int64_t)(pq.wave >> 1) * pq.group_bytes + (pq.wave & 1) * 4096;
+    const char* const iown = pq.group + (int64_t)(pq.wave >> 1) * pq.group_bytes + 16384 + (pq.wave & 1) * 1024;
+    const uint32_t xdst = pq.lds0 + (uint32_t)pq.wave * 8192u, adst = pq.lds0 + SQ_X + (uint32_t)pq.wave * 4096u, idst = pq.lds0 + SQ_I + (uint32_t)pq.wave * 1024u;
+    auto load = [&](auto which, int s, uint32_t buf) {
+        constexpr int u = decltype(which)::value;
+        const int sc = s < s1 ? s : s1 - 1;
+        if constexpr (u < 8) load_to_lds_at<u * 1024>(xdst + buf, pq.xoff[u], pq.xt + (int64_t)sc * 128);
+        else if constexpr (u < 12) load_to_lds_at<(u - 8) * 1024>(adst + buf, pq.aoff[u - 8], own + (int64_t)(sc >> 1) * PN_PAIR24 + (sc & 1) * 8192);
+        else load_to_lds_at<0>(idst + (uint32_t)((s >> 1) & 1) * 4096u, pq.aoff[0], iown + (int64_t)(sc >> 1) * PN_PAIR24);
+    };
+    const uint32_t alane = pq.a_lane();
+    const uint32_t ilane = SQ_I + (uint32_t)(pq.wave >> 1) * 2048u + (uint32_t)pq.lane * 4u;
+    const uint32_t blane = pq.b_lane();
+    u32x8 b[4];
+    u32x4 a0[8], a1[8];
+    uint32_t x0[8], x1[8];
+    auto b_read = [&](uint32_t buf, int tt) {              // pieces g and 4 + g
+        const char* const base = lds + tt * 2048;
+        const uint4 lo = *reinterpret_cast<const uint4*>(base + (buf + blane)), hi = *reinterpret_cast<const uint4*>(base + (buf + (blane ^ 64u)));
+        b[tt & 3] = u32x8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    };
+    auto a_read = [&](u32x4 (&a)[8], uint32_t buf, int r) { a[r] = *reinterpret_cast<const u32x4*>(lds + (buf + alane) + r * 1024); };
+    auto i_read = [&](uint32_t (&x)[8], int s, int r) {
+        x[r] = *reinterpret_cast<const uint32_t*>(lds + (((uint32_t)(s >> 1) & 1u) * 4096u + ilane) + r * 256);
+    };
+    auto all_loads = [&](auto with_index, int s, uint32_t buf) {
+        load(IntC<0>{}, s, buf); load(IntC<1>{}, s, buf); load(IntC<2>{}, s, buf); load(IntC<3>{}, s, buf);
+        load(IntC<4>{}, s, buf); load(IntC<5>{}, s, buf); load(IntC<6>{}, s, buf); load(IntC<7>{}, s, buf);
+        load(IntC<8>{}, s, buf); load(IntC<9>{}, s, buf); load(IntC<10>{}, s, buf); load(IntC<11>{}, s, buf);
+        if constexpr (decltype(with_index)::value) load(IntC<12>{}, s, buf);
+    };
+    constexpr uint32_t SZ = SQ_STAGE;
+    all_loads(IntC<1>{}, s0, 0);
+    all_loads(IntC<0>{}, s0 + 1, SZ);
+    all_loads(IntC<1>{}, s0 + 2, 2 * SZ);
+    wait_loads<12 + 13>();
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; q++) a_read(a0, 0, q);
+#pragma unroll
+    for (int q = 0; q < 8; q++) i_read(x0, s0, q);
+#pragma unroll
+    for (int tt = 0; tt < 4; tt++) b_read(0, tt);
+
+    uint32_t cur = 0, next = SZ;
+    // stage s on the operands `a` and index words `x`; `an` (and, odd stages, `xn`) takes those of the next
+    auto step = [&](auto odd, u32x4 (&a)[8], u32x4 (&an)[8], uint32_t (&x)[8], uint32_t (&xn)[8], int s) {
+        constexpr int c = decltype(odd)::value;
+        auto one = [&](auto tile, auto row) {
+            constexpr int tt = decltype(tile)::value, r = decltype(row)::value;
+            sparse_into<c>(acc[r][tt], a[r], b[tt & 3], x[r]);
+            if constexpr (tt < 4 && r == 7) b_read(cur, tt + 4);
+            if constexpr (tt == 4 && r == 7) {
+                wait_loads<c ? 12 : 13>();       // (those of stage s + 2)
+                __syncthreads();
+                b_read(next, 0);
+            }
+            if constexpr (tt > 4) {
+                constexpr int slot = (tt - 5) * 4 + r / 2;
+                if constexpr (r % 2 == 0) load(IntC<slot>{}, s + 3, cur);
+                if constexpr (r % 2 == 1 && slot < 8) a_read(an, next, slot);
+                if constexpr (r % 2 == 1 && slot >= 4 && c) i_read(xn, s + 1, slot - 4);
+                if constexpr (slot == 10 && r % 2 == 1 && c) load(IntC<12>{}, s + 3, cur);
+                if constexpr (r == 7) b_read(next, tt - 4);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto eight = [&](auto tile) {
+            one(tile, IntC<0>{}); one(tile, IntC<1>{}); one(tile, IntC<2>{}); one(tile, IntC<3>{});
+            one(tile, IntC<4>{}); one(tile, IntC<5>{}); one(tile, IntC<6>{}); one(tile, IntC<7>{});
+        };
+        eight(IntC<0>{}); eight(IntC<1>{}); eight(IntC<2>{}); eight(IntC<3>{});
+        eight(IntC<4>{}); eight(IntC<5>{}); eight(IntC<6>{}); eight(IntC<7>{});
+        cur = next;
+        next = next == 2 * SZ ? 0 : next + SZ;
+    };
+    for (int s = s0; s < s1; s += 2) {
+        asm volatile("s_nop 1");
+        step(IntC<0>{}, a0, a1, x0, x1, s);
+        step(IntC<1>{}, a1, a0, x0, x1, s + 1);
+#pragma unroll
+        for (int q = 0; q < 8; q++) x0[q] = x1[q];
+    }
+    wait_loads<0>();
+    __syncthreads();
+}
+
+// The same over the stages [d0, d1) of 64 residual columns behind pq's rows (the gathered columns) and abase: two stages in LDS (X, then two chunks
+// of A'), a chunk of 32 columns a step.  In a stage's second step all its LDS reads are issued: wait and barrier as above, behind the first tile.
+__device__ __forceinline__ void square_dense(SquareAcc& acc, char* lds, const SquareLoads& pq, const char* abase, int d0, int d1) {
+    constexpr uint32_t SZ = SQ_X + 2 * SQ_A;
+    // the wavefront's share of a stage: 8 loads of X, 8 of A' (chunk wave & 1 of row group wave >> 1)
+    const char* const own = abase + (int64_t)(pq.wave >> 1) * pq.group_bytes + (pq.wave & 1) * 8192;
+    const uint32_t xdst = pq.lds0 + (uint32_t)pq.wave * 8192u, adst = pq.lds0 + SQ_X + (uint32_t)(pq.wave & 1) * 16384u + (uint32_t)(pq.wave >> 1) * 8192u;
+    auto load = [&](auto which, int s, uint32_t buf) {
+        constexpr int u = decltype(which)::value;
+        const int sc = s < d1 ? s : d1 - 1;
+        if constexpr (u < 8) load_to_lds_at<u * 1024>(xdst + buf, pq.xoff[u], pq.xt + (int64_t)sc * 128);
+        else load_to_lds_at<(u - 8) * 1024>(adst + buf, pq.aoff[u - 8], own + (int64_t)sc * 16384);
+    };
+    const uint32_t alane = pq.a_lane();
+    const uint32_t blane = pq.b_lane();
+    u32x4 b[8], a0[8], a1[8];
+    auto b_read = [&](uint32_t buf, int c, int tt) { b[tt] = *reinterpret_cast<const u32x4*>(lds + (buf + (blane ^ (uint32_t)(64 * c))) + tt * 2048); };
+    auto a_read = [&](u32x4 (&a)[8], uint32_t buf, int c, int r) { a[r] = *reinterpret_cast<const u32x4*>(lds + (buf + alane) + c * 16384 + r * 1024); };
+    auto all_loads = [&](int s, uint32_t buf) {
+        load(IntC<0>{}, s, buf); load(IntC<1>{}, s, buf); load(IntC<2>{}, s, buf); load(IntC<3>{}, s, buf);
+        load(IntC<4>{}, s, buf); load(IntC<5>{}, s, buf); load(IntC<6>{}, s, buf); load(IntC<7>{}, s, buf);
+        load(IntC<8>{}, s, buf); load(IntC<9>{}, s, buf); load(IntC<10>{}, s, buf); load(IntC<11>{}, s, buf);
+        load(IntC<12>{}, s, buf); load(IntC<13>{}, s, buf); load(IntC<14>{}, s, buf); load(IntC<15>{}, s, buf);
+    };
+    all_loads(d0, 0);
+    all_loads(d0 + 1, SZ);
+    wait_loads<16>();
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; q++) a_read(a0, 0, 0, q);
+#pragma unroll
+    for (int q = 0; q < 8; q++) b_read(0, 0, q);
+    uint32_t cur = 0;
+    auto step = [&](auto odd, u32x4 (&a)[8], u32x4 (&an)[8], int s) {
+        constexpr int c = decltype(odd)::value;
+        const uint32_t from = c ? SZ - cur : cur;              // where the next step's operands are
+        auto one = [&](auto tile, auto row) {
+            constexpr int tt = decltype(tile)::value, r = decltype(row)::value;
+            dense_into(acc[r][tt], a[r], b[tt]);
+            if constexpr (c && tt == 0 && r == 7) {
+                wait_loads<0>();
+                __syncthreads();
+            }
+            if constexpr (r == 7) b_read(from, c ^ 1, tt);
+            if constexpr (tt > 0 && r == 0) a_read(an, from, c ^ 1, tt - 1);
+            if constexpr (tt == 7 && r == 1) a_read(an, from, c ^ 1, 7);
+            if constexpr (c && tt > 0 && r % 2 == 1 && r > 1) {
+                constexpr int u = (tt - 1) * 3 + r / 2 - 1;
+                if constexpr (u < 16) load(IntC<u>{}, s + 2, cur);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto eight = [&](auto tile) {
+            one(tile, IntC<0>{}); one(tile, IntC<1>{}); one(tile, IntC<2>{}); one(tile, IntC<3>{});
+            one(tile, IntC<4>{}); one(tile, IntC<5>{}); one(tile, IntC<6>{}); one(tile, IntC<7>{});
+        };
+        eight(IntC<0>{}); eight(IntC<1>{}); eight(IntC<2>{}); eight(IntC<3>{});
+        eight(IntC<4>{}); eight(IntC<5>{}); eight(IntC<6>{}); eight(IntC<7>{});
+        if (c) cur = SZ - cur;
+    };
+    for (int s = d0; s < d1; s++) {
+        step(IntC<0>{}, a0, a1, s);
+        step(IntC<1>{}, a1, a0, s);
+    }
+    wait_loads<0>();
+    __syncthreads();
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 1) void gemm_square_kernel(const char* __restrict__ A, int64_t main_bytes, int64_t group_bytes, int stages,
+                                                             const __half* __restrict__ X, int k, const __half* __restrict__ xsal, int sp, int T, int n,
+                                                             void* __restrict__ Y, int y_fp32, float* __restrict__ part,
+                                                             int pairs_per, int tiles_t, int tiles_r, int total) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int per = (total + 7) / 8, lin = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || lin >= total) return;
+    const int tiles = tiles_t * tiles_r, split = __builtin_amdgcn_readfirstlane(lin / tiles), rem = lin - split * tiles;
+    const int tg = __builtin_amdgcn_readfirstlane(rem / (4 * tiles_r)), width = tiles_t - 4 * tg < 4 ? tiles_t - 4 * tg : 4, idx = rem - tg * 4 * tiles_r;
+    const int row_tile = __builtin_amdgcn_readfirstlane(idx / width), t0 = (4 * tg + idx - row_tile * width) * SQ_TOK;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int s0 = SPLIT ? 2 * pairs_per * split : 0, s1 = SPLIT && s0 + 2 * pairs_per < stages ? s0 + 2 * pairs_per : stages;
+    SquareAcc acc;
+#pragma unroll
+    for (int r = 0; r < 8; r++)
+#pragma unroll
+        for (int tt = 0; tt < 8; tt++) acc[r][tt] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    const char* const group = A + (int64_t)(row_tile * 2) * group_bytes;
+    const int sx = k / 64, e = s1 < sx ? s1 : sx, d0 = s0 > sx ? s0 : sx;
+    if (s0 < e) {
+        const SquareLoads pq(reinterpret_cast<const char*>(X), (uint32_t)k * 2u, T, t0, group, group_bytes, lds, wave, lane);
+        square_sparse(acc, lds, pq, s0, e);
+    }
+    if (d0 < s1) {
+        const SquareLoads pq(reinterpret_cast<const char*>(xsal), (uint32_t)sp * 2u, T, t0, group, group_bytes, lds, wave, lane);
+        square_dense(acc, lds, pq, group + main_bytes, d0 - sx, s1 - sx);
+    }
+    settle(acc);
+    float* const ep = reinterpret_cast<float*>(lds + wave * ST_AREA);
+    if (SPLIT) { Y = part + (int64_t)split * T * n; y_fp32 = 1; }
+#pragma unroll
+    for (int rh = 0; rh < 2; rh++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {                  // 32 tokens x 64 rows at a time; D[row][token]: lane = token i, rows 4 g + v
+#pragma unroll
+            for (int h = 0; h < 2; h++)
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                    *reinterpret_cast<float4_t*>(ep + (16 * h + (lane & 15)) * ST_ES + 16 * r + 4 * (lane >> 4)) = -acc[4 * rh + r][2 * q + h];
+            store_runs(ep, t0 + 128 * (wave & 1) + 32 * q, row_tile * 256 + (wave >> 1) * 128 + rh * 64, Y, y_fp32, T, n, lane);
+        }
+}
+
+enum { PN_DENSE, PN_SPARSE, PN_SQUARE };        // gemm_panel_kernel on either kind of layer, gemm_square_kernel
+template <int KIND, bool SPLIT>
 hipError_t launch_panel_as(hipStream_t st, const char* A, const PanelShape& ps, const __half* X, int k, const __half* xsal, int T, int n,
                            void* Y, int y_fp32, float* part, int groups, int pairs_per) {
     static std::atomic<bool> attr_set{false};              // a failure is not remembered: the next call tries again
-    const auto fn = gemm_panel_kernel<SPARSE, SPLIT>;
+    constexpr int lds = KIND == PN_SQUARE ? SQ_LDS : PN_LDS, tok = KIND == PN_SQUARE ? SQ_TOK : PN_TOK;
+    const auto fn = [] {
+        if constexpr (KIND == PN_SQUARE) return gemm_square_kernel<SPLIT>;
+        else return gemm_panel_kernel<KIND == PN_SPARSE, SPLIT>;
+    }();
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t attr = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, PN_LDS);
+        const hipError_t attr = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (attr != hipSuccess) return attr;
         attr_set.store(true, std::memory_order_release);
     }
-    const int tiles_t = (T + PN_TOK - 1) / PN_TOK, tiles_r = (n + 255) / 256, total = tiles_t * tiles_r * groups;
-    hipLaunchKernelGGL(fn, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), PN_LDS, st, A, ps.main_bytes, ps.group_bytes, ps.kc / 2, X, k, xsal, ps.sp, T, n, Y, y_fp32, part,
+    const int tiles_t = (T + tok - 1) / tok, tiles_r = (n + 255) / 256, total = tiles_t * tiles_r * groups;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), lds, st, A, ps.main_bytes, ps.group_bytes, ps.kc / 2, X, k, xsal, ps.sp, T, n, Y, y_fp32, part,
                        pairs_per, tiles_t, tiles_r, total);
     return hipGetLastError();
 }
 
 struct PanelPlan {
     int groups, pairs_per;                      // K split: groups of pairs_per stage pairs (1 group: none)
+    bool square;                                // tiles of 256 x 256 (gemm_square_kernel)
 };
 
 template <int N8, bool SPARSE>

@@ -897,6 +897,50 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
                     assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
 
 
+@pytest.mark.parametrize("n,k,T,every", [(1104, 4096, 6945, 20), (2151, 3328, 4066, 0), (9754, 5376, 999, 17), (4868, 8064, 838, 20), (3632, 13440, 762, 0)])
+def test_gemm_2of4_in_tiles_of_256_rows_and_tokens(n, k, T, every, torch_cuda):
+    """Shapes whose expanded 2:4 product runs in tiles of 256 x 256 by the library's own choice: rows and tokens past the last full tile, an
+    odd number of 128-column blocks, with and without salient columns (every `every`-th), whole and in 3 or 5 K groups, twice with the
+    same bits.  Against float64 on the dequantised weights (an fp32 sum of k exact products is off by less than k 2^-24 of the sum of
+    magnitudes), and the bits of the other tiles, which add in the same order."""
+    torch = torch_cuda
+    _say(f"[case] 2:4 gemm in square tiles {n}x{k} T={T} every {every}")
+    g = torch.Generator(device="cuda").manual_seed(n + T)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    bits = np.zeros(k, dtype=np.uint8)
+    if every:
+        bits[::every] = 1
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, 2, 4, int(bits.sum()), 1)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    S.stb_pack_device(W, torch.rand(k, generator=g, device="cuda") + 0.5, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    x = torch.randn((T, k), generator=g, device="cuda").half()
+    ref = x.double() @ What.double().t()
+    bound = x.double().abs() @ What.double().abs().t()
+    for fp32 in (True, False):
+        form = S.stb_gemm_form(tl, T, fp32)
+        assert form.kernel == S.STB_GEMM_EXPANDED
+        outs = []
+        for asked in (0, 0) + ((S.GEMM_WHOLE,) if form.k_groups == 1 else ()):
+            with forced(gemm_kernel=asked):
+                ws = S.new_device_scratch(form.workspace_bytes)
+                ws.fill_(0xFF)
+                y = torch.full((T, n), float("nan"), dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+                S.stb_gemm(tl, x, T, y, fp32, ws)
+                torch.cuda.synchronize()
+                outs.append(y)
+        slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+        assert bool(((outs[0].double() - ref).abs() <= slack).all()), fp32
+        for y in outs[1:]:
+            assert bool((y.view(torch.int32 if fp32 else torch.int16) == outs[0].view(torch.int32 if fp32 else torch.int16)).all()), fp32
+
+
 @pytest.mark.parametrize("n,k,N,M,T", [(13824, 5120, 6, 8, 64), (13184, 2560, 4, 8, 64), (13184, 2560, 2, 4, 64), (13184, 2560, 6, 8, 24),
                                        (10880, 3072, 4, 8, 69), (5632, 1024, 2, 4, 200), (6608, 1408, 4, 8, 770), (1536, 1024, 6, 8, 770)])
 def test_an_fp32_sum_runs_over_no_more_columns_than_fill_the_chip(n, k, N, M, T, torch_cuda):
