@@ -645,12 +645,18 @@ __device__ inline void candidate(int t, double mx, double& q1, double& q2, bool&
 // 11008 x 4096 4:8 of one magnitude 7.6 ms, now 1.0; of two 7.7 and 1.8; 28672 x 8192 of 15 9.3 and 3.2.)  Where several are left
 // k_exact_errors / k_exact_pick evaluate D_t for those alone, in the defined order.
 constexpr int SC_NV = 70;                  // candidates that are not skipped when the block has a non-zero weight: 2 c_t <= 0.9
-constexpr int SC_ROWS = 64;                // rows whose histograms are in LDS at a time: a lane a row
+constexpr int SC_ROWS = 64;                // rows of a workgroup whose histograms are in LDS at a time, 8 a wavefront
 constexpr int SC_WAVES = 8;
 constexpr int SC_STEPS = 8;                // ... and how often at most: rows per workgroup = SC_ROWS * steps
-constexpr int SC_SEG = 18;                 // bins per lane of the suffix sums (SC_WAVES lanes a row)
-constexpr int SC_BINS = SC_WAVES * SC_SEG + 1;    // bin b: the value exceeds b of the 2 SC_NV break points (141 bins; the row stride is odd)
+constexpr int SC_SEG = 19;                 // bins per lane of the suffix sums (8 lanes a row; odd: their 8 x 8 first bins lie in all banks)
+constexpr int SC_BINS = 8 * SC_SEG;        // bin b: the value exceeds b of the 2 SC_NV break points (141 bins)
 constexpr int SC_MASKW = 8;                // words of a block's candidate mask (CAND bits)
+
+// LDS keeps a wavefront's accesses in order; the compiler has to as well where lanes read what others wrote.
+__device__ inline void wave_order() {
+    asm volatile("" : : : "memory");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // The largest fp32 not above p >= 0: for an fp32 value a, a > p iff a > that.
 __device__ inline float round_down_f32(double p) {
@@ -681,23 +687,22 @@ __device__ inline int search_bin(float a, float gs, float go, const float* tau) 
     return g - (a <= tau[g]);              // (tau[0] is below everything)
 }
 
-// A workgroup takes SC_ROWS * steps rows of one block.  Per step: all threads bin 64 rows x 128 columns (magnitudes as
-// 36-bit fractions of the block's largest, the count in bits 44 up: one 64-bit LDS atomic a value), then a wavefront takes 18
-// bins of the 64 rows, a lane a row (the row stride is odd: no two lanes share a bank), for the suffix sums, and every eighth
-// candidate, whose G_t over its lane's rows it keeps in a register.  The next step's weights load meanwhile.
+// A workgroup takes SC_ROWS * steps rows of one block, a wavefront 8 of every 64: it bins them (magnitudes as 36-bit fractions of the block's
+// largest, the count in bits 44 up: one 64-bit LDS atomic a value) into histograms of its own, [bin][row], takes 19 bins of a row a lane for
+// the suffix sums, and every eighth candidate of a row a lane, whose G_t it keeps in a register.  Nothing in the loop waits for another
+// wavefront, so that the vector instructions of some run beside the LDS accesses of others.  The next step's weights load meanwhile.
 // Error bound, with K = count * mx^2 >= sum a^2 and u = 2^-53: the fractions move G_t by at most 2^-36 K, float64
 // rounding of G_t and of D_t (sequential sums over n rows of sums over 128 values) by less than (4 n + 200) u K.
 // A load instruction covers 8 rows x 128 bytes, so that few lanes of one atomic instruction share a row's bin (with 2 rows
-// x 512 bytes and a histogram for either break point: 1281 us).  Bound by LDS accesses and vector instructions.
-// 28672 x 8192 at 4:8: 0.44 ms (0.82 with 32 rows a step, suffix sums by 128 of 320 threads and a lane a candidate, which meet in
-// banks; 1.14 with loops around every bin search), against 21.7 ms for evaluating every candidate in the defined order.
+// x 512 bytes and a histogram for either break point: 1281 us).  Bound by vector instructions and LDS accesses.
+// 28672 x 8192 at 4:8: 0.41 ms; 0.44 with the histograms of 64 rows shared by eight wavefronts, five barriers a step (each pipe busy for about
+// half of the time); 0.82 with 32 rows a step, suffix sums by 128 of 320 threads and a lane a candidate, which meet in
+// banks; 1.14 with loops around every bin search; 21.7 for evaluating every candidate in the defined order.
 __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int steps, double* __restrict__ gain, unsigned long long* __restrict__ above) {
-    __shared__ __attribute__((aligned(16))) unsigned long long hist[SC_ROWS * SC_BINS];
-    __shared__ unsigned long long seg[SC_WAVES][SC_ROWS];
+    __shared__ __attribute__((aligned(16))) unsigned long long hists[SC_WAVES][SC_BINS * 8];   // a wavefront's: [bin][row]
     __shared__ double inv[256];            // 1 / count (a count is at most 128; 8 bits are read)
     __shared__ float tau[2 * SC_NV + 2];
-    constexpr int THREADS = 64 * SC_WAVES, PER = (SC_NV + SC_WAVES - 1) / SC_WAVES;
-    static_assert(SC_ROWS * SC_BINS % 2 == 0, "cleared 16 bytes at a time");
+    constexpr int PER = (SC_NV + 7) / 8;
     if (given_up(a)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
@@ -734,15 +739,28 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     const bool tiny = !(mxf > 1e-30f);     // (or not a number: the loops end all the same)
     const float gs = (float)(1.0 / (step * mx)), go = (float)(1.0 + 0.0009765625 - 0.1 / step);
     double g_t[PER];
-    uint32_t n_t[PER];                     // values above p1(t) and above p2(t)
+    uint32_t n_t[PER];                     // 8 x the values above p1(t) and above p2(t)
 #pragma unroll
     for (int j = 0; j < PER; j++) { g_t[j] = 0.0; n_t[j] = 0; }
-    unsigned long long* const row = hist + lane * SC_BINS;
+    unsigned long long* const hist = hists[wave];
+    unsigned long long* const bins = hist + (lane >> 3);       // of the row whose weights the lane holds
+    // the row and the part of its bins and candidates that the lane takes (8 rows next to each other: no two lanes share a bank)
+    const int part = lane >> 3;
+    unsigned long long* const row = hist + (lane & 7);
+    int at[PER];                           // where the suffix sums of candidate part + 8 j are: p1(t) below, p2(t) in bits 16 up
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const int t = part + 8 * j < SC_NV ? part + 8 * j : SC_NV - 1;
+        at[j] = (rank_p1(t) + 1) * 8 | (rank_p2(t) + 1) * 8 << 16;
+    }
+    __syncthreads();
     for (int st = 0; st < steps; st++) {
         const int i0 = first + st * SC_ROWS;
-        if (i0 >= a.n) break;                                  // uniform
-        for (int e = tid; e < SC_ROWS * SC_BINS / 2; e += THREADS) reinterpret_cast<uint4*>(hist)[e] = make_uint4(0u, 0u, 0u, 0u);
-        __syncthreads();
+        if (i0 + 8 * wave >= a.n) break;                       // uniform
+#pragma unroll
+        for (int e = 0; e < SC_BINS * 4; e += 64)
+            if (e + 64 <= SC_BINS * 4 || lane < SC_BINS * 4 - e) reinterpret_cast<uint4*>(hist)[e + lane] = make_uint4(0u, 0u, 0u, 0u);
+        wave_order();
         const bool live = i0 + r0 < a.n;
         auto count = [&](auto any_size) {
 #pragma unroll
@@ -759,54 +777,56 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
                 }
 #pragma unroll
                 for (int u = 0; u < 4; u++)
-                    if ((keep >> u) & 1u) atomicAdd(&hist[r0 * SC_BINS + b[u]], fx[u]);
+                    if ((keep >> u) & 1u) atomicAdd(&bins[b[u] * 8], fx[u]);
             }
         };
         if (tiny) count(std::true_type{});
         else count(std::false_type{});
         if (st + 1 < steps) load(i0 + SC_ROWS + r0);
-        __syncthreads();
+        wave_order();
         {
             unsigned long long h[SC_SEG], run = 0;
 #pragma unroll
-            for (int b = 0; b < SC_SEG; b++) { h[b] = row[wave * SC_SEG + b]; run += h[b]; }
-            seg[wave][lane] = run;
-            __syncthreads();
-            run = 0;
+            for (int b = 0; b < SC_SEG; b++) { h[b] = row[(part * SC_SEG + b) * 8]; run += h[b]; }
+            // the sums of the parts behind the lane's
+            unsigned long long all = run;
 #pragma unroll
-            for (int w = 1; w < SC_WAVES; w++)
-                if (w > wave) run += seg[w][lane];
+            for (int d = 8; d < 64; d <<= 1) {
+                const unsigned long long next = __shfl_down(all, d);
+                if (lane + d < 64) all += next;
+            }
+            run = all - run;
 #pragma unroll
-            for (int b = SC_SEG - 1; b >= 0; b--) { run += h[b]; row[wave * SC_SEG + b] = run; }
+            for (int b = SC_SEG - 1; b >= 0; b--) { run += h[b]; row[(part * SC_SEG + b) * 8] = run; }
         }
-        __syncthreads();
-        auto sum_of = [](unsigned long long s) {               // the low 44 bits as a double
+        wave_order();
+        // the low 44 bits as a double (whole numbers: their differences are exact) and 8 x the count
+        auto sum_of = [](unsigned long long s) {
             return __longlong_as_double((long long)((s & 0xFFFFFFFFFFFull) | 0x4330000000000000ull)) - 4503599627370496.0;
         };
-        auto inv_of = [&](unsigned long long s) { return inv[(s >> 44) & 255]; };
+        auto count_of = [](unsigned long long s) { return ((uint32_t)(s >> 32) >> 9) & (255u << 3); };
+        auto inv_of = [&](uint32_t c8) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(inv) + c8); };
         const unsigned long long all = row[0];
+        const double all_sum = sum_of(all);
+        const uint32_t all_n = count_of(all);
 #pragma unroll
-        for (int j = 0; j < PER; j++) {
-            const int t = wave + SC_WAVES * j;
-            if (t < SC_NV) {                                   // uniform
-                const unsigned long long above1 = row[rank_p1(t) + 1], above2 = row[rank_p2(t) + 1];
-                const unsigned long long mid = above1 - above2, low = all - above1;
-                n_t[j] += (uint32_t)(above1 >> 44) + (uint32_t)(above2 >> 44);
-                const double s0 = sum_of(low), s1 = sum_of(mid), s2 = sum_of(above2);
-                g_t[j] += s0 * s0 * inv_of(low) + s1 * s1 * inv_of(mid) + s2 * s2 * inv_of(above2);
-            }
+        for (int j = 0; j < PER; j++) {                        // (lanes past the last candidate take that one once more)
+            const unsigned long long above1 = row[at[j] & 0xFFFF], above2 = row[at[j] >> 16];
+            const double s1 = sum_of(above1), s2 = sum_of(above2), low = all_sum - s1, mid = s1 - s2;
+            const uint32_t n1 = count_of(above1), n2 = count_of(above2);
+            n_t[j] += n1 + n2;
+            g_t[j] = __builtin_fma(s2 * s2, inv_of(n2), __builtin_fma(mid * mid, inv_of(n1 - n2), __builtin_fma(low * low, inv_of(all_n - n1), g_t[j])));
         }
-        __syncthreads();
+        wave_order();
     }
 #pragma unroll
     for (int j = 0; j < PER; j++) {
-        const int t = wave + SC_WAVES * j;
-        if (t >= SC_NV) break;                                 // uniform
+        const int t = part + 8 * j;
         double g = g_t[j];
-        uint32_t cnt = n_t[j];
+        uint32_t cnt = n_t[j] >> 3;
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) { g += __shfl_xor(g, d); cnt += __shfl_xor(cnt, d); }
-        if (lane == 0) {                                       // in units of (mx / 2^36)^2
+        for (int d = 4; d > 0; d >>= 1) { g += __shfl_xor(g, d); cnt += __shfl_xor(cnt, d); }
+        if ((lane & 7) == 0 && t < SC_NV) {                    // in units of (mx / 2^36)^2
             unsafeAtomicAdd(gain + (size_t)q * SC_NV + t, g);
             atomicAdd(above + (size_t)q * SC_NV + t, (unsigned long long)cnt);
         }
@@ -1023,11 +1043,6 @@ __global__ __launch_bounds__(64) void k_select_step(PK a, int pass) {
 // 0.27 ms, against 0.65 + 0.99 ms with one thread per (row, block) that reads and
 // writes its own 512 and 24 bytes, once here and once for the salient columns.  Three workgroups a compute unit, two where all 8 are kept, which
 // takes more registers than three leave (11008 x 4096 8:8: 79 us, 88 with 15 of them in scratch).
-// LDS keeps a wavefront's accesses in order; the compiler has to as well where lanes read what others wrote.
-__device__ inline void wave_order() {
-    asm volatile("" : : : "memory");
-    __builtin_amdgcn_wave_barrier();
-}
 constexpr int AS_COLS = 32, AS_STRIDE = AS_COLS + 1, AS_SAL = 8;
 template <int N8>                                              // kept weights of 8 columns
 __global__ __launch_bounds__(256, N8 == 8 ? 2 : 3) void k_assign(PK a) {
