@@ -591,10 +591,26 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
     const int64_t n16 = (int64_t)nrt * 16;
     const uint32_t b_magic = B > 1 ? (uint32_t)((0x100000000ull + (uint32_t)B - 1) / (uint32_t)B) : 0u;
     auto div_b = [&](int v) { return B > 1 ? (int)__umulhi((uint32_t)v, b_magic) : v; };     // v / B, v < 2^27
-    auto store_y = [&](int row, int b, float s) {
-        if (b < B && row < n) {
-            if (y_fp32) global_at<float>(y)[(int64_t)b * n + row] = -s;
-            else global_at<__half>(y)[(int64_t)b * n + row] = __float2half(-s);
+    auto store_y = [&](int row, int b, float4_t s) {             // rows row .. row + 3
+        s = -s;
+        const int64_t at = (int64_t)b * n + row;
+        uint32_t odd = (uint32_t)(n & 3) | ((uint32_t)y & (y_fp32 ? 15u : 7u));
+        asm volatile("" : "+s"(odd));                        // (see wa below)
+        if (odd == 0) {                                      // the four lie in one aligned piece
+            if (row < n) {
+                if (y_fp32) *global_at<float4_t>(y + 4 * at) = s;
+                else {
+                    const __half2 lo = __floats2half2_rn(s[0], s[1]), hi = __floats2half2_rn(s[2], s[3]);
+                    *global_at<uint2_t>(y + 2 * at) = uint2_t{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (row + e < n) {
+                    if (y_fp32) global_at<float>(y)[at + e] = s[e];
+                    else global_at<__half>(y)[at + e] = __float2half(s[e]);
+                }
         }
     };
 
@@ -669,22 +685,17 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
             }
         }
     };
-    // partial products in LDS: [slot][row of the tile as 4 v + g][row of x]
+    // partial products in LDS: [slot][g][row of x][rows 4 g .. 4 g + 3 of the tile], 16 bytes a lane as the matrix instruction leaves them.  (Where B is
+    // a multiple of 4 the rows of x of a group are exchanged, so that the four groups of one row of x do not share banks.)
+    auto swapped = [&](int b, int group) { return (B & 3) == 0 ? b ^ group : b; };
+    float4_t* const own = reinterpret_cast<float4_t*>(part) + g * B + swapped(i, g);
     auto store_partial = [&](int slot) {
-        float* dst = part + (slot * 16 + g) * B + i;
-        if (i < B) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) dst[4 * v * B] = acc[v];
-        }
+        if (i < B) own[slot * 4 * B] = acc;
         acc = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
 
     auto add_partial = [&](int slot) {
-        float* dst = part + (slot * 16 + g) * B + i;
-        if (i < B) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) dst[4 * v * B] += acc[v];
-        }
+        if (i < B) own[slot * 4 * B] += acc;
         acc = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
 
@@ -773,50 +784,56 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
                 }
         }
         __syncthreads();
-        // outputs of this phase: (slot, b, row in tile), consecutive threads on consecutive rows
-        const int total = (ph1 > ph0 ? ph1 - ph0 : 0) * B * 16;
+        // outputs of this phase, four rows a thread: (slot, b, quad of rows), added up over the wavefronts in their order
+        const int total = (ph1 > ph0 ? ph1 - ph0 : 0) * B * 4;
         float* const ws_part = S > 1 ? scratch_of(layer).part : nullptr;
         for (int o = threadIdx.x; o < total; o += nthr) {
-            const int r16 = o & 15, j = div_b(o >> 4), b = (o >> 4) - j * B;
-            const char* src = lds_base + PART_OFF + ((j * 16 + 4 * (r16 & 3) + (r16 >> 2)) * B + b) * 4;
-            float t[8];
+            const int quad = o & 3, j = div_b(o >> 2), b = (o >> 2) - j * B;
+            const char* src = lds_base + PART_OFF + ((j * 4 + quad) * B + swapped(b, quad)) * 16;
+            int wa = Wa;
+            asm volatile("" : "+s"(wa));               // (eight conditions on it kept in scalar registers over the loops would spill others)
+            float4_t t[8];                             // (past the last wavefront: its sums once more, not added)
 #pragma unroll
-            for (int w = 0; w < 8; w++) t[w] = w < Wa ? *reinterpret_cast<const float*>(src + (int64_t)w * WREG) : 0.0f;   // fixed order of adds
-            float s = 0.0f;
+            for (int w = 0; w < 8; w++) t[w] = *reinterpret_cast<const float4_t*>(src + (w < wa ? w : wa - 1) * WREG);
+            float4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int w = 0; w < 8; w++) s += t[w];
-            const int row = (ph0 + j) * 16 + r16;
+            for (int w = 0; w < 8; w++)
+                if (w < wa) s += t[w];
+            const int row = (ph0 + j) * 16 + 4 * quad;
             if (S == 1) store_y(row, b, s);
-            else __hip_atomic_store(ws_part + ((int64_t)ks * 16 + b) * n16 + row, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(ws_part + ((int64_t)ks * 16 + b) * n16 + row), "v"(s) : "memory");
         }
         if (ph + PHT < R) __syncthreads();           // the next phase overwrites the partial products
     }
     if (S == 1) return;
     const Scratch24 scratch = scratch_of(layer);
-    float* const ws_part = scratch.part;
-    uint32_t* const ws_count = scratch.count;
 
     // ---- several column splits: the partial sums are in the workspace [split][16][n16]; take a ticket.  They are
-    //      written and read with agent-scope accesses, so no cache write-back or invalidate is needed: the stores
+    //      written and read with agent-scope accesses (sc1), so no cache write-back or invalidate is needed: the stores
     //      have completed (vmcnt = 0, then the barrier) before thread 0 takes the ticket, and the last arrival
-    //      issues its loads after it has seen the ticket. ----
+    //      issues its loads after it has seen the ticket.  16 bytes an access: a workgroup's sums take one round of its threads where
+    //      4 took several, each of which waits for memory. ----
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) ticket = atomicInc(ws_count + gr, (uint32_t)(S - 1));    // wraps to 0 after S arrivals
+    if (threadIdx.x == 0) ticket = atomicInc(scratch.count + gr, (uint32_t)(S - 1));    // wraps to 0 after S arrivals
     __syncthreads();
     if (ticket != (uint32_t)(S - 1)) return;
-    const int total = (r1 - r0) * 16 * B;
+    const int total = (r1 - r0) * 4 * B;
     for (int o = threadIdx.x; o < total; o += nthr) {
-        const int r16 = o & 15, tb = div_b(o >> 4), b = (o >> 4) - tb * B;
-        const int row = (r0 + tb) * 16 + r16;
-        float s = 0.0f;
+        const int quad = o & 3, tb = div_b(o >> 2), b = (o >> 2) - tb * B;
+        const int row = (r0 + tb) * 16 + 4 * quad;
+        const float* const sums = scratch.part + (int64_t)b * n16 + row;
+        float4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int c0 = 0; c0 < S; c0 += 4) {
-            float t[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++)
-                t[u] = c0 + u < S ? __hip_atomic_load(ws_part + ((int64_t)(c0 + u) * 16 + b) * n16 + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 4; u++) s += t[u];
+            auto at = [&](int c) { return sums + (int64_t)(c < S ? c : S - 1) * 16 * n16; };
+            float4_t v0, v1, v2, v3;
+            asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                         "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                         : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3) : "v"(at(c0)), "v"(at(c0 + 1)), "v"(at(c0 + 2)), "v"(at(c0 + 3)) : "memory");
+            s += v0;
+            if (c0 + 1 < S) s += v1;
+            if (c0 + 2 < S) s += v2;
+            if (c0 + 3 < S) s += v3;
         }
         store_y(row, b, s);
     }
