@@ -733,6 +733,43 @@ def test_gemv_with_any_number_of_tiles_a_wavefront(tiles, N, M, torch_cuda):
         assert float((y.double() - ref).norm() / ref.norm()) < 2e-6, (tiles, B)      # (fp32 sums of 384 exact products)
 
 
+@pytest.mark.parametrize("n,k,N,M", [(12289, 640, 4, 8), (12292, 2048, 6, 8), (20480, 1024, 2, 4), (24577, 1536, 2, 4), (12304, 1536, 5, 8), (4100, 7168, 4, 8)])
+def test_gemv_with_few_superblocks_and_outputs_of_any_alignment(n, k, N, M, torch_cuda):
+    """Layers of 2 to 4 superblocks and rows enough for several workgroups a compute unit (their LDS fits two to four times, by the
+    rows of x), and one with column splits: rows past the last tile of 16, outputs whose four rows lie in one aligned piece and
+    outputs 4 bytes off it.  Against float64 on the dequantised weights: an fp32 sum of k exact products is off by less than
+    k 2^-24 of the sum of magnitudes, an fp16 output by half a last place more.  Nothing outside the output is written."""
+    torch = torch_cuda
+    _say(f"[case] gemv {n}x{k} {N}:{M}, few superblocks")
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    bits = np.zeros(k, dtype=np.uint8)
+    bits[::23] = 1
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 1)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    S.stb_pack_device(W, torch.rand(k, generator=g, device="cuda") + 0.5, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    for B in (1, 3, 4, 16):
+        x = torch.randn((B, k), generator=g, device="cuda").half()
+        ref = x.double() @ What.double().t()
+        bound = x.double().abs() @ What.double().abs().t()
+        for fp32 in (True, False):
+            for off in (0, 1 if fp32 else 2):                     # 4 bytes
+                buf = torch.full((B * n + 16,), 7.0, dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+                S.stb_gemv(tl, x, B, buf[off:off + B * n], fp32, S.new_device_scratch(S.stb_gemv_workspace_bytes(cfg, B), zero=True))
+                torch.cuda.synchronize()
+                y = buf[off:off + B * n].view(B, n)
+                slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+                assert bool(((y.double() - ref).abs() <= slack).all()), (B, fp32, off)
+                assert bool((buf[:off] == 7.0).all()) and bool((buf[off + B * n:] == 7.0).all()), (B, fp32, off)
+
+
 @pytest.mark.parametrize("N,M", [(2, 4), (4, 8), (6, 8)])
 @pytest.mark.parametrize("tiles,B", [(17, 16), (25, 16), (33, 9)])
 def test_gemv_with_several_visits_in_several_phases(tiles, B, N, M, torch_cuda):
