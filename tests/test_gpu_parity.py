@@ -978,6 +978,47 @@ def test_gemm_2of4_in_tiles_of_256_rows_and_tokens(n, k, T, every, torch_cuda):
             assert bool((y.view(torch.int32 if fp32 else torch.int16) == outs[0].view(torch.int32 if fp32 else torch.int16)).all()), fp32
 
 
+@pytest.mark.parametrize("n,k,N,M,T", [(1030, 1536, 4, 8, 65), (1001, 1152, 5, 8, 127), (1356, 3328, 4, 8, 331), (2049, 5120, 6, 8, 129), (1210, 1536, 3, 8, 768), (1024, 8192, 6, 8, 100)])
+def test_gemm_of_small_dense_layers_in_small_workgroups(n, k, N, M, T, torch_cuda):
+    """Small layers at more than 64 tokens, which run in workgroups of 64 tokens: tokens and rows past the last full tile, up to twelve token
+    tiles, K groups.  Against float64 on the dequantised weights: an fp32 sum of k exact products is off by less than k 2^-24 of the
+    sum of magnitudes, an fp16 output by half a last place more; and the bits do not change from call to call."""
+    torch = torch_cuda
+    _say(f"[case] gemm in small workgroups {n}x{k} {N}:{M} T={T}")
+    g = torch.Generator(device="cuda").manual_seed(n + T)
+    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
+    bits = np.zeros(k, dtype=np.uint8)
+    bits[::19] = 1
+    bits[130:170] = 1
+    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
+    cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 1)
+    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
+    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
+    S.stb_layout_bind(rm, img.data_ptr())
+    S.stb_layout_bind(tl, timg.data_ptr())
+    S.stb_pack_device(W, torch.rand(k, generator=g, device="cuda") + 0.5, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
+    S.stb_tile_device(rm, tl)
+    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
+    S.stb_dequant(rm, What)
+    x = torch.randn((T, k), generator=g, device="cuda").half()
+    ref = x.double() @ What.double().t()
+    bound = x.double().abs() @ What.double().abs().t()
+    for fp32 in (True, False):
+        outs = []
+        for _ in range(2):
+            ws = S.new_device_scratch(S.stb_gemm_workspace_bytes(tl, T))
+            ws.fill_(0xFF)
+            buf = torch.full((T * n + 16,), 7.0, dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+            S.stb_gemm(tl, x, T, buf[:T * n], fp32, ws)
+            torch.cuda.synchronize()
+            assert bool((buf[T * n:] == 7.0).all())
+            outs.append(buf)
+        y = outs[0][:T * n].view(T, n)
+        slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+        assert bool(((y.double() - ref).abs() <= slack).all()), fp32
+        assert bool((outs[0] == outs[1]).all())
+
+
 @pytest.mark.parametrize("n,k,N,M,T", [(13824, 5120, 6, 8, 64), (13184, 2560, 4, 8, 64), (13184, 2560, 2, 4, 64), (13184, 2560, 6, 8, 24),
                                        (10880, 3072, 4, 8, 69), (5632, 1024, 2, 4, 200), (6608, 1408, 4, 8, 770), (1536, 1024, 6, 8, 770)])
 def test_an_fp32_sum_runs_over_no_more_columns_than_fill_the_chip(n, k, N, M, T, torch_cuda):
