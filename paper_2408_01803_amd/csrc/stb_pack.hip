@@ -695,7 +695,7 @@ __device__ inline int search_bin(float a, float gs, float go, const float* tau) 
 // rounding of G_t and of D_t (sequential sums over n rows of sums over 128 values) by less than (4 n + 200) u K.
 // A load instruction covers 8 rows x 128 bytes, so that few lanes of one atomic instruction share a row's bin (with 2 rows
 // x 512 bytes and a histogram for either break point: 1281 us).  Bound by vector instructions and LDS accesses.
-// 28672 x 8192 at 4:8: 0.41 ms; 0.44 with the histograms of 64 rows shared by eight wavefronts, five barriers a step (each pipe busy for about
+// 28672 x 8192 at 4:8: 0.40 ms; 0.44 with the histograms of 64 rows shared by eight wavefronts, five barriers a step (each pipe busy for about
 // half of the time); 0.82 with 32 rows a step, suffix sums by 128 of 320 threads and a lane a candidate, which meet in
 // banks; 1.14 with loops around every bin search; 21.7 for evaluating every candidate in the defined order.
 __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int steps, double* __restrict__ gain, unsigned long long* __restrict__ above) {
@@ -703,6 +703,7 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     __shared__ double inv[256];            // 1 / count (a count is at most 128; 8 bits are read)
     __shared__ float tau[2 * SC_NV + 2];
     constexpr int PER = (SC_NV + 7) / 8;
+    __shared__ uint32_t where[8 * PER];    // where a candidate's suffix sums are: p1(t) below, p2(t) in bits 16 up (9 registers a lane otherwise)
     if (given_up(a)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = (int)(blockIdx.x % (unsigned)a.nb), chunk = (int)(blockIdx.x / (unsigned)a.nb);
@@ -729,6 +730,10 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
         tau[rank_p1(tid) + 1] = round_down_f32(p1);
         tau[rank_p2(tid) + 1] = round_down_f32(p2);
     }
+    if (tid < 8 * PER) {
+        const int t = tid < SC_NV ? tid : SC_NV - 1;
+        where[tid] = (uint32_t)((rank_p1(t) + 1) * 8 | (rank_p2(t) + 1) * 8 << 16);
+    }
     if (tid == 0) { tau[0] = -1.0f; tau[2 * SC_NV + 1] = __builtin_inff(); }
     if (tid < 256) inv[tid] = tid > 0 ? 1.0 / (double)tid : 0.0;
     uint32_t sal[4];
@@ -747,12 +752,6 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     // the row and the part of its bins and candidates that the lane takes (8 rows next to each other: no two lanes share a bank)
     const int part = lane >> 3;
     unsigned long long* const row = hist + (lane & 7);
-    int at[PER];                           // where the suffix sums of candidate part + 8 j are: p1(t) below, p2(t) in bits 16 up
-#pragma unroll
-    for (int j = 0; j < PER; j++) {
-        const int t = part + 8 * j < SC_NV ? part + 8 * j : SC_NV - 1;
-        at[j] = (rank_p1(t) + 1) * 8 | (rank_p2(t) + 1) * 8 << 16;
-    }
     __syncthreads();
     for (int st = 0; st < steps; st++) {
         const int i0 = first + st * SC_ROWS;
@@ -811,7 +810,8 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
         const uint32_t all_n = count_of(all);
 #pragma unroll
         for (int j = 0; j < PER; j++) {                        // (lanes past the last candidate take that one once more)
-            const unsigned long long above1 = row[at[j] & 0xFFFF], above2 = row[at[j] >> 16];
+            const uint32_t at = where[part + 8 * j];
+            const unsigned long long above1 = row[at & 0xFFFFu], above2 = row[at >> 16];
             const double s1 = sum_of(above1), s2 = sum_of(above2), low = all_sum - s1, mid = s1 - s2;
             const uint32_t n1 = count_of(above1), n2 = count_of(above2);
             n_t[j] += n1 + n2;
