@@ -6,6 +6,7 @@
 //                         in which a wavefront of the product reads them, with the residual term of the salient columns
 //                         (Eq. 4) as further columns of A'; and those columns of X, gathered, as further columns of X
 //   gemm_panel_kernel     Y = X' A'^T over k + n_salient_pad columns: nothing but loads, LDS reads and matrix instructions
+//   gemm_square_kernel    the same for 2:4 layers in larger tiles, where its estimated time is less (panel_plan)
 // A'  [row group of 128][chunk of 32 columns][row tile][lane = 16 g + i][8]: row i of the tile, columns 8 g .. of the chunk
 //     2:4 layers: per 128 columns [stage of 64 columns][row tile][lane = 16 g + i][8 kept weights of columns 16 g ..], twice,
 //     then [row tile][lane] index words (16 bits a stage); the residual columns follow in the form above
@@ -179,7 +180,7 @@ template <int K> __device__ inline void wait_a(ASet& a) {
 // 8192 at T = 2048: 0.80 in 217 us, 3.5 GB through L2), as a library product of that size does; the sparse form for 0.50 (8192 x 28672:
 // 610 us), bound by the operands' way through L2 (14.3 MB a us, hit rate 0.72) and LDS.  (Eight wavefronts on 256 tokens, one workgroup a compute unit, read less
 // but wait for each other: 266 against 258 us on 8192 x 8192 at T = 2048, 630 against 601 on 11008 x 4096 at 8192.  Four wavefronts
-// of 128 x 128 need 256 accumulator registers, which the compiler moves about: 584 register copies for 256 matrix instructions.)
+// of 128 x 128 need 256 accumulator registers, which the compiler moves about unless asm statements hold them: gemm_square_kernel, for 2:4.)
 constexpr int PN_TOK = 128, PN_XSZ = PN_TOK * 128, PN_LDS = PN_BUFS * PN_XSZ;
 
 // Where a workgroup's X stages come from: 64 columns of its 128 token rows, from X (stages below sx) or the gathered columns.
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void gemm_panel_kernel(const char* __restri
 // 128 each, three stages of X and A' in LDS, the loads of a stage two stages ahead.  256 accumulator registers a wavefront: the matrix
 // instructions are asm statements that keep them in AGPRs (left to the compiler, the loop holds up to 484 register copies).  A lone
 // wavefront issues everything in its one stream, so loads and LDS reads are dealt out one or two behind a matrix instruction.
-// Same order of additions as gemm_panel_kernel: the same bits.  8192 x 28672 at T = 2048: pipes 0.61 busy, the call 673 -> 577 us; 8192 x
+// Same order of additions as gemm_panel_kernel: the same bits.  8192 x 28672 at T = 2048: pipes 0.58 busy, the call 661 -> 581 us; 8192 x
 // 8192 at 2048 175 -> 160, 4096 x 4096 at 4096 99 -> 93.5.  The 32 x 32 x 32 form of the instruction: 583, 161 and 96.  Dense layers gain
 // nothing (8192 x 8192 6:8 at 2048 250 -> 248, 8192 x 8192 4:8 at 8192 798 -> 796, 11008 x 4096 4:8 at 8192 592 -> 616).
 constexpr int SQ_TOK = 256, SQ_X = SQ_TOK * 128, SQ_A = 16384, SQ_STAGE = SQ_X + SQ_A, SQ_BUFS = 3;
