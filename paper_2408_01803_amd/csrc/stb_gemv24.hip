@@ -801,7 +801,8 @@ __device__ __forceinline__ void gemv24_body(const kernarg_ptr layer, const uint1
                 if (w < wa) s += t[w];
             const int row = (ph0 + j) * 16 + 4 * quad;
             if (S == 1) store_y(row, b, s);
-            else asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(ws_part + ((int64_t)ks * 16 + b) * n16 + row), "v"(s) : "memory");
+            // (the compiler does not see a store whose data a vector instruction must not overwrite right behind it: the wait states)
+            else asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(ws_part + ((int64_t)ks * 16 + b) * n16 + row), "v"(s) : "memory");
         }
         if (ph + PHT < R) __syncthreads();           // the next phase overwrites the partial products
     }
