@@ -465,9 +465,15 @@ extern "C" int stb_pack_obc_hybrid(const float* W, const double* Hc, const float
     return rc;
 }
 
-static std::atomic<int> g_override[4] = {{0}, {0}, {0}, {0}};
+static std::atomic<int> g_override[5] = {{0}, {0}, {0}, {0}, {0}};
 
-extern "C" int stb_kernel_override(int which) { return which >= 0 && which < 4 ? g_override[which].load(std::memory_order_relaxed) : 0; }
+extern "C" int stb_kernel_override(int which) { return which >= 0 && which < 5 ? g_override[which].load(std::memory_order_relaxed) : 0; }
+
+extern "C" int stb_set_gemm_tile(int tokens) {
+    if (tokens != 0 && tokens != 64 && tokens != 128 && tokens != 256) return STB_EINVAL;
+    g_override[4].store(tokens, std::memory_order_relaxed);
+    return STB_OK;
+}
 
 extern "C" int stb_set_kernel_override(int32_t gemv_kernel, int32_t gemv_visits, int32_t gemv_splits, int32_t gemm_kernel) {
     if (gemv_kernel < 0 || gemv_kernel > 1 || gemv_visits < 0 || gemv_visits > 8 || gemv_splits < 0 || gemv_splits > 64 ||

@@ -23,8 +23,14 @@ extern "C" {
 // The kernel choices forced by stb_set_kernel_override (stb_device.hip): which = 0 decode kernel (0 automatic,
 // 1 thin wavefronts), 1 superblock visits per wavefront of the decode kernel (0 automatic, 1 .. 8), 2 prefill kernel
 // (0 automatic, 1 dense 16x16x32, 2 dense 32x32x16, 3 sparse 16x16x64, 4 shared expansion, 5 and 6 expanded weights without and
-// with a K split), 3 column splits of the decode kernel (0 automatic).
+// with a K split), 3 column splits of the decode kernel (0 automatic), 4 tokens of a prefill workgroup (stb_set_gemm_tile).
 int stb_kernel_override(int which);
+// Test hook like stb_set_kernel_override, for the tile alone, by the tokens of a workgroup: 0 automatic; 64 dense layers run in the fused kernel's
+// small workgroups at any T; 128 the fused kernels' large workgroups, above 64 tokens, and gemm_panel_kernel; 256 gemm_square_kernel wherever a 2:4
+// layer's expanded weights are multiplied.  The K split stays as it is chosen or forced.
+int stb_set_gemm_tile(int tokens);
+// Tokens of a workgroup of the product that stb_tiled_gemm runs in workspace_bytes bytes: 64 or 128 fused, 128 or 256 expanded.
+int stb_tiled_gemm_tile(const stb_layout_t* L, int T, int y_fp32, int64_t workspace_bytes);
 
 // STB_OK iff the size fields agree with the closed form for L->cfg and every required plane pointer is
 // set and 16-byte aligned.

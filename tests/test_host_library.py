@@ -363,6 +363,28 @@ def test_decode_launch_plan_invariants():
     assert plan(16, 8, 1, 2, 7, 0, out) != 0 and plan(16, 8, 1, 2, 7, 257, out) != 0
 
 
+def _gemm_tile(n, k, N, M, T, salient, fp32=False):
+    """(form, tokens of a workgroup) of a prefill call in the workspace the library asks for."""
+    lib = S.binding._lib()
+    lib.stb_tiled_gemm_tile.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int64]
+    lay = S.stb_tiled_sizes(S.make_cfg(n, k, N, M, int(salient * k), 0))
+    lay.max_sal_half = int(128 * salient)
+    need = S.stb_gemm_workspace_bytes(lay, T)
+    return S.stb_gemm_form(lay, T, fp32, need), lib.stb_tiled_gemm_tile(C.addressof(lay), T, int(fp32), need)
+
+
+@pytest.mark.parametrize("n,k,N,M,T,salient,small", [
+    # measured slower in workgroups of 64 tokens, whose estimate comes near the expanded form's or the large workgroups'
+    (5761, 3200, 4, 8, 647, 0.15, False), (23200, 1920, 4, 8, 701, 0.05, False), (14304, 3840, 3, 8, 566, 0.15, False),
+    (10864, 1664, 6, 8, 381, 0.15, False), (3705, 3200, 6, 8, 643, 0.05, False), (12979, 10624, 5, 8, 185, 0.0, False), (16624, 1408, 3, 8, 116, 0.05, False),
+    # measured faster, with few rows and with many
+    (1024, 4096, 4, 8, 72, 0.05, True), (4096, 4096, 4, 8, 128, 0.05, True), (9952, 2176, 5, 8, 141, 0.05, True), (24923, 1536, 6, 8, 105, 0.05, True), (11344, 3456, 4, 8, 665, 0.05, True)])
+def test_which_dense_prefill_calls_run_in_workgroups_of_64_tokens(n, k, N, M, T, salient, small):
+    form, tile = _gemm_tile(n, k, N, M, T, salient)
+    assert (tile == 64) == small, (form.kernel, tile)
+    assert tile != 64 or form.kernel == S.STB_GEMM_FUSED
+
+
 # ----------------------------------------------------------------------------------------------
 # the 2:4 group code of App. C, out of and into the mask and sign planes
 # ----------------------------------------------------------------------------------------------
