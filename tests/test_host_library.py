@@ -385,6 +385,19 @@ def test_which_dense_prefill_calls_run_in_workgroups_of_64_tokens(n, k, N, M, T,
     assert tile != 64 or form.kernel == S.STB_GEMM_FUSED
 
 
+@pytest.mark.parametrize("n,k,T,salient,tile", [
+    # measured slower in tiles of 256 x 256: several rounds, K groups, many residual columns
+    (6115, 3328, 6848, 0.05, 128), (22655, 3328, 2798, 0.05, 128), (18064, 2816, 8017, 0.05, 128), (7140, 2944, 4509, 0.05, 128), (4082, 2560, 8107, 0.05, 128),
+    (6326, 21632, 1312, 0.05, 128), (8042, 7424, 1224, 0.05, 128), (2000, 11136, 4715, 0.0, 128), (3216, 17024, 1615, 0.05, 128), (624, 26880, 2865, 0.15, 128),
+    (3736, 12800, 2233, 0.15, 128), (3760, 21376, 2493, 0.15, 128), (8538, 2560, 4843, 0.15, 128),
+    # measured faster, whole and in K groups
+    (8192, 28672, 2048, 0.05, 256), (16880, 9984, 2558, 0.05, 256), (2896, 7424, 3866, 0.1, 256), (1664, 8320, 7680, 0.0, 256),
+    (1024, 25728, 5179, 0.0, 256), (1040, 24960, 2906, 0.0, 256), (2847, 28416, 2343, 0.0, 256)])
+def test_which_2of4_products_run_in_tiles_of_256_rows_and_tokens(n, k, T, salient, tile):
+    form, took = _gemm_tile(n, k, 2, 4, T, salient)
+    assert form.kernel == S.STB_GEMM_EXPANDED and took == tile
+
+
 # ----------------------------------------------------------------------------------------------
 # the 2:4 group code of App. C, out of and into the mask and sign planes
 # ----------------------------------------------------------------------------------------------
