@@ -975,6 +975,29 @@ extern "C" int stb_tiled_gemv24_plan(int nrt, int nsb, int B, int mode, int max_
     return STB_OK;
 }
 
+// The launch shape of a layer that has the chip to itself, and the workgroups a compute unit (out[7]).  Few superblocks: a workgroup has a wavefront
+// each, and one a compute unit leaves SIMDs idle.  As many as make eight wavefronts, with fewer row tiles each, where their LDS
+// fits.  Below 4 row tiles a workgroup (6 on the sparse instruction with 3 or 4 superblocks) the further set-ups cost what the
+// wavefronts give: 28672 x 1024 4:8 at 1 and 4 rows of x 11.1 -> 8.2 and 11.4 -> 9.3, 13824 x 2048 6:8 8.8 -> 8.4 and 9.0 -> 8.8, but 8192 x 2048 6:8
+// at 4 rows 7.0 -> 7.4 and 13824 x 2048 2:4 at 16 8.4 -> 8.9.  (Launches of several layers keep one a compute unit: nothing else was tried.)
+extern "C" int stb_tiled_gemv24_plan_alone(int nrt, int nsb, int B, int mode, int max_splits, int* out) {
+    const int rc = stb_tiled_gemv24_plan(nrt, nsb, B, mode, max_splits, 256, out);
+    if (rc != STB_OK) return rc;
+    out[7] = 1;
+    const int R = out[1], SPS = out[2];
+    if (out[0] != 1 || out[3] != 1 || R < (mode == 2 && SPS > 2 ? 6 : 4)) return STB_OK;
+    const int64_t head = LDS24_HEAD + (mode == 2 ? 0 : (int64_t)sizeof(ScatterLds));
+    const int xbytes = (B < 16 ? B + 1 : 16) * 1040;
+    for (int m = 8 / SPS; m > 1; m--) {
+        const int r = (nrt + 256 * m - 1) / (256 * m), pht = r < PHASE24 ? r : PHASE24;
+        const int rec = xbytes > pht * 1024 ? xbytes : pht * 1024;
+        if (m * (head + (int64_t)SPS * (rec + 768) + 256) > 160 * 1024) continue;        // (256: the granule of an allocation)
+        out[1] = r; out[4] = rec + 768; out[5] = rec; out[7] = m;
+        break;
+    }
+    return STB_OK;
+}
+
 // Plans and launches one kernel over n_layers tiled layouts (1 .. GROUP24_MAX) at the same batch; layer l reads xs[l],
 // writes ys[l] and keeps the arrival counters of its column splits at counters[l] (4 bytes per row tile, zero before
 // and after) and their partial sums at partials[l] (partial_bytes[l] bytes).  Returns STB_EUNSUPPORTED, and launches
@@ -1030,22 +1053,10 @@ extern "C" int stb_tiled_gemv24_group(int n_layers, const stb_layout_t* const* L
             d.off_mask = off[0]; d.off_sign = off[1]; d.off_region = off[2]; d.off_scales = off[3];
             d.off_res_scale = off[4]; d.off_res_t = off[5];
         }
-        int plan[7];
-        if (stb_tiled_gemv24_plan(d.p.nrt, d.p.nsb, B, mode, max_splits24(d.p.nsb), cus, plan) != STB_OK) return STB_EUNSUPPORTED;
-        // Few superblocks: a workgroup has a wavefront each, and one a compute unit leaves SIMDs idle.  As many as make eight wavefronts, with
-        // fewer row tiles each, where their LDS fits.  Below 4 row tiles a workgroup (6 on the sparse instruction with 3 or 4
-        // superblocks) the further set-ups cost what the wavefronts give: 28672 x 1024 4:8 at 1 and 4 rows of x 11.1 -> 8.2 and 11.4 -> 9.3,
-        // 13824 x 2048 6:8 8.8 -> 8.4 and 9.0 -> 8.8, but 8192 x 2048 6:8 at 4 rows 7.0 -> 7.4 and 13824 x 2048 2:4 at 16 8.4 -> 8.9.
-        if (n_layers == 1 && plan[0] == 1 && plan[3] == 1 && plan[1] >= (mode == 2 && plan[2] > 2 ? 6 : 4)) {
-            const int64_t head = LDS24_HEAD + (mode == 2 ? 0 : (int64_t)sizeof(ScatterLds));
-            for (int m = 8 / plan[2]; m > 1; m--) {
-                const int r = (d.p.nrt + 256 * m - 1) / (256 * m), pht = r < PHASE24 ? r : PHASE24;
-                const int rec = xbytes > pht * 1024 ? xbytes : pht * 1024;
-                if (m * (head + (int64_t)plan[2] * (rec + 768) + 256) > 160 * 1024) continue;        // (256: the granule of an allocation)
-                plan[1] = r; plan[4] = rec + 768; plan[5] = rec;
-                break;
-            }
-        }
+        int plan[8];
+        const int rc = n_layers == 1 ? stb_tiled_gemv24_plan_alone(d.p.nrt, d.p.nsb, B, mode, max_splits24(d.p.nsb), plan)
+                                     : stb_tiled_gemv24_plan(d.p.nrt, d.p.nsb, B, mode, max_splits24(d.p.nsb), cus, plan);
+        if (rc != STB_OK) return STB_EUNSUPPORTED;
         d.S = plan[0]; d.R = plan[1]; d.SPS = plan[2]; d.V = plan[3]; d.WREG = plan[4]; d.REC_OFF = plan[5]; d.PART_OFF = plan[6];
         d.XS = xbytes;
         d.G = (d.p.nrt + d.R - 1) / d.R;

@@ -363,6 +363,45 @@ def test_decode_launch_plan_invariants():
     assert plan(16, 8, 1, 2, 7, 0, out) != 0 and plan(16, 8, 1, 2, 7, 257, out) != 0
 
 
+def test_decode_launch_plan_of_a_layer_alone():
+    """The shape a launch of one layer takes.  It is the plan for 256 compute units, or, for layers of few superblocks, has several workgroups a
+    unit: together at most eight wavefronts, their LDS fits, no row tile is left out and no workgroup idle, and a wavefront's partial
+    sums (64 bytes a row tile and row of x, of as many row tiles as a phase has) end before its records."""
+    lib = S.binding._lib()
+    alone, plan = lib.stb_tiled_gemv24_plan_alone, lib.stb_tiled_gemv24_plan
+    alone.argtypes = [C.c_int] * 5 + [C.POINTER(C.c_int)]
+    plan.argtypes = [C.c_int] * 6 + [C.POINTER(C.c_int)]
+    alone.restype = plan.restype = C.c_int
+    out, one = (C.c_int * 8)(), (C.c_int * 7)()
+    seen = set()
+    for mode in (2, 4, 6):
+        head = 16 + (0 if mode == 2 else 32768)
+        for nsb in (1, 2, 3, 4, 5, 8, 9, 27):
+            for nrt in list(range(1, 60)) + list(range(250, 270)) + list(range(500, 2400, 7)) + [4000, 16384]:
+                for B in range(1, 17):
+                    rc = alone(nrt, nsb, B, mode, (nsb + 1) // 2 + 3, out)
+                    assert rc == plan(nrt, nsb, B, mode, (nsb + 1) // 2 + 3, 256, one)
+                    if rc != 0:
+                        continue
+                    Sn, R, SPS, V, wreg, rec_off, part_off, m = list(out)
+                    what = (mode, nsb, nrt, B, list(out), list(one))
+                    if V == 1:
+                        fit = min(R, 15) * 16 // B
+                        phase = R if R <= fit else fit // 4 * 4
+                        assert phase >= 1 and part_off == 0 and phase * 64 * B <= rec_off and wreg == rec_off + 768, what
+                        assert rec_off >= (B + 1 if B < 16 else 16) * 1040, what
+                    if m == 1:
+                        assert list(out)[:7] == list(one), what
+                        continue
+                    seen.add((mode, SPS, m))
+                    assert Sn == V == 1 and SPS == nsb and [Sn, SPS, V] == [one[0], one[2], one[3]], what
+                    assert m * SPS <= 8 and m * (head + SPS * wreg + 256) <= 160 * 1024, what
+                    assert R == -(-nrt // (256 * m)) and R * (-(-nrt // R) - 1) < nrt <= R * 256 * m, what
+                    assert one[1] >= (6 if mode == 2 and SPS > 2 else 4), what
+    assert {2, 3, 4} <= {m for _, _, m in seen} and {mode for mode, _, _ in seen} == {2, 4, 6}
+    assert alone(16, 8, 17, 2, 7, out) != 0 and alone(0, 8, 1, 2, 7, out) != 0
+
+
 def _gemm_tile(n, k, N, M, T, salient, fp32=False):
     """(form, tokens of a workgroup) of a prefill call in the workspace the library asks for."""
     lib = S.binding._lib()
