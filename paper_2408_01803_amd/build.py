@@ -45,7 +45,7 @@ def build(verbose: bool = True) -> str:
     # the translation units are independent: compile them side by side (five processes)
     with ThreadPoolExecutor(max_workers=len(cmds)) as pool:
         list(pool.map(_run, cmds))
-    # the loads issued from asm statements must keep their distance from scalar restores (see isa_check)
+    # loads, stores and matrix instructions in asm statements must keep their distance from what the compiler puts around them (see isa_check)
     try:
         from . import isa_check
     except ImportError:                      # run as a script
@@ -59,9 +59,9 @@ def build(verbose: bool = True) -> str:
             if ws < 0:
                 print(f"{src}: {m}: {w}", flush=True)
             else:
-                print(f"{src}.s:{m_line}: '{m}' reads a scalar that '{w}' (line {w_line}) wrote {ws} wait states earlier", flush=True)
+                print(f"{src}.s:{m_line}: '{m}' comes {ws} wait states behind '{w}' (line {w_line}): too close", flush=True)
     if any(found):
-        raise RuntimeError("hazard in the generated code (asm loads): see the lines above")
+        raise RuntimeError("hazard in the generated code (asm statements): see the lines above")
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs, "-pthread"])
     shutil.move(tmp, LIB)

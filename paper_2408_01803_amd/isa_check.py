@@ -18,6 +18,10 @@ with what was there before the load (seen once with a tighter occupancy bound: w
 A register move does the same without a spill: a branch inside a loop with loads in flight (around a rare step, say) made
 the compiler give values new registers ahead of the wait.  `copied_asm_kernels` lists the kernels with such a move.
 
+A third rule is about asm statements that hold a matrix instruction (which the compiler does not see as one, so that its accumulators
+stay where they are put) or a store of 16 bytes: it pads neither, and `asm_matrix_hazards` looks for vector writes
+too close before or behind them and for results touched too early.
+
 `build()` runs the checks on every device source and fails on a finding; tests call them too.
 """
 from __future__ import annotations
@@ -70,11 +74,15 @@ def _wait_states(text: str) -> int:
     return 1
 
 
-def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
-    """Findings as (line of the write, write, line of the memory instruction, memory instruction, wait states between)."""
-    ins: List[Tuple[int, str]] = []
+def _flow(isa_text: str) -> Tuple[List[Tuple[int, str, bool]], List[List[int]]]:
+    """The instructions as (line, text, inside an asm statement), and the predecessors of each."""
+    ins: List[Tuple[int, str, bool]] = []
     labels: Dict[str, int] = {}
+    in_asm = False
     for n, raw in enumerate(isa_text.splitlines(), 1):
+        if raw.strip().startswith(";;#ASM"):
+            in_asm = raw.strip().startswith(";;#ASMSTART")
+            continue
         s = raw.split(";")[0].strip()
         if not s:
             continue
@@ -84,9 +92,9 @@ def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
             continue
         if s.startswith("."):
             continue
-        ins.append((n, s))
+        ins.append((n, s, in_asm))
     preds: List[List[int]] = [[] for _ in ins]
-    for i, (_, s) in enumerate(ins):
+    for i, (_, s, _) in enumerate(ins):
         op = s.split()[0]
         falls = op not in ("s_branch", "s_endpgm", "s_setpc_b64")
         if op == "s_branch" or op.startswith("s_cbranch"):
@@ -95,8 +103,14 @@ def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
                 preds[tgt].append(i)
         if falls and i + 1 < len(ins):
             preds[i + 1].append(i)
+    return ins, preds
+
+
+def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
+    """Findings as (line of the write, write, line of the memory instruction, memory instruction, wait states between)."""
+    ins, preds = _flow(isa_text)
     found = []
-    for i, (ln, s) in enumerate(ins):
+    for i, (ln, s, _) in enumerate(ins):
         op = s.split()[0]
         if not op.startswith(_VMEM):
             continue
@@ -114,7 +128,7 @@ def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
             if ws >= WAIT_STATES or seen.get(j, WAIT_STATES) <= ws:
                 continue
             seen[j] = ws
-            lnj, t = ins[j]
+            lnj, t, _ = ins[j]
             hit = _valu_scalar_writes(t) & need
             if hit:
                 found.append((lnj, t, ln, s, ws))
@@ -122,6 +136,78 @@ def hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
             ws2 = ws + _wait_states(t)
             for k in preds[j]:
                 stack.append((k, ws2))
+    return found
+
+
+_MATRIX = ("v_mfma_", "v_smfmac_")
+OPERAND_STATES = 2          # between a vector write of an operand and the matrix instruction that reads it
+RESULT_STATES = 20          # between a matrix instruction (up to 16 passes) and anything else that touches its result
+STORE_STATES = 2            # between a store of more than 8 bytes and a vector write of its data
+_WIDE_STORE = re.compile(r"(global|flat|buffer|scratch)_store_dwordx[34]\b")
+
+
+def _vector_regs(text: str) -> set:
+    """Vector and accumulation registers named in an operand list, as ("v" or "a", number)."""
+    out = set()
+    for m in re.finditer(r"\b([va])\[(\d+):(\d+)\]|\b([va])(\d+)\b", text):
+        if m.group(1):
+            out |= {(m.group(1), r) for r in range(int(m.group(2)), int(m.group(3)) + 1)}
+        else:
+            out.add((m.group(4), int(m.group(5))))
+    return out
+
+
+def _valu_vector_writes(text: str) -> set:
+    op = text.split()[0]
+    if not op.startswith("v_") or op.startswith(_MATRIX):
+        return set()
+    ops = _operands(text)
+    return _vector_regs(",".join(ops[:2] if op.startswith("v_swap") else ops[:1]))
+
+
+def asm_matrix_hazards(isa_text: str) -> List[Tuple[int, str, int, str, int]]:
+    """The compiler keeps no distance from matrix instructions and wide stores inside asm statements.  Findings, as in `hazards`:
+      * a vector-ALU write of an operand or accumulator of such a matrix instruction less than OPERAND_STATES before it;
+      * anything that reads or writes the result of one less than RESULT_STATES after it, but for the same instruction adding to the
+        same registers again;
+      * a vector-ALU write of the data of such a store of 12 or 16 bytes less than STORE_STATES behind it."""
+    ins, preds = _flow(isa_text)
+    succs: List[List[int]] = [[] for _ in ins]
+    for i, ps in enumerate(preds):
+        for p in ps:
+            succs[p].append(i)
+    found = []
+
+    def near(i, states, way):
+        """(j, wait states between) for what lies less than `states` from i over some path."""
+        stack, seen = [(j, 0) for j in way[i]], {}
+        while stack:
+            j, ws = stack.pop()
+            if ws >= states or seen.get(j, states) <= ws:
+                continue
+            seen[j] = ws
+            stack += [(k, ws + _wait_states(ins[j][1])) for k in way[j]]
+        return sorted(seen.items())
+
+    for i, (ln, s, asm) in enumerate(ins):
+        if not asm:
+            continue
+        if s.startswith(_MATRIX):
+            ops = _operands(s)
+            result, touched = _vector_regs(ops[0]), _vector_regs(",".join(ops))
+            for j, ws in near(i, OPERAND_STATES, preds):
+                if _valu_vector_writes(ins[j][1]) & touched:
+                    found.append((ins[j][0], ins[j][1], ln, s, ws))
+            for j, ws in near(i, RESULT_STATES, succs):
+                t = _operands(ins[j][1])
+                again = ins[j][1].split()[0] == s.split()[0] and t[0] == ops[0] and not result & _vector_regs(",".join(t[1:3]))
+                if not again and result & _vector_regs(",".join(t)):
+                    found.append((ln, s, ins[j][0], ins[j][1], ws))
+        elif _WIDE_STORE.match(s):
+            data = _vector_regs(_operands(s)[0 if s.startswith("buffer") else 1])
+            for j, ws in near(i, STORE_STATES, succs):
+                if _valu_vector_writes(ins[j][1]) & data:
+                    found.append((ln, s, ins[j][0], ins[j][1], ws))
     return found
 
 
@@ -224,10 +310,10 @@ def compile_to_isa(source: str, out_path: str, hipcc: str, flags: List[str]) -> 
 
 
 def check_source(source: str, build_dir: str, hipcc: str, flags: List[str]) -> List[tuple]:
-    """Findings of the three checks for one device source (empty: clean)."""
+    """Findings of the checks for one device source (empty: clean)."""
     out = os.path.join(build_dir, os.path.basename(source) + ".s")
     text = compile_to_isa(source, out, hipcc, flags)
-    return hazards(text) + [(0, f"spills v{regs}", 0, f"kernel {name}: destinations of its asm loads", -1)
+    return hazards(text) + asm_matrix_hazards(text) + [(0, f"spills v{regs}", 0, f"kernel {name}: destinations of its asm loads", -1)
                             for name, regs in spilled_asm_kernels(text)] + \
         [(0, f"copies v{regs}", 0, f"kernel {name}: destinations of its asm loads, ahead of the wait", -1)
          for name, regs in copied_asm_kernels(text)]

@@ -4,6 +4,8 @@ import os
 import re
 from concurrent.futures import ThreadPoolExecutor
 
+import pytest
+
 from paper_2408_01803_amd import build as stb_build
 from paper_2408_01803_amd import isa_check
 
@@ -156,6 +158,49 @@ def test_a_move_of_a_register_that_an_asm_load_still_writes_is_found():
 
 def test_moves_of_other_registers_and_after_the_wait_are_no_finding():
     assert isa_check.copied_asm_kernels(COPIES_THAT_ARE_FINE) == []
+
+
+def _asm(text):
+    return f"\t;;#ASMSTART\n\t{text}\n\t;;#ASMEND\n"
+
+
+MATRIX = _asm("v_smfmac_f32_16x16x64_f16 a[0:3], v[4:7], v[8:15], v16")
+
+
+@pytest.mark.parametrize("before,found", [
+    ("v_mov_b32_e32 v16, v20\n", True), ("v_mov_b32_e32 v16, v20\n\ts_nop 0\n", True), ("v_mov_b32_e32 v16, v20\n\ts_nop 1\n", False),
+    ("v_add_u32_e32 v8, v1, v2\n", True), ("v_accvgpr_write_b32 a2, 0\n", True), ("v_add_u32_e32 v17, v4, v5\n", False),
+    ("ds_read_b128 v[4:7], v1\n\ts_waitcnt lgkmcnt(0)\n", False),                         # (waited for, as the compiler does)
+    ("s_cbranch_scc1 .LBB0_1\n\tv_mov_b32_e32 v4, 0\n.LBB0_1:\n", True)])
+def test_vector_writes_right_ahead_of_a_matrix_instruction_in_an_asm_statement(before, found):
+    got = isa_check.asm_matrix_hazards("kernel:\n\t" + before + MATRIX + "\ts_endpgm\n")
+    assert len(got) == found, got
+    # the compiler pads the matrix instructions that it sees
+    assert isa_check.asm_matrix_hazards("kernel:\n\t" + before + MATRIX.split("\n")[1] + "\n\ts_endpgm\n") == []
+
+
+@pytest.mark.parametrize("behind,found", [
+    ("\tv_accvgpr_read_b32 v1, a3\n", True), ("\ts_nop 15\n\tv_accvgpr_read_b32 v1, a3\n", True), ("\ts_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 v1, a3\n", False),
+    ("\tv_accvgpr_read_b32 v1, a4\n", False), ("\tv_accvgpr_write_b32 a0, 0\n", True), ("\tglobal_store_dwordx4 v1, a[0:3], s[4:5]\n", True),
+    (MATRIX, False),                                                                         # adds to the same registers again
+    (_asm("v_smfmac_f32_16x16x64_f16 a[2:5], v[4:7], v[8:15], v16"), True), (_asm("v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], a[0:3]"), True),
+    (_asm("v_smfmac_f32_16x16x64_f16 a[0:3], a[0:3], v[8:15], v16"), True)])
+def test_results_of_a_matrix_instruction_in_an_asm_statement_that_are_touched_too_early(behind, found):
+    got = isa_check.asm_matrix_hazards("kernel:\n" + MATRIX + behind + "\ts_endpgm\n")
+    assert (len(got) > 0) == found, got
+
+
+def test_a_loop_back_to_another_kind_of_matrix_instruction_is_followed():
+    other = _asm("v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], a[0:3]")
+    assert len(isa_check.asm_matrix_hazards("kernel:\n.LBB0_1:\n" + other + "\ts_nop 15\n\ts_nop 15\n" + MATRIX + "\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n")) == 1
+
+
+@pytest.mark.parametrize("store,behind,found", [
+    ("global_store_dwordx4 v[0:1], v[4:7], off sc1", "\tv_mov_b32_e32 v6, 0\n", True), ("global_store_dwordx4 v[0:1], v[4:7], off sc1", "\tv_mov_b32_e32 v0, 0\n", False),
+    ("global_store_dwordx4 v[0:1], v[4:7], off sc1\n\ts_nop 1", "\tv_mov_b32_e32 v6, 0\n", False), ("global_store_dwordx2 v[0:1], v[4:5], off", "\tv_mov_b32_e32 v4, 0\n", False),
+    ("buffer_store_dwordx4 v[4:7], v0, s[0:3], 0 offen", "\ts_nop 0\n\tv_add_u32_e32 v7, v1, v2\n", True)])
+def test_data_of_a_wide_store_in_an_asm_statement_that_is_overwritten_right_behind_it(store, behind, found):
+    assert len(isa_check.asm_matrix_hazards("kernel:\n" + _asm(store) + behind + "\ts_endpgm\n")) == found
 
 
 def test_the_device_sources_of_the_package_are_clean(tmp_path):
