@@ -4,6 +4,7 @@ Bars: packed bytes and dequantised fp32 weights bit-exact; outputs within
 |y_gpu - y_oracle| <= 2e-3 * sum_j |x_j| |W_hat_ij| (and exactly 0 where that bound is 0).
 """
 import contextlib
+import ctypes as C
 import hashlib
 import json
 import os
@@ -934,62 +935,29 @@ def test_gemm_on_expanded_weights(n, k, N, M, T, sal, torch_cuda):
                     assert (np.abs(outs[0] - y_ref) <= 1e-5 * bound + 1e-12).all()
 
 
-@pytest.mark.parametrize("n,k,T,every", [(1104, 4096, 6945, 20), (2151, 3328, 4066, 0), (9754, 5376, 999, 17), (4868, 8064, 838, 20), (3632, 13440, 762, 0)])
-def test_gemm_2of4_in_tiles_of_256_rows_and_tokens(n, k, T, every, torch_cuda):
-    """Shapes whose expanded 2:4 product runs in tiles of 256 x 256 by the library's own choice: rows and tokens past the last full tile, an
-    odd number of 128-column blocks, with and without salient columns (every `every`-th), whole and in 3 or 5 K groups, twice with the
-    same bits.  Against float64 on the dequantised weights (an fp32 sum of k exact products is off by less than k 2^-24 of the sum of
-    magnitudes), and the bits of the other tiles, which add in the same order."""
-    torch = torch_cuda
-    _say(f"[case] 2:4 gemm in square tiles {n}x{k} T={T} every {every}")
-    g = torch.Generator(device="cuda").manual_seed(n + T)
-    W = torch.randn((n, k), generator=g, device="cuda") * 0.02
-    bits = np.zeros(k, dtype=np.uint8)
-    if every:
-        bits[::every] = 1
-    bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
-    cfg = S.make_cfg(n, k, 2, 4, int(bits.sum()), 1)
-    rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
-    img, timg = S.new_device_scratch(rm.image_bytes), S.new_device_scratch(tl.image_bytes)
-    S.stb_layout_bind(rm, img.data_ptr())
-    S.stb_layout_bind(tl, timg.data_ptr())
-    S.stb_pack_device(W, torch.rand(k, generator=g, device="cuda") + 0.5, bitmap, rm, False, S.new_device_scratch(S.stb_pack_device_workspace_bytes(cfg)))
-    S.stb_tile_device(rm, tl)
-    What = torch.empty((n, k), dtype=torch.float32, device="cuda")
-    S.stb_dequant(rm, What)
-    x = torch.randn((T, k), generator=g, device="cuda").half()
-    ref = x.double() @ What.double().t()
-    bound = x.double().abs() @ What.double().abs().t()
-    for fp32 in (True, False):
-        form = S.stb_gemm_form(tl, T, fp32)
-        assert form.kernel == S.STB_GEMM_EXPANDED
-        outs = []
-        for asked in (0, 0) + ((S.GEMM_WHOLE,) if form.k_groups == 1 else ()):
-            with forced(gemm_kernel=asked):
-                ws = S.new_device_scratch(form.workspace_bytes)
-                ws.fill_(0xFF)
-                y = torch.full((T, n), float("nan"), dtype=torch.float32 if fp32 else torch.float16, device="cuda")
-                S.stb_gemm(tl, x, T, y, fp32, ws)
-                torch.cuda.synchronize()
-                outs.append(y)
-        slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
-        assert bool(((outs[0].double() - ref).abs() <= slack).all()), fp32
-        for y in outs[1:]:
-            assert bool((y.view(torch.int32 if fp32 else torch.int16) == outs[0].view(torch.int32 if fp32 else torch.int16)).all()), fp32
+@contextlib.contextmanager
+def prefill_tile(tokens):
+    """The tile of a prefill workgroup, asked for through the library's internal test hook."""
+    lib = S.binding._lib()
+    assert lib.stb_set_gemm_tile(tokens) == S.STB_OK
+    try:
+        yield
+    finally:
+        lib.stb_set_gemm_tile(0)
 
 
-@pytest.mark.parametrize("n,k,N,M,T", [(1030, 1536, 4, 8, 65), (1001, 1152, 5, 8, 127), (1356, 3328, 4, 8, 331), (2049, 5120, 6, 8, 129), (1210, 1536, 3, 8, 768), (1024, 8192, 6, 8, 100)])
-def test_gemm_of_small_dense_layers_in_small_workgroups(n, k, N, M, T, torch_cuda):
-    """Small layers at more than 64 tokens, which run in workgroups of 64 tokens: tokens and rows past the last full tile, up to twelve token
-    tiles, K groups.  Against float64 on the dequantised weights: an fp32 sum of k exact products is off by less than k 2^-24 of the
-    sum of magnitudes, an fp16 output by half a last place more; and the bits do not change from call to call."""
-    torch = torch_cuda
-    _say(f"[case] gemm in small workgroups {n}x{k} {N}:{M} T={T}")
-    g = torch.Generator(device="cuda").manual_seed(n + T)
+def _tile_that_runs(layout, T, fp32, workspace_bytes):
+    lib = S.binding._lib()
+    lib.stb_tiled_gemm_tile.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int64]
+    return lib.stb_tiled_gemm_tile(C.addressof(layout), T, int(fp32), workspace_bytes)
+
+
+def _layer_packed_on_the_gpu(torch, n, k, N, M, salient, seed):
+    """(layout, its image, dequantised fp32 weights) of a random layer whose salient columns are those given."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
     W = torch.randn((n, k), generator=g, device="cuda") * 0.02
     bits = np.zeros(k, dtype=np.uint8)
-    bits[::19] = 1
-    bits[130:170] = 1
+    bits[salient] = 1
     bitmap = torch.from_numpy(np.packbits(bits, bitorder="little").view(np.int32).copy()).cuda()
     cfg = S.make_cfg(n, k, N, M, int(bits.sum()), 1)
     rm, tl = S.stb_layout_sizes(cfg), S.stb_tiled_sizes(cfg)
@@ -1000,21 +968,94 @@ def test_gemm_of_small_dense_layers_in_small_workgroups(n, k, N, M, T, torch_cud
     S.stb_tile_device(rm, tl)
     What = torch.empty((n, k), dtype=torch.float32, device="cuda")
     S.stb_dequant(rm, What)
-    x = torch.randn((T, k), generator=g, device="cuda").half()
+    torch.cuda.synchronize()
+    return tl, timg, What
+
+
+@pytest.mark.parametrize("n,k,T,salient", [
+    (1104, 4096, 6945, range(0, 4096, 20)), (2151, 3328, 4066, []), (9754, 5376, 999, range(0, 5376, 17)), (4868, 8064, 838, range(0, 8064, 20)), (3632, 13440, 762, []),
+    (1, 128, 1, []), (16, 128, 255, range(128)), (17, 256, 257, [0, 130]),   # one pair of stages, less than a tile either way
+    (255, 1408, 130, range(0, 1408, 9)), (257, 2048, 513, range(2048)), (300, 640, 31, range(100, 300))])
+def test_gemm_2of4_in_tiles_of_256_rows_and_tokens(n, k, T, salient, torch_cuda):
+    """The expanded 2:4 product in tiles of 256 x 256: rows and tokens short of a tile and past the last full one, an odd number of 128-column
+    blocks, without salient columns and with up to all of them, whole, in as many K groups as there are (the last of which may hold residual
+    columns alone) and in the split that the call takes by itself, twice with the same bits.  Against float64 on the dequantised weights
+    (an fp32 sum of k exact products, and one more a salient column, is off by less than 2^-24 of the sum of magnitudes for each), and in every
+    split the bits of the other tiles, which add in the same order."""
+    torch = torch_cuda
+    _say(f"[case] 2:4 gemm in square tiles {n}x{k} T={T} salient {len(salient)}")
+    tl, _img, What = _layer_packed_on_the_gpu(torch, n, k, 2, 4, list(salient), n + T)
+    x = torch.randn((T, k), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda").half()
+    ref = x.double() @ What.double().t()
+    bound = x.double().abs() @ What.double().abs().t()
+    pairs = (k + -(-len(salient) // 128) * 128) // 128
+    splits = set()
+    for asked in (S.GEMM_WHOLE, S.GEMM_WHOLE_SPLIT, 0):
+        for fp32 in (True, False):
+            outs = {}
+            for tile in (256, 128):
+                with forced(gemm_kernel=asked), prefill_tile(tile):
+                    form = S.stb_gemm_form(tl, T, fp32)
+                    if form.kernel != S.STB_GEMM_EXPANDED:
+                        assert asked == 0
+                        continue
+                    assert _tile_that_runs(tl, T, fp32, form.workspace_bytes) == tile
+                    splits.add(form.k_groups)
+                    if asked:
+                        assert form.k_groups == (1 if asked == S.GEMM_WHOLE else -(-pairs // -(-pairs // 16)))
+                    for again in range(2 if tile == 256 else 1):
+                        ws = S.new_device_scratch(form.workspace_bytes)
+                        ws.fill_(0xFF)
+                        y = torch.full((T * n + 16,), 7.0, dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+                        S.stb_gemm(tl, x, T, y[:T * n], fp32, ws)
+                        torch.cuda.synchronize()
+                        assert bool((y[T * n:] == 7.0).all())
+                        outs[tile, again] = y[:T * n].view(T, n)
+            if not outs:
+                continue
+            slack = (k + len(salient)) * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+            assert bool(((outs[256, 0].double() - ref).abs() <= slack).all()), (asked, fp32)
+            bits = {key: y.contiguous().view(torch.int32 if fp32 else torch.int16) for key, y in outs.items()}
+            assert bool((bits[256, 0] == bits[256, 1]).all()) and bool((bits[256, 0] == bits[128, 0]).all()), (asked, fp32, form.k_groups)
+    assert pairs == 1 or max(splits) > 1
+
+
+@pytest.mark.parametrize("n,k,N,M,T,every,split", [
+    (1030, 1536, 4, 8, 65, 19, True), (1001, 1152, 5, 8, 127, 19, True), (1356, 3328, 4, 8, 331, 19, True), (2049, 5120, 6, 8, 129, 19, True), (1210, 1536, 3, 8, 768, 19, True),
+    (1024, 8192, 6, 8, 100, 19, True),
+    (7656, 896, 3, 8, 245, 0, False), (7656, 896, 4, 8, 245, 19, False), (9001, 640, 6, 8, 197, 0, False), (16401, 1152, 6, 8, 141, 19, False), (20000, 512, 5, 8, 130, 0, False),
+    (3000, 896, 3, 8, 705, 0, False), (11344, 3456, 4, 8, 665, 19, False), (2049, 2560, 5, 8, 193, 0, True)])
+def test_gemm_of_small_dense_layers_in_small_workgroups(n, k, N, M, T, every, split, torch_cuda):
+    """Dense layers at more than 64 tokens in workgroups of 64 tokens, few rows and many: tokens and rows past the last full tile, up to twelve token
+    tiles, with and without salient columns (every `every`-th and a cluster), in K groups and not (fp16 outputs; fp32 ones may be split further).  They are
+    asked for (which calls take them by themselves is the host library's test); the form that runs is asserted.
+    Against float64 on the dequantised weights: an fp32 sum of k exact products, and one more a salient column, is off by less than 2^-24 of
+    the sum of magnitudes for each, an fp16 output by half a last place more; and the bits do not change from call to call."""
+    torch = torch_cuda
+    _say(f"[case] gemm in small workgroups {n}x{k} {N}:{M} T={T}")
+    salient = sorted({*range(0, k, every), *range(130, 170)}) if every else []
+    tl, _img, What = _layer_packed_on_the_gpu(torch, n, k, N, M, salient, n + T)
+    x = torch.randn((T, k), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda").half()
     ref = x.double() @ What.double().t()
     bound = x.double().abs() @ What.double().abs().t()
     for fp32 in (True, False):
         outs = []
         for _ in range(2):
-            ws = S.new_device_scratch(S.stb_gemm_workspace_bytes(tl, T))
-            ws.fill_(0xFF)
-            buf = torch.full((T * n + 16,), 7.0, dtype=torch.float32 if fp32 else torch.float16, device="cuda")
-            S.stb_gemm(tl, x, T, buf[:T * n], fp32, ws)
-            torch.cuda.synchronize()
+            with prefill_tile(64):
+                need = S.stb_gemm_workspace_bytes(tl, T)
+                form = S.stb_gemm_form(tl, T, fp32, need)
+                assert form.kernel == S.STB_GEMM_FUSED and _tile_that_runs(tl, T, fp32, need) == 64
+                assert fp32 or (form.k_groups > 1) == split
+                ws = S.new_device_scratch(need)
+                if ws is not None:
+                    ws.fill_(0xFF)
+                buf = torch.full((T * n + 16,), 7.0, dtype=torch.float32 if fp32 else torch.float16, device="cuda")
+                S.stb_gemm(tl, x, T, buf[:T * n], fp32, ws)
+                torch.cuda.synchronize()
             assert bool((buf[T * n:] == 7.0).all())
             outs.append(buf)
         y = outs[0][:T * n].view(T, n)
-        slack = k * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
+        slack = (k + len(salient)) * 2.0 ** -24 * bound + (0.0 if fp32 else 2.0 ** -11 * ref.abs() + 2.0 ** -24)
         assert bool(((y.double() - ref).abs() <= slack).all()), fp32
         assert bool((outs[0] == outs[1]).all())
 
