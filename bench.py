@@ -187,7 +187,8 @@ def gemm_kernel_name(S, spec, layout, T):
     sparse = (spec.N, spec.M) == (2, 4)
     split = f", {form.k_groups} K groups" if form.k_groups > 1 else ""
     if form.kernel == S.STB_GEMM_EXPANDED:
-        return f"gemm_panel_kernel ({'v_smfmac_f32_16x16x64_f16' if sparse else 'v_mfma_f32_16x16x32_f16'}{split}) on weights that gemm_prepare_kernel expands"
+        kernel = "gemm_square_kernel" if S.binding.gemm_tile(layout, T) == 256 else "gemm_panel_kernel"
+        return f"{kernel} ({'v_smfmac_f32_16x16x64_f16' if sparse else 'v_mfma_f32_16x16x32_f16'}{split}) on weights that gemm_prepare_kernel expands"
     if sparse:
         return f"gemm24_kernel (v_smfmac_f32_16x16x64_f16{split})" if T <= 64 else f"gemm24_wide_kernel (v_smfmac_f32_32x32x32_f16{split})"
     return f"gemm_tiled_kernel (v_mfma_f32_16x16x32_f16{split})"

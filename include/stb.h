@@ -394,7 +394,8 @@ int64_t stb_gemv_batched_workspace_bytes(int32_t n_layers, const stb_cfg_t* cons
  * Where a (tokens x rows) tile per workgroup would not fill the chip, or not whole rounds of it, the columns are dealt to up to 16
  * groups of workgroups that each leave an fp32 partial tile in the workspace, and a second kernel adds the partial tiles in a
  * fixed order: the result is reproducible, and equal to the unsplit one up to fp32 summation order.  fp32 outputs are split
- * further where that shortens the sums of an idle chip, so an fp16 output need not be the rounded fp32 one of another call.
+ * further where that shortens the sums of an idle chip; for fp16 ones, whose rounding is hundreds of times an fp32 sum's, the fastest split is
+ * taken, also where its sums run over all columns.  So an fp16 output need not be the rounded fp32 one of another call.
  * X: device fp16 [T][k], finite values (a padding column or token re-reads valid elements of X and meets zero
  * weights or an output that is never stored).  Y: device [T][n], fp16 or fp32, fully overwritten.  workspace: device scratch of at
  * least stb_gemm_workspace_bytes() bytes, 256-byte aligned (may be NULL when that is 0); it needs no

@@ -447,6 +447,13 @@ def stb_gemm_form(layout: stb_layout_t, T: int, y_fp32: bool = False, workspace_
     return out
 
 
+def gemm_tile(layout: stb_layout_t, T: int, y_fp32: bool = False, workspace_bytes: int = 2 ** 63 - 1) -> int:
+    """Tokens of a workgroup of the product that stb_gemm runs on a tiled layout (not part of the C ABI: for tests and measurements)."""
+    lib = _lib()
+    lib.stb_tiled_gemm_tile.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int64]
+    return lib.stb_tiled_gemm_tile(C.addressof(layout), T, int(y_fp32), workspace_bytes)
+
+
 def stb_gemm(layout_dev: stb_layout_t, X_dev, T: int, Y_dev, y_fp32: bool = False, workspace=None,
              stream=None) -> None:
     ws_ptr, ws_bytes = _ws(workspace)

@@ -749,7 +749,8 @@ __global__ __launch_bounds__(64 * SC_WAVES, 4) void k_search_gain(PK a, int step
     for (int j = 0; j < PER; j++) { g_t[j] = 0.0; n_t[j] = 0; }
     unsigned long long* const hist = hists[wave];
     unsigned long long* const bins = hist + (lane >> 3);       // of the row whose weights the lane holds
-    // the row and the part of its bins and candidates that the lane takes (8 rows next to each other: no two lanes share a bank)
+    // the row and the part of its bins and candidates that the lane takes (8 rows next to each other: in the
+    // suffix sums no two lanes share a bank; the candidates' reads, whose bins repeat modulo 4, do)
     const int part = lane >> 3;
     unsigned long long* const row = hist + (lane & 7);
     __syncthreads();

@@ -4,7 +4,6 @@ Bars: packed bytes and dequantised fp32 weights bit-exact; outputs within
 |y_gpu - y_oracle| <= 2e-3 * sum_j |x_j| |W_hat_ij| (and exactly 0 where that bound is 0).
 """
 import contextlib
-import ctypes as C
 import hashlib
 import json
 import os
@@ -946,12 +945,6 @@ def prefill_tile(tokens):
         lib.stb_set_gemm_tile(0)
 
 
-def _tile_that_runs(layout, T, fp32, workspace_bytes):
-    lib = S.binding._lib()
-    lib.stb_tiled_gemm_tile.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int64]
-    return lib.stb_tiled_gemm_tile(C.addressof(layout), T, int(fp32), workspace_bytes)
-
-
 def _layer_packed_on_the_gpu(torch, n, k, N, M, salient, seed):
     """(layout, its image, dequantised fp32 weights) of a random layer whose salient columns are those given."""
     g = torch.Generator(device="cuda").manual_seed(seed)
@@ -999,7 +992,7 @@ def test_gemm_2of4_in_tiles_of_256_rows_and_tokens(n, k, T, salient, torch_cuda)
                     if form.kernel != S.STB_GEMM_EXPANDED:
                         assert asked == 0
                         continue
-                    assert _tile_that_runs(tl, T, fp32, form.workspace_bytes) == tile
+                    assert S.binding.gemm_tile(tl, T, fp32, form.workspace_bytes) == tile
                     splits.add(form.k_groups)
                     if asked:
                         assert form.k_groups == (1 if asked == S.GEMM_WHOLE else -(-pairs // -(-pairs // 16)))
@@ -1044,7 +1037,7 @@ def test_gemm_of_small_dense_layers_in_small_workgroups(n, k, N, M, T, every, sp
             with prefill_tile(64):
                 need = S.stb_gemm_workspace_bytes(tl, T)
                 form = S.stb_gemm_form(tl, T, fp32, need)
-                assert form.kernel == S.STB_GEMM_FUSED and _tile_that_runs(tl, T, fp32, need) == 64
+                assert form.kernel == S.STB_GEMM_FUSED and S.binding.gemm_tile(tl, T, fp32, need) == 64
                 assert fp32 or (form.k_groups > 1) == split
                 ws = S.new_device_scratch(need)
                 if ws is not None:

@@ -404,12 +404,10 @@ def test_decode_launch_plan_of_a_layer_alone():
 
 def _gemm_tile(n, k, N, M, T, salient, fp32=False):
     """(form, tokens of a workgroup) of a prefill call in the workspace the library asks for."""
-    lib = S.binding._lib()
-    lib.stb_tiled_gemm_tile.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int64]
     lay = S.stb_tiled_sizes(S.make_cfg(n, k, N, M, int(salient * k), 0))
     lay.max_sal_half = int(128 * salient)
     need = S.stb_gemm_workspace_bytes(lay, T)
-    return S.stb_gemm_form(lay, T, fp32, need), lib.stb_tiled_gemm_tile(C.addressof(lay), T, int(fp32), need)
+    return S.stb_gemm_form(lay, T, fp32, need), S.binding.gemm_tile(lay, T, fp32, need)
 
 
 @pytest.mark.parametrize("n,k,N,M,T,salient,small", [
